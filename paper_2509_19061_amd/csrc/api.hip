@@ -229,11 +229,17 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
         return STK_OK;
     }
 
+    // Jacobi in either form, and RAS whose overlap covers its sweeps, are all exactly
+    // `total` Jacobi sweeps: passes of as many sweeps as the pipelined kernel runs best.
+    const bool ras = variant == STK_RAS_JACOBI;
+    const int total = ras && !o.last_partial ? nouter * o.k : sweeps;
+    const bool piped = jacobi_pipe_takes(dt, g) && (!ras || (ctx->ras_kernel == 0 && h >= o.k - 1));
+    const int kp = piped ? jacobi_pipe_sweeps(ctx, dt, g, total) : 0;
+
     // Out-of-place steps: the first reads the caller's arrays, the last writes them, and the
     // ones between alternate over two scratch pairs, so no copy is needed for n >= 2 steps
     // (two buffers alone would end an odd count in scratch).
-    const bool ras = !(variant == STK_JACOBI_FUSED || variant == STK_JACOBI);
-    const int n = ras ? nouter : sweeps;
+    const int n = piped ? (total + kp - 1) / kp : ras ? nouter : sweeps;
     void *tx = nullptr, *ty = nullptr, *ux = nullptr, *uy = nullptr;
     STK_TRY(scratch(ctx, stk_ctx::S_VX, vbytes, &tx));
     STK_TRY(scratch(ctx, stk_ctx::S_VY, vbytes, &ty));
@@ -242,6 +248,7 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
         STK_TRY(scratch(ctx, stk_ctx::S_VY2, vbytes, &uy));
     }
     const void *cx = vx, *cy = vy;  // current iterate
+    int left = total;
     for (int t = 0; t < n; ++t) {
         void *dx = tx, *dy = ty;  // next
         if (t == n - 1 && n >= 2) {
@@ -251,9 +258,11 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
             dx = ux;
             dy = uy;
         }
-        if (variant == STK_JACOBI_FUSED) {
-            STK_TRY(launch_jacobi_fused(ctx, dt, g, f, omega, cx, cy, dx, dy));
-        } else if (variant == STK_JACOBI) {
+        if (piped) {
+            const int kt = (left + (n - t) - 1) / (n - t);  // equal passes
+            STK_TRY(launch_jacobi_pipe(ctx, dt, g, f, omega, kt, cx, cy, dx, dy));
+            left -= kt;
+        } else if (!ras) {
             STK_TRY(launch_jacobi_split(ctx, dt, g, f, omega, cx, cy, dx, dy));
         } else {
             int kt = o.k;

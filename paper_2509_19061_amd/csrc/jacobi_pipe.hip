@@ -1,0 +1,152 @@
+// K damped Jacobi sweeps per pass over memory (jacobi_pipe.hpp): the kernel of
+// every smoother that equals plain Jacobi (Sec. 5 (ii), (iii); RAS, Sec. 4.3,
+// with an overlap of at least k - 1, whose values do not depend on the tiles).
+#include <algorithm>
+
+#include "jacobi_pipe.hpp"
+#include "stk_internal.hpp"
+
+namespace stk {
+namespace {
+
+using namespace pipe;
+
+// Waves per SIMD the registers must leave room for.
+template <typename T>
+constexpr int pipe_occupancy(int K) { return sizeof(T) == 8 ? (K <= 3 ? 3 : K <= 7 ? 2 : 1) : (K <= 4 ? 4 : K <= 8 ? 3 : 2); }
+
+template <typename T, int K, bool SQ>
+__global__ __launch_bounds__(64 * WPB, pipe_occupancy<T>(K)) void k_jacobi_pipe(Grid<T> g, const T* __restrict__ vx,
+                                                                               const T* __restrict__ vy,
+                                                                               T* __restrict__ ox, T* __restrict__ oy,
+                                                                               Shape sh) {
+    const int wv = xcd_tile((int)blockIdx.x, (int)gridDim.x) * WPB + rows::wave_in_group();
+    const int strip_ = wv % sh.nstrip, segm = wv / sh.nstrip;
+    if (segm >= sh.nseg) return;  // the whole wave
+    const int nx = g.nx, ny = g.ny, lane = threadIdx.x & 63;
+    const int i = strip_ * strip(K) - K + lane, y0 = segm * sh.seg, y1 = min(y0 + sh.seg, ny + 1);
+    const rows::Loader<T> L = rows::make_loader<T>(vx, vy, g.ec, g.en, g.bx, g.by, nullptr, g.ld, nx, ny, i);
+    const bool own = lane >= K && lane < 64 - K && i <= nx;
+    const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
+    const unsigned col = (unsigned)i * (unsigned)sizeof(T);
+    const unsigned s_x = own ? col : OOB, s_y = own && ycol ? col : OOB;
+    walk<T, K, SQ>(L, y0, sh.seg, i, g.omega, g.idx, g.idy, [&](int j, T ux, T uy) {
+        const bool in = j >= y0 && j < y1;
+        const int64_t o = (int64_t)j * g.ld;
+        const bool xu = xcol && j <= ny - 1, yu = ycol && j >= 1 && j <= ny - 1;
+        buf_store(xu ? ux : T(0), buf_rsrc(ox + o, in && j <= ny - 1 ? (size_t)(nx + 1) * sizeof(T) : 0), s_x);
+        buf_store(yu ? uy : T(0), buf_rsrc(oy + o, in ? (size_t)nx * sizeof(T) : 0), s_y);
+    });
+}
+
+// Time of one step of one wave that has the SIMD to itself, in us: about 217
+// (FP64, K = 7) or 180 (FP32, K = 8) vector instructions; measured 0.48 and
+// 0.30 (2048^2, two waves per SIMD).
+template <typename T>
+double step_us(int K) { return sizeof(T) == 8 ? 2.2e-3 * (30 + 27 * K) : 1.6e-3 * (44 + 17 * K); }
+
+// Launch shape: about w waves per SIMD, w = 1, 2, ..., each a segment of equal
+// rows (rounded so that the walk is a whole number of unrolled trips).  The
+// waves of a SIMD share its issue slots, so a launch takes about (waves per
+// SIMD) x (rows walked + 2K rows that fill the pipeline); a single wave leaves
+// some of them unused (FP64 x 1.1, FP32 x 1.35: 2048^2, K = 7, one or two
+// waves per SIMD, 69 / 66 us and 56 / 45 us).  *us: that time.
+template <typename T>
+Shape pipe_shape(const stk_ctx* ctx, int nx, int ny, int K, double* us) {
+    const int U = ring_rows<T>(K);
+    const int64_t ns = (nx + 1 + strip(K) - 1) / strip(K), cu4 = (int64_t)std::max(ctx->num_cu, 1) * 4;
+    Shape best{K, (int)ns, 0, 0};
+    double cost = 1e300;
+    for (int w = 1; w <= pipe_occupancy<T>(K); ++w) {
+        const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(w * cu4 / ns, ny + 1));
+        const int steps = ((int)((ny + 1 + segs - 1) / segs) + 2 * K + U - 1) / U * U, H = steps - 2 * K;
+        const int64_t nseg = (ny + 1 + H - 1) / H, per_simd = (ns * nseg + cu4 - 1) / cu4;
+        const double c = (steps + 4) * std::max(sizeof(T) == 8 ? 1.1 : 1.35, (double)per_simd);
+        if (c < cost) {
+            cost = c;
+            best.nseg = (int)nseg;
+            best.seg = H;
+        }
+    }
+    if (us) *us = cost * step_us<T>(K);
+    return best;
+}
+
+// Sweeps per pass for `left` sweeps in all: the count whose passes, equal in
+// size, take the least time.  A pass takes the longest of its steps and its
+// eight planes at 5 TB/s (measured 4.6 to 5.0), and 3 us between launches.
+// FP64 stops at 7, where two waves per SIMD still fit their registers (8: one
+// wave, 283 us against 247 us for 7 at 4096^2, no faster per sweep), FP32 at 10.
+template <typename T>
+int pick_sweeps(const stk_ctx* ctx, const stk_grid* g, int left) {
+    const int kmax = sizeof(T) == 8 ? 7 : 10;
+    const double mem = 8.0 * sizeof(T) * g->nx * g->ny / 5e6;
+    int best = 1, last = 0;
+    double cost = 1e300;
+    for (int m = (left + kmax - 1) / kmax; m <= left; ++m) {
+        const int K = (left + m - 1) / m;
+        if (K == last) continue;
+        last = K;
+        double us = 0.0;
+        pipe_shape<T>(ctx, g->nx, g->ny, K, &us);
+        const double c = m * (std::max(us, mem) + 3.0);
+        if (c < cost) {
+            cost = c;
+            best = K;
+        }
+        if (K == 1) break;
+    }
+    return best;
+}
+
+template <typename T, int K>
+int launch_k(stk_ctx* ctx, const Grid<T>& g, const T* vx, const T* vy, T* ox, T* oy) {
+    const Shape sh = pipe_shape<T>(ctx, g.nx, g.ny, K, nullptr);
+    const dim3 grid((unsigned)(((int64_t)sh.nstrip * sh.nseg + WPB - 1) / WPB)), block(64 * WPB);
+    if (g.idx == g.idy)
+        hipLaunchKernelGGL((k_jacobi_pipe<T, K, true>), grid, block, 0, ctx->stream, g, vx, vy, ox, oy, sh);
+    else
+        hipLaunchKernelGGL((k_jacobi_pipe<T, K, false>), grid, block, 0, ctx->stream, g, vx, vy, ox, oy, sh);
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+
+template <typename T>
+int launch_t(stk_ctx* ctx, const stk_grid* g, const FieldPtrs& f, double omega, int K, const void* vx, const void* vy,
+             void* ox, void* oy) {
+    const Grid<T> gg{static_cast<const T*>(f.eta_c), static_cast<const T*>(f.eta_n), static_cast<const T*>(f.bx),
+                     static_cast<const T*>(f.by), g->ld, g->nx, g->ny, T(1.0 / g->dx), T(1.0 / g->dy), T(omega)};
+    const T *a = static_cast<const T*>(vx), *b = static_cast<const T*>(vy);
+    T *c = static_cast<T*>(ox), *d = static_cast<T*>(oy);
+    switch (K) {
+        case 1: return launch_k<T, 1>(ctx, gg, a, b, c, d);
+        case 2: return launch_k<T, 2>(ctx, gg, a, b, c, d);
+        case 3: return launch_k<T, 3>(ctx, gg, a, b, c, d);
+        case 4: return launch_k<T, 4>(ctx, gg, a, b, c, d);
+        case 5: return launch_k<T, 5>(ctx, gg, a, b, c, d);
+        case 6: return launch_k<T, 6>(ctx, gg, a, b, c, d);
+        case 7: return launch_k<T, 7>(ctx, gg, a, b, c, d);
+        case 8: return launch_k<T, 8>(ctx, gg, a, b, c, d);
+        case 9: return launch_k<T, 9>(ctx, gg, a, b, c, d);
+        case 10: return launch_k<T, 10>(ctx, gg, a, b, c, d);
+        default: return set_error(STK_EINVAL, "internal: %d sweeps in one pass", K);
+    }
+}
+
+}  // namespace
+
+bool jacobi_pipe_takes(stk_dtype dt, const stk_grid* g) {
+    return ((int64_t)g->nx + 1) * (int64_t)elem_size(dt) < INT32_MAX && g->ny < INT32_MAX - 4096;
+}
+
+int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int left) {
+    return dt == STK_F64 ? pick_sweeps<double>(ctx, g, left) : pick_sweeps<float>(ctx, g, left);
+}
+
+int launch_jacobi_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int sweeps,
+                       const void* vx, const void* vy, void* ox, void* oy) {
+    return dt == STK_F64 ? launch_t<double>(ctx, g, f, omega, sweeps, vx, vy, ox, oy)
+                         : launch_t<float>(ctx, g, f, omega, sweeps, vx, vy, ox, oy);
+}
+
+}  // namespace stk

@@ -1,0 +1,178 @@
+// Temporally blocked damped Jacobi with the sweeps pipelined in registers.
+//
+// A wave owns a strip of 64 - 2K columns and a segment of rows; its 64 lanes
+// hold the strip and K columns on each side, and it walks up the rows once for
+// K sweeps.  When row r arrives from memory, sweep level 1 relaxes row r - 1,
+// level 2 row r - 2 and so on: each level needs one row ahead of the level
+// below, which that level has just produced, so all K levels advance by one
+// row per step with nothing but registers between them.  There is no LDS and
+// no barrier, and waves never wait for each other.  A level's values are exact
+// one column and one row further in than the level below, so the K columns at
+// either side and the first K rows of the walk are discarded.
+//
+// Work per level and cell.  The operator's differences are shared: the shear
+// strain of node (i, j) serves the rows j - 1 and j of vx and the columns
+// i - 1 and i of vy, the normal differences both neighbours of a cell.  Each is
+// formed once, in the shared expression order (stencil.hpp), and carried to
+// the next row in a register or to the next column by DPP, which leaves 18 or
+// 19 floating-point operations and 8 moves per cell and sweep; the values are
+// bit for bit those of the gathering kernels.  The coefficients of a row
+// (A, N and their neighbours, b, omega / d) are formed once, when it arrives,
+// and live in a register ring of K + 2 rows until the last level has passed.
+//
+// Cells that are not relaxed (walls, outside the grid) carry omega / d = 0.
+//
+// What bounds it: the eight planes of memory traffic up to K = 5 (4096^2 FP64:
+// 0.22 - 0.23 ms a pass whatever K is, 4.6 - 4.9 TB/s of the 5.8 a flat stream
+// of the same planes reaches), then vector issue.  Against the LDS pipeline
+// with one wave per level that ran these sweeps before (4096^2): FP64 k = 4
+// 0.238 -> 0.232 ms a pass, and 0.246 ms for K = 7 (480 GLUP/s against 284);
+// FP32 0.156 ms for k = 4 -> 0.122, and 0.156 for K = 8 (860 against 520).
+#pragma once
+
+#include "rowstream.hpp"
+
+namespace stk {
+namespace pipe {
+
+constexpr int WPB = 4;  // waves per workgroup (independent)
+// rows loaded ahead of the walk
+template <typename T>
+constexpr int ahead() { return sizeof(T) == 8 ? 2 : 4; }
+
+// Rows of the coefficient ring, and steps per unrolled trip (the ring slots,
+// the load queue and the carried rows rotate by renaming): K + 2, made a
+// multiple of the load queue.
+template <typename T>
+constexpr int ring_rows(int K) { return (K + 1 + ahead<T>()) / ahead<T>() * ahead<T>(); }
+__host__ __device__ constexpr int strip(int K) { return 64 - 2 * K; }
+
+// Launch geometry of one grid: strips x segments waves of `seg` rows each
+// (seg + 2K is a multiple of the unrolled trip).
+struct Shape {
+    int K, nstrip, nseg, seg;
+};
+
+// One row's coefficients at the lane's column: A = 2 eta_c idx^2 at (i, j) and
+// (i - 1, j), N = eta_n idx idy at (i, j) and (i + 1, j), the right-hand side
+// and the Jacobi factors of vx(i, j) and vy(i, j).
+template <typename T>
+struct Coef {
+    T A, aL, N, nR, bx, by, gx, gy;
+};
+// A level's carried state, of the level below it at row j: v, the node strains
+// of row j (S scaled for vx, Q for vy), and vy(j) - vy(j - 1).
+template <typename T>
+struct State {
+    T vx, vy, S, Q, ey;
+};
+
+// Level update at row j from the state (row j) and the new row j + 1 of the
+// level below (nx, ny); c: the coefficients of row j, nR: N(i + 1, j), Ab:
+// A(i, j - 1), Nt: N(i, j + 1).
+template <typename T, bool SQ>
+__device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c, T nR, T Ab, T Nt, const Scale<T>& sc,
+                                      T& ux, T& uy) {
+    const T a = nx - s.vx;
+    const T d = ny - wave_shift<DPP_FROM_PREV>(ny);
+    const T S1 = SQ ? a + d : fmaT(sc.ry, a, d);
+    const T Q1 = SQ ? S1 : fmaT(sc.rx, d, a);
+    const T ey = ny - s.vy;
+    const T ex = wave_shift<DPP_FROM_NEXT>(s.vx) - s.vx;
+    const T exl = wave_shift<DPP_FROM_PREV>(ex);
+    const T Qr = wave_shift<DPP_FROM_NEXT>(s.Q);
+    T mx = c.A * ex;
+    mx = fmaT(-c.aL, exl, mx);
+    mx = fmaT(Nt, S1, mx);
+    mx = fmaT(-c.N, s.S, mx);
+    T B = c.A, Bb = Ab;
+    if (!SQ) {
+        // B = A kap is formed by every level: an opaque copy of the (scalar) kap
+        // keeps the compiler from holding B of all the ring's rows in registers
+        Scale<T> sk = sc;
+        asm volatile("" : "+s"(sk.kap));
+        B = coef_b(c.A, sk);
+        Bb = coef_b(Ab, sk);
+    }
+    T my = B * ey;
+    my = fmaT(-Bb, s.ey, my);
+    my = fmaT(nR, Qr, my);
+    my = fmaT(-c.N, s.Q, my);
+    ux = jac_step<T>(s.vx, c.gx, c.bx, mx);
+    uy = jac_step<T>(s.vy, c.gy, c.by, my);
+    s.vx = nx;
+    s.vy = ny;
+    s.S = S1;
+    s.Q = Q1;
+    s.ey = ey;
+}
+
+// K sweeps of the wave's strip and segment; put(j, ux, uy) receives row j of
+// the last level for y0 <= j < y0 + seg, rows past the grid included.
+// SQ: square cells (ry = rx = kap = 1 exactly, so B = A and the two strains
+// are the same sum).
+template <typename T, int K, bool SQ, typename PUT>
+__device__ __forceinline__ void walk(const rows::Loader<T>& L, int y0, int seg, int i, T omega, T idx, T idy,
+                                     const PUT& put) {
+    constexpr int R = ring_rows<T>(K), U = R, PFD = ahead<T>();
+    // many FP64 sweeps on cells that are not square: N(i + 1, j) is taken again
+    // by each level rather than kept in the ring, so that 256 registers do
+    constexpr bool KEEP_NR = SQ || sizeof(T) == 4 || K <= 5;
+    const int nx = L.nx, ny = L.ny;
+    const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
+    const Scale<T> sv = stencil_scale(idx, idy);
+    const Scale<T> sc{wave_uniform(sv.a), wave_uniform(sv.n), wave_uniform(sv.kap), wave_uniform(sv.ry),
+                      wave_uniform(sv.rx)};
+    State<T> st[K];
+    Coef<T> cf[R];
+#pragma unroll
+    for (int s = 0; s < K; ++s) st[s] = State<T>{T(0), T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < R; ++q) cf[q] = Coef<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    const int r0 = y0 - K, r1 = y0 + seg + K;  // rows loaded: r0 .. r1 - 1
+    rows::Row<T> q[PFD];
+#pragma unroll
+    for (int p = 0; p < PFD; ++p) q[p] = L.load(r0 + p);
+    for (int rb = r0; rb < r1; rb += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = rb + u;
+            const rows::Row<T> w = q[u % PFD];
+            q[u % PFD] = L.load(r + PFD);
+            Coef<T>& c0 = cf[u];                 // row r
+            Coef<T>& c1 = cf[(u + R - 1) % R];   // row r - 1
+            const Coef<T>& c2 = cf[(u + R - 2) % R];
+            c0.A = coef_a(w.ec, sc);
+            c0.N = coef_n(w.en, sc);
+            c0.aL = wave_shift<DPP_FROM_PREV>(c0.A);
+            if (KEEP_NR) c0.nR = wave_shift<DPP_FROM_NEXT>(c0.N);
+            c0.bx = w.bx;
+            c0.by = w.by;
+            {  // the factors of row r - 1, whose upper shear coefficient is now here
+                const int j = r - 1;
+                const T dx = SQ ? (c1.N + c0.N) + (c1.aL + c1.A) : diagx_scaled<T>(c1.aL, c1.A, c1.N, c0.N, sc.ry);
+                const T nR = KEEP_NR ? c1.nR : wave_shift<DPP_FROM_NEXT>(c1.N);
+                const T dy = SQ ? (c1.N + nR) + (c2.A + c1.A)
+                                : diagy_scaled<T>(coef_b(c2.A, sc), coef_b(c1.A, sc), c1.N, nR, sc.rx);
+                const T gx = jac_factor(omega, dx), gy = jac_factor(omega, dy);
+                c1.gx = (xcol && j >= 0 && j <= ny - 1) ? gx : T(0);
+                c1.gy = (ycol && j >= 1 && j <= ny - 1) ? gy : T(0);
+            }
+            T ux = w.vx, uy = w.vy;
+#pragma unroll
+            for (int s = 1; s <= K; ++s) {  // level s: row r - s
+                const Coef<T>& c = cf[(u + 2 * R - s) % R];
+                const T Ab = cf[(u + 2 * R - s - 1) % R].A, Nt = cf[(u + 2 * R - s + 1) % R].N;
+                const T nR = KEEP_NR ? c.nR : wave_shift<DPP_FROM_NEXT>(c.N);
+                T vx, vy;
+                level<T, SQ>(st[s - 1], ux, uy, c, nR, Ab, Nt, sc, vx, vy);
+                ux = vx;
+                uy = vy;
+            }
+            put(r - K, ux, uy);
+        }
+    }
+}
+
+}  // namespace pipe
+}  // namespace stk

@@ -1,6 +1,7 @@
-// Smoother kernels for gfx950: fused / split damped Jacobi, red-black
-// Gauss-Seidel and RAS-type temporally blocked Jacobi (paper Sec. 4, Sec. 5,
-// Alg. 2), plus the right-hand-side fold b = f - G p and a velocity copy.
+// Smoother kernels for gfx950: split damped Jacobi (rows too long for the
+// pipelined kernel of jacobi_pipe.hip), red-black Gauss-Seidel and RAS-type
+// temporally blocked Jacobi (paper Sec. 4, Sec. 5, Alg. 2), plus the
+// right-hand-side fold b = f - G p and a velocity copy.
 #include <algorithm>
 
 #include "stencil.hpp"
@@ -265,13 +266,6 @@ int launch_fold_rhs(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* f
     return STK_OK;
 }
 
-// Fused Jacobi (one pass updates vx and vy of a cell, Sec. 4.1): the
-// row-streaming kernel (rowstream.hip).
-int launch_jacobi_fused(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
-                        const void* vx, const void* vy, void* ox, void* oy) {
-    return launch_jacobi_rows(ctx, dt, g, f, omega, vx, vy, ox, oy);
-}
-
 int launch_jacobi_split(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
                         const void* vx, const void* vy, void* ox, void* oy) {
     const dim3 grid = cell_grid(g), block(BX, BY);
@@ -338,6 +332,9 @@ int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f
     if (lds > (size_t)ctx->lds_max)
         return set_error(STK_EUNSUPPORTED, "RAS tile %dx%d with halo %d needs %zu bytes of LDS (limit %d)", tile_x,
                          tile_y, halo, lds, ctx->lds_max);
+    // full overlap is exactly kt Jacobi sweeps, wherever the tiles are cut
+    if (ctx->ras_kernel == 0 && kt >= 1 && kt <= PIPE_MAX_SWEEPS && halo >= kt - 1 && jacobi_pipe_takes(dt, g))
+        return launch_jacobi_pipe(ctx, dt, g, f, omega, kt, vx, vy, ox, oy);
     if (ctx->ras_kernel != 1) {
         bool done = false;
         STK_TRY(launch_ras_stream(ctx, dt, g, f, omega, tile_x, tile_y, halo, kt, sx, sy, vx, vy, ox, oy, &done));

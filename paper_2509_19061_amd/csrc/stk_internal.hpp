@@ -78,10 +78,17 @@ int launch_fold_rhs(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* f
 int launch_residual_to32(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
                          const double* eta_c, const double* eta_n, const double* fx, const double* fy, float* r32x,
                          float* r32y, float* z32x, float* z32y);
-int launch_jacobi_rows(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
+// K = `sweeps` damped Jacobi sweeps in one pass over memory (1 <= K <=
+// PIPE_MAX_SWEEPS), out of place; every velocity entry of the used extents is
+// written (walls 0).
+constexpr int PIPE_MAX_SWEEPS = 10;
+// Its rows are addressed through 32-bit buffer offsets: false where a row is
+// 2 GiB or longer.
+bool jacobi_pipe_takes(stk_dtype dt, const stk_grid* g);
+// Sweeps of the next pass when `left` are to be done.
+int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int left);
+int launch_jacobi_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int sweeps,
                        const void* vx, const void* vy, void* ox, void* oy);
-int launch_jacobi_fused(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
-                        const void* vx, const void* vy, void* ox, void* oy);
 int launch_jacobi_split(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
                         const void* vx, const void* vy, void* ox, void* oy);
 int launch_zero_walls(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy);
