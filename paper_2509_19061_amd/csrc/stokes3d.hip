@@ -20,7 +20,7 @@
 //                smoother and the residual call the same row functions, so
 //                RAS with an overlap >= k - 1 is bit-identical to k Jacobi
 //                sweeps.
-//   k_jacobi3d_z the same sweep with the velocity staged plane by plane: a
+//   k_walk3d     the same sweep with the velocity staged plane by plane: a
 //                64 x 4 workgroup walks up a segment of z-planes with a ring
 //                of four planes (the planes k - 1, k, k + 1 it reads, and
 //                k + 2, loaded meanwhile) of the three components in LDS,
@@ -33,8 +33,10 @@
 //                two buffers), k sweeps run there with a barrier between
 //                sweeps, the owned unknowns are written back; coefficients
 //                and right-hand side come from global memory (L2).
-//   k_energy3d   per-workgroup FP64 sums of r^2/d and f^2/d, summed in a
-//                fixed order by a second kernel (reproducible).
+//                The residual and the norms' sums take the same walk.
+//   k_energy3d   per-workgroup FP64 sums of r^2/d and f^2/d (arrays beyond 2^32
+//                bytes), summed in a fixed order by a second kernel
+//                (reproducible).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -323,11 +325,21 @@ __device__ __forceinline__ Coef3<T> coef3_load(const Fields3<T>& f, uint32_t q, 
     return c;
 }
 
-template <typename T>
-__global__ __launch_bounds__(ZNT) void k_jacobi3d_z(Fields3<T> f, T omega, const T* __restrict__ vx,
-                                                     const T* __restrict__ vy, const T* __restrict__ vz,
-                                                     T* __restrict__ ox, T* __restrict__ oy, T* __restrict__ oz,
-                                                     int ntx, int nty) {
+__device__ __forceinline__ double wsum3(double v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_down(v, o, 64);
+    return v;
+}
+
+// What a walk does with the operator values of a cell: a damped Jacobi sweep, the
+// residual r = b - M v, or the norms' sums of r^2/d and b^2/d (FP64, per workgroup).
+enum { Z_JACOBI = 0, Z_RESIDUAL, Z_ENERGY };
+
+template <typename T, int OP>
+__global__ __launch_bounds__(ZNT) void k_walk3d(Fields3<T> f, T omega, const T* __restrict__ vx,
+                                                 const T* __restrict__ vy, const T* __restrict__ vz,
+                                                 T* __restrict__ ox, T* __restrict__ oy, T* __restrict__ oz,
+                                                 double* __restrict__ part, int ntx, int nty) {
     __shared__ T ring[4 * ZSLOT];
     const int nx = f.nx, ny = f.ny, nz = f.nz;
     // tiles numbered x fastest, then y, then z segments, renumbered by XCD
@@ -375,6 +387,7 @@ __global__ __launch_bounds__(ZNT) void k_jacobi3d_z(Fields3<T> f, T omega, const
     c.b0 = at_b(f.exz, q);
     c.c0 = at_b(f.eyz, q);
     const RingV<T> v{ring, i0, j0};
+    double nv = 0.0, nf = 0.0;
     for (int k = k0; k < k1; ++k, q += slp) {
         load(k + 2, r);  // in flight while plane k is relaxed
         Coef3<T> n = coef3_load<T>(f, k + 1 < k1 ? q + slp : q, dxm, dym, sld, slp);
@@ -385,25 +398,58 @@ __global__ __launch_bounds__(ZNT) void k_jacobi3d_z(Fields3<T> f, T omega, const
         const T sxy = xi0 && yj0 ? c.a0 : T(0), sxy_y = xi0 && yj1 ? c.a1 : T(0), sxy_x = xi1 && yj0 ? c.a2 : T(0);
         const T sxz = xi0 && kz0 ? c.b0 : T(0), sxz_z = xi0 && kz1 ? c.b1 : T(0), sxz_x = xi1 && kz0 ? c.b2 : T(0);
         const T syz = yj0 && kz0 ? c.c0 : T(0), syz_z = yj0 && kz1 ? c.c1 : T(0), syz_y = yj1 && kz0 ? c.c2 : T(0);
-        T d;
-        const T mx = mvx3c<T>(f, v, i, j, k, Row3<T>{c.ecx, c.ec, sxy, sxy_y, sxz, sxz_z}, d);
-        const T nvx = jac_step<T>(v(0, i, j, k), omega / d, c.bx, mx);
-        const T my = mvy3c<T>(f, v, i, j, k, Row3<T>{c.ecy, c.ec, sxy, sxy_x, syz, syz_z}, d);
-        const T nvy = jac_step<T>(v(1, i, j, k), omega / d, c.by, my);
-        const T mz = mvz3c<T>(f, v, i, j, k, Row3<T>{c.ecz, c.ec, sxz, sxz_x, syz, syz_y}, d);
-        const T nvz = jac_step<T>(v(2, i, j, k), omega / d, c.bz, mz);
-        if (act) {
-            put_b(ox, q, xi0 ? nvx : T(0));  // vx(0) is a wall
-            put_b(oy, q, yj0 ? nvy : T(0));  // vy(0)
-            put_b(oz, q, kz0 ? nvz : T(0));  // vz(0)
-            if (i == nx - 1) put_b(ox, q + es, T(0));
-            if (j == ny - 1) put_b(oy, q + sld, T(0));
-            if (k == nz - 1) put_b(oz, q + slp, T(0));
+        T dx, dy, dz;
+        const T mx = mvx3c<T>(f, v, i, j, k, Row3<T>{c.ecx, c.ec, sxy, sxy_y, sxz, sxz_z}, dx);
+        const T my = mvy3c<T>(f, v, i, j, k, Row3<T>{c.ecy, c.ec, sxy, sxy_x, syz, syz_z}, dy);
+        const T mz = mvz3c<T>(f, v, i, j, k, Row3<T>{c.ecz, c.ec, sxz, sxz_x, syz, syz_y}, dz);
+        if constexpr (OP == Z_ENERGY) {
+            auto add = [&](bool in, T b, T m, T d) {  // a cell that holds no unknown adds 0
+                const double r = (double)b - (double)m, w = in ? 1.0 / (double)d : 0.0;
+                nv += in ? r * r * w : 0.0;
+                nf += in ? (double)b * (double)b * w : 0.0;
+            };
+            add(act && xi0, c.bx, mx, dx);
+            add(act && yj0, c.by, my, dy);
+            add(act && kz0, c.bz, mz, dz);
+        } else {
+            T ux, uy, uz;
+            if constexpr (OP == Z_JACOBI) {
+                ux = jac_step<T>(v(0, i, j, k), omega / dx, c.bx, mx);
+                uy = jac_step<T>(v(1, i, j, k), omega / dy, c.by, my);
+                uz = jac_step<T>(v(2, i, j, k), omega / dz, c.bz, mz);
+            } else {
+                ux = c.bx - mx;
+                uy = c.by - my;
+                uz = c.bz - mz;
+            }
+            if (act) {
+                put_b(ox, q, xi0 ? ux : T(0));  // vx(0) is a wall
+                put_b(oy, q, yj0 ? uy : T(0));  // vy(0)
+                put_b(oz, q, kz0 ? uz : T(0));  // vz(0)
+                if (i == nx - 1) put_b(ox, q + es, T(0));
+                if (j == ny - 1) put_b(oy, q + sld, T(0));
+                if (k == nz - 1) put_b(oz, q + slp, T(0));
+            }
         }
         c = n;
         // slot (k + 2) & 3 held plane k - 2, last read in the previous step
         zwin_store<T>(ring, k + 2, r);
         __syncthreads();
+    }
+    if constexpr (OP == Z_ENERGY) {
+        __shared__ double red[2][ZNT / 64];
+        nv = wsum3(nv);
+        nf = wsum3(nf);
+        if ((threadIdx.x & 63) == 0) {
+            red[0][threadIdx.x >> 6] = nv;
+            red[1][threadIdx.x >> 6] = nf;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double sum = 0.0;
+            for (int q2 = 0; q2 < ZNT / 64; ++q2) sum += red[threadIdx.x][q2];
+            part[2 * (int64_t)t + threadIdx.x] = sum;
+        }
     }
 }
 
@@ -503,12 +549,6 @@ __global__ __launch_bounds__(J3X* J3Y) void k_residual3d(Fields3<T> f, const T* 
     if (k < nz && j < ny) rx[q] = vx_unknown3(nx, ny, nz, i, j, k) ? f.bx[q] - mvx3<T>(f, v, i, j, k, d) : T(0);
     if (k < nz && i < nx) ry[q] = vy_unknown3(nx, ny, nz, i, j, k) ? f.by[q] - mvy3<T>(f, v, i, j, k, d) : T(0);
     if (j < ny && i < nx) rz[q] = vz_unknown3(nx, ny, nz, i, j, k) ? f.bz[q] - mvz3<T>(f, v, i, j, k, d) : T(0);
-}
-
-__device__ __forceinline__ double wsum3(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;
 }
 
 // Per-workgroup (N_v, N_f) partial sums in FP64, f = b: one workgroup per (x-y tile, plane).
@@ -623,21 +663,65 @@ int check_grid3(const stk_grid3* g) {
     return STK_OK;
 }
 
+// Workgroups of the plane-streaming kernels, 0 where they cannot take the grid:
+// they address each array by 32-bit byte offsets.
+template <typename T>
+int64_t walk3d_groups(const stk_grid3* g) {
+    const int64_t ntx = (g->nx + ZX - 1) / ZX, nty = (g->ny + ZY - 1) / ZY, ntz = (g->nz + ZS - 1) / ZS;
+    const int64_t nwg = ntx * nty * ntz;
+    return nwg < INT32_MAX && (uint64_t)(g->nz + 1) * (uint64_t)g->lp * sizeof(T) <= UINT32_MAX ? nwg : 0;
+}
+template <typename T, int OP>
+void walk3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, int64_t nwg, double omega, const void* vx,
+            const void* vy, const void* vz, void* ox, void* oy, void* oz, void* part) {
+    hipLaunchKernelGGL((k_walk3d<T, OP>), dim3((unsigned)nwg), dim3(ZX * ZY), 0, ctx->stream, f, T(omega),
+                       static_cast<const T*>(vx), static_cast<const T*>(vy), static_cast<const T*>(vz),
+                       static_cast<T*>(ox), static_cast<T*>(oy), static_cast<T*>(oz), static_cast<double*>(part),
+                       (g->nx + ZX - 1) / ZX, (g->ny + ZY - 1) / ZY);
+}
+
 template <typename T>
 int launch_jacobi3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, double omega, const void* vx,
                     const void* vy, const void* vz, void* ox, void* oy, void* oz) {
-    const int ntx = (g->nx + ZX - 1) / ZX, nty = (g->ny + ZY - 1) / ZY, ntz = (g->nz + ZS - 1) / ZS;
-    const int64_t nwg = (int64_t)ntx * nty * ntz;
-    // the plane-streaming sweep addresses each array by 32-bit byte offsets
-    if (nwg < INT32_MAX && (uint64_t)(g->nz + 1) * (uint64_t)g->lp * sizeof(T) <= UINT32_MAX) {
-        hipLaunchKernelGGL(k_jacobi3d_z<T>, dim3((unsigned)nwg), dim3(ZX * ZY), 0, ctx->stream, f, T(omega),
-                           static_cast<const T*>(vx), static_cast<const T*>(vy), static_cast<const T*>(vz),
-                           static_cast<T*>(ox), static_cast<T*>(oy), static_cast<T*>(oz), ntx, nty);
+    if (const int64_t nwg = walk3d_groups<T>(g)) {
+        walk3d<T, Z_JACOBI>(ctx, g, f, nwg, omega, vx, vy, vz, ox, oy, oz, nullptr);
     } else {
         hipLaunchKernelGGL(k_jacobi3d<T>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream, f, T(omega),
                            static_cast<const T*>(vx), static_cast<const T*>(vy), static_cast<const T*>(vz),
                            static_cast<T*>(ox), static_cast<T*>(oy), static_cast<T*>(oz));
     }
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+
+template <typename T>
+int launch_residual3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
+                      const void* vz, void* rx, void* ry, void* rz) {
+    if (const int64_t nwg = walk3d_groups<T>(g)) {
+        walk3d<T, Z_RESIDUAL>(ctx, g, f, nwg, 1.0, vx, vy, vz, rx, ry, rz, nullptr);
+    } else {
+        hipLaunchKernelGGL(k_residual3d<T>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream, f, (const T*)vx, (const T*)vy,
+                           (const T*)vz, (T*)rx, (T*)ry, (T*)rz);
+    }
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+
+// (N_v, N_f) into red[0..1] (device memory), from per-workgroup partial sums.
+template <typename T>
+int launch_energy3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
+                    const void* vz, double* red) {
+    const int64_t nwg = walk3d_groups<T>(g);
+    const dim3 gr = grid3(g);
+    const int64_t npart = nwg ? nwg : (int64_t)gr.x * gr.y * gr.z;
+    void* part = nullptr;
+    STK_TRY(scratch(ctx, stk_ctx::S_PART, sizeof(double) * 2 * (size_t)npart, &part));
+    if (nwg)
+        walk3d<T, Z_ENERGY>(ctx, g, f, nwg, 1.0, vx, vy, vz, nullptr, nullptr, nullptr, part);
+    else
+        hipLaunchKernelGGL(k_energy3d<T>, gr, dim3(J3X, J3Y), 0, ctx->stream, f, (const T*)vx, (const T*)vy,
+                           (const T*)vz, (double*)part);
+    hipLaunchKernelGGL(k_energy3d_final, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, npart, red);
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
@@ -731,10 +815,15 @@ int stk_smooth3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, void* vx, void*
     static const int slots[6] = {stk_ctx::S_VX, stk_ctx::S_VY, stk_ctx::S_VX2, stk_ctx::S_VY2, stk_ctx::S_BX,
                                  stk_ctx::S_BY};
     for (int q = 0; q < 6; ++q) STK_TRY(scratch(ctx, slots[q], fb, &t[q]));
-    const int k = variant == STK_RAS_JACOBI ? o.k : 1;
+    // RAS with an overlap of at least k - 1 is exactly its sweeps of Jacobi, wherever the
+    // tiles are cut (the frozen ring, at distance k, enters only exact values), and a sweep
+    // of the plane-streaming kernel costs a seventh of a tile's: 87 against 610 us at
+    // 160 x 144 x 150 in FP64.
+    const bool tiles = variant == STK_RAS_JACOBI && o.halo >= 0 && o.halo < o.k - 1;
+    const int k = tiles ? o.k : 1;
     const int nsteps = (sweeps + k - 1) / k;
     std::vector<int32_t> sh;
-    if (variant == STK_RAS_JACOBI) {
+    if (tiles) {
         sh.resize(3 * (size_t)nsteps);
         if (o.shifts) {
             for (size_t q = 0; q < sh.size(); ++q) sh[q] = o.shifts[q] % o.tile;
@@ -764,10 +853,10 @@ int stk_smooth3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, void* vx, void*
         const int kt = std::min(k, left);
         left -= kt;
         int rc;
-        if (variant == STK_RAS_JACOBI) {
-            const int h = o.halo < 0 ? kt : o.halo;
+        if (tiles) {
             rc = stk_ras_outer3d(ctx, dt, g, src[0], src[1], src[2], eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz, dst[0],
-                                 dst[1], dst[2], o.omega, o.tile, h, kt, sh[3 * st], sh[3 * st + 1], sh[3 * st + 2]);
+                                 dst[1], dst[2], o.omega, o.tile, o.halo, kt, sh[3 * st], sh[3 * st + 1],
+                                 sh[3 * st + 2]);
         } else if (dt == STK_F64) {
             rc = launch_jacobi3d<double>(ctx, g, fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), o.omega,
                                          src[0], src[1], src[2], dst[0], dst[1], dst[2]);
@@ -795,15 +884,10 @@ int stk_residual3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, const void* v
         return set_error(STK_EINVAL, "NULL array");
     STK_TRY(use_device(ctx));
     if (dt == STK_F64)
-        hipLaunchKernelGGL(k_residual3d<double>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream,
-                           fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), (const double*)vx,
-                           (const double*)vy, (const double*)vz, (double*)rx, (double*)ry, (double*)rz);
-    else
-        hipLaunchKernelGGL(k_residual3d<float>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream,
-                           fields3<float>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), (const float*)vx,
-                           (const float*)vy, (const float*)vz, (float*)rx, (float*)ry, (float*)rz);
-    STK_HIP(hipGetLastError());
-    return STK_OK;
+        return launch_residual3d<double>(ctx, g, fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), vx, vy,
+                                         vz, rx, ry, rz);
+    return launch_residual3d<float>(ctx, g, fields3<float>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), vx, vy, vz,
+                                    rx, ry, rz);
 }
 
 int stk_energy_norm3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, const void* vx, const void* vy, const void* vz,
@@ -815,22 +899,14 @@ int stk_energy_norm3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, const void
     if (!vx || !vy || !vz || !eta_c || !eta_xy || !eta_xz || !eta_yz || !fx || !fy || !fz || !out)
         return set_error(STK_EINVAL, "NULL argument");
     STK_TRY(use_device(ctx));
-    const dim3 gr = grid3(g);
-    const int64_t nblk = (int64_t)gr.x * gr.y * gr.z;
-    void *part = nullptr, *red = nullptr;
-    STK_TRY(scratch(ctx, stk_ctx::S_PART, sizeof(double) * 2 * (size_t)nblk, &part));
+    void* red = nullptr;
     STK_TRY(scratch(ctx, stk_ctx::S_RED, 64 * sizeof(double), &red));
     if (dt == STK_F64)
-        hipLaunchKernelGGL(k_energy3d<double>, gr, dim3(J3X, J3Y), 0, ctx->stream,
-                           fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, fx, fy, fz), (const double*)vx,
-                           (const double*)vy, (const double*)vz, (double*)part);
+        STK_TRY(launch_energy3d<double>(ctx, g, fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, fx, fy, fz), vx, vy,
+                                        vz, (double*)red));
     else
-        hipLaunchKernelGGL(k_energy3d<float>, gr, dim3(J3X, J3Y), 0, ctx->stream,
-                           fields3<float>(g, eta_c, eta_xy, eta_xz, eta_yz, fx, fy, fz), (const float*)vx,
-                           (const float*)vy, (const float*)vz, (double*)part);
-    hipLaunchKernelGGL(k_energy3d_final, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, nblk,
-                       (double*)red);
-    STK_HIP(hipGetLastError());
+        STK_TRY(launch_energy3d<float>(ctx, g, fields3<float>(g, eta_c, eta_xy, eta_xz, eta_yz, fx, fy, fz), vx, vy,
+                                       vz, (double*)red));
     STK_HIP(hipMemcpyAsync(ctx->host_red, red, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     STK_HIP(hipStreamSynchronize(ctx->stream));
     out[0] = ctx->host_red[0];
