@@ -16,6 +16,7 @@
 
 #include "coarse_stencil.hpp"
 #include "mg_internal.hpp"
+#include "mg_transfer.hpp"
 #include "rowstream.hpp"
 #include "stencil.hpp"
 
@@ -278,24 +279,6 @@ __global__ __launch_bounds__(NT) void k_mg_residual(const LevelJob<T>* __restric
 }
 
 // --------------------------------------------------------------- transfers --
-// Weights of a fine index f on coarse indices along one axis (see header):
-// normal axis: f even -> f/2 (1); f odd -> (f-1)/2, (f+1)/2 (1/2 each).
-// tangential axis: J = f/2 with 3/4, neighbour J-1 (f even) or J+1 (f odd)
-// with 1/4, the neighbour mirrored onto J outside [0, nc).
-__device__ __forceinline__ int w_normal(int f, int* c, double* w) {
-    if ((f & 1) == 0) { c[0] = f >> 1; w[0] = 1.0; return 1; }
-    c[0] = (f - 1) >> 1; w[0] = 0.5;
-    c[1] = (f + 1) >> 1; w[1] = 0.5;
-    return 2;
-}
-__device__ __forceinline__ int w_tangent(int f, int nc, int* c, double* w) {
-    const int J = f >> 1, nb = (f & 1) ? J + 1 : J - 1;
-    if (nb < 0 || nb >= nc) { c[0] = J; w[0] = 1.0; return 1; }
-    c[0] = J; w[0] = 0.75;
-    c[1] = nb; w[1] = 0.25;
-    return 2;
-}
-
 // coarse rhs = R r = P^T r / 4, gathered per coarse unknown from the fine
 // unknowns that prolongate from it; the coarse iterate is set to 0 in the same
 // pass (the coarse problem is solved for the correction from 0).  The fine
@@ -405,65 +388,6 @@ __global__ __launch_bounds__(NT) void k_mg_restrict(const LevelJob<T>* __restric
         J, i, j, [&](int c, int fi, int fj) { return (double)(c == 0 ? J.rx : J.ry)[(int64_t)fj * ld + fi]; }, omega);
 }
 
-// Interpolation terms of one fine unknown: up to 2 x 2 coarse indices with
-// weights; absent terms repeat the first index and are masked out.
-struct Terms {
-    int ci[2], cj[2];
-    double wi[2], wj[2];
-    int na, nb;
-};
-__device__ __forceinline__ void pad_terms(Terms& t) {
-    if (t.na == 1) { t.ci[1] = t.ci[0]; t.wi[1] = 0.0; }
-    if (t.nb == 1) { t.cj[1] = t.cj[0]; t.wj[1] = 0.0; }
-}
-
-// (P e_c) at a fine vx / vy unknown (i, j), as double.  The coarse values are
-// loaded first, all at once (their indices are inside the coarse arrays
-// whether or not the term is used), and the terms added in the order the
-// weights list them.
-template <typename T>
-__device__ __forceinline__ double prolong_sx(const LevelJob<T>& J, int i, int j) {
-    Terms t;
-    t.na = w_normal(i, t.ci, t.wi);
-    t.nb = w_tangent(j, J.cny, t.cj, t.wj);
-    pad_terms(t);
-    double c[2][2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) c[p][q] = (double)J.cvx[(int64_t)t.cj[q] * J.cld + t.ci[p]];
-    double s = 0.0;
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const double cv = (t.ci[p] >= 1 && t.ci[p] <= J.cnx - 1) ? c[p][q] : 0.0;
-            if (p < t.na && q < t.nb) s += t.wi[p] * t.wj[q] * cv;
-        }
-    return s;
-}
-template <typename T>
-__device__ __forceinline__ double prolong_sy(const LevelJob<T>& J, int i, int j) {
-    Terms t;
-    t.na = w_tangent(i, J.cnx, t.ci, t.wi);
-    t.nb = w_normal(j, t.cj, t.wj);
-    pad_terms(t);
-    double c[2][2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) c[p][q] = (double)J.cvy[(int64_t)t.cj[q] * J.cld + t.ci[p]];
-    double s = 0.0;
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const double cv = (t.cj[q] >= 1 && t.cj[q] <= J.cny - 1) ? c[p][q] : 0.0;
-            if (p < t.na && q < t.nb) s += t.wi[p] * t.wj[q] * cv;
-        }
-    return s;
-}
-
 // v += P e_c on the fine unknowns.
 template <typename T>
 __global__ __launch_bounds__(NT) void k_mg_prolong(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
@@ -527,52 +451,53 @@ __global__ __launch_bounds__(NT) void k_mg_jacobi_prolonged(const LevelJob<T>* _
 }
 
 // ------------------------------------------------------------ coarsest grid --
-// One workgroup per instance: dense FP64 solve x = A^{-1} (-b) of the coarsest
-// problem (A = -M assembled and inverted on the host at setup), gathered from
-// and scattered to the level layout through the unknown index map.
-// Coarsest solve v = A^-1 (-b).  A workgroup takes 64 rows (grid x) of one
-// instance (grid y); its CW waves each sum a contiguous chunk of the columns
-// for those rows, and the chunk sums are added in chunk order.  The inverse is
-// stored column by column, so a wave's loads of one column are contiguous, and
-// a large coarsest level spreads its inverse over many waves and CUs (a single
-// chain per row left the 1984-unknown solve of a 32^2 level latency-bound at
-// about 200 us; the chunks, each loaded one column at a time, at 63 us).
-constexpr int CW = 16;
+// Dense FP64 solve x = A^{-1} (-b) of the coarsest problem (A = -M assembled
+// and inverted on the host at setup), gathered from and scattered to the level
+// layout through the unknown index map.
+// Coarsest solve v = A^-1 (-b).  A workgroup takes CR rows (grid x) of one
+// instance (grid y); its CW x CR threads each sum a contiguous chunk of the
+// columns for one row, and the chunk sums are added in chunk order.  The
+// inverse is stored column by column, so the rows of a workgroup are one
+// 128-byte line per column.  It is bound by the latency of the chunk's loads:
+// CL columns are loaded at once, and the rows are spread over many CUs (1984
+// unknowns of a 32^2 level, 31 MB: 64 rows per workgroup with eight loads in
+// flight used 31 CUs and took 29 us, 16 rows with 32 in flight 11 us).
+constexpr int CW = 16, CR = 16, CL = 32;
 template <typename T>
-__global__ __launch_bounds__(64 * CW) void k_mg_coarse(const CoarseJob<T>* __restrict__ jobs) {
-    extern __shared__ double csh[];  // CW x 64 chunk sums, then the right-hand side
+__global__ __launch_bounds__(CW* CR) void k_mg_coarse(const CoarseJob<T>* __restrict__ jobs) {
+    extern __shared__ double csh[];  // CW x CR chunk sums, then the right-hand side
     double* part = csh;
-    double* rhs = csh + CW * 64;
+    double* rhs = csh + CW * CR;
     const CoarseJob<T>& J = jobs[blockIdx.y];
     const int nu = J.n;
-    if ((int)blockIdx.x * 64 >= nu) return;  // the whole workgroup: no rows of this instance
-    for (int r = threadIdx.x; r < nu; r += 64 * CW) {
+    if ((int)blockIdx.x * CR >= nu) return;  // the whole workgroup: no rows of this instance
+    const int w = (int)threadIdx.x / CR, row = (int)threadIdx.x % CR, q = min((int)blockIdx.x * CR + row, nu - 1);
+    const int c0 = (int)((int64_t)nu * w / CW), c1 = (int)((int64_t)nu * (w + 1) / CW);
+    const auto* col = J.ainv + q;
+    double a[CL];
+    auto fetch = [&](int c) {  // columns c .. c + CL - 1 (clamped onto the matrix; the surplus is not added)
+#pragma unroll
+        for (int u = 0; u < CL; ++u) a[u] = col[(int64_t)min(c + u, nu - 1) * nu];
+    };
+    fetch(c0);  // in flight while the right-hand side is gathered
+    for (int r = threadIdx.x; r < nu; r += CW * CR) {
         const int code = J.map[r];  // (component << 30) | (j * ld + i) offset
         const int off = code & 0x3fffffff;
         rhs[r] = -(double)((code >> 30) ? J.by[off] : J.bx[off]);
     }
     __syncthreads();
-    const int w = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64, q = (int)blockIdx.x * 64 + lane;
-    const int c0 = (int)((int64_t)nu * w / CW), c1 = (int)((int64_t)nu * (w + 1) / CW);
     double s = 0.0;
-    if (q < nu) {
-        // eight loads in flight before their products are added, in column order
-        const double* col = J.ainv + q;
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {
-            double a[8];
+    for (int c = c0; c < c1; c += CL) {
+        if (c > c0) fetch(c);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = col[(int64_t)(c + u) * nu];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += a[u] * rhs[c + u];
-        }
-        for (; c < c1; ++c) s += col[(int64_t)c * nu] * rhs[c];
+        for (int u = 0; u < CL; ++u)
+            if (c + u < c1) s += a[u] * rhs[c + u];
     }
-    part[w * 64 + lane] = s;
+    part[w * CR + row] = s;
     __syncthreads();
-    if (w == 0 && q < nu) {
-        double t = part[lane];
-        for (int u = 1; u < CW; ++u) t += part[u * 64 + lane];
+    if (w == 0 && (int)blockIdx.x * CR + row < nu) {
+        double t = part[row];
+        for (int u = 1; u < CW; ++u) t += part[u * CR + row];
         const int code = J.map[q];
         const int off = code & 0x3fffffff;
         if (code >> 30) J.vy[off] = T(t); else J.vx[off] = T(t);
@@ -954,8 +879,8 @@ int mg_jacobi_prolonged(stk_ctx* ctx, const Batch& b, double omega) {
 template <typename T>
 int mg_coarse(stk_ctx* ctx, const void* jobs, int n, int max_unknowns) {
     if (!n) return STK_OK;
-    hipLaunchKernelGGL(k_mg_coarse<T>, dim3((unsigned)((max_unknowns + 63) / 64), (unsigned)n), dim3(64 * CW),
-                       (size_t)(CW * 64 + max_unknowns) * sizeof(double), ctx->stream,
+    hipLaunchKernelGGL(k_mg_coarse<T>, dim3((unsigned)((max_unknowns + CR - 1) / CR), (unsigned)n), dim3(CW * CR),
+                       (size_t)(CW * CR + max_unknowns) * sizeof(double), ctx->stream,
                        static_cast<const CoarseJob<T>*>(jobs));
     STK_LAUNCH_CHECK();
     return STK_OK;
