@@ -398,6 +398,20 @@ static LevelJob<T> level_job(const stk_mg* m, size_t l, int t) {
     return J;
 }
 
+// Do the coarse levels run their two sweeps each way in one pass (mg_pair.hip)?
+// With Jacobi and two sweeps before and after on every level, where a stencil
+// plane is below 2 GiB and has padding to the right of column nx.
+static bool takes_pairs(stk_mg* const* mgs, int n, int t) {
+    const stk_mg_opts& o = mgs[0]->o;
+    if (o.coarse_smoother == 1 || o.nu1 != 2 || o.nu2 != 2 || o.sweep_growth != 1.0) return false;
+    for (int q = 0; q < n; ++q)
+        for (size_t l = 1; l + 1 < mgs[q]->L.size(); ++l) {
+            const MgLevel& L = mgs[q]->L[l];
+            if (L.ld < L.nx + 2 || (int64_t)L.plane * (t ? 4 : 8) >= (int64_t)1 << 31) return false;
+        }
+    return true;
+}
+
 template <typename T>
 static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, bool z32) {
     hipStream_t s = ctx->stream;
@@ -419,8 +433,10 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     P->fine_t.assign(maxl, Batch{});
     P->relax.assign(maxl, Batch{});
     P->relax_t.assign(maxl, Batch{});
+    P->fine_p.assign(maxl, Batch{});
     const stk_mg_opts& o0 = mgs[0]->o;
     const bool cras = o0.coarse_smoother == 1;
+    P->pair = takes_pairs(mgs, n, t);
     // Does the restriction into level l (>= 1) also take its first smoothing
     // sweep?  When it is smoothed by Jacobi from zero with at least one sweep
     // before its residual, or is a relaxed last level; not the solved
@@ -433,14 +449,20 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     };
     for (int d = 0; d < maxl; ++d) {
         std::vector<LevelJob<T>> jobs, rj;
-        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, rpf{0}, rpt{0};
+        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, pp{0}, rpf{0}, rpt{0};
         std::vector<CoarseJob<T>> cj;
         for (int q = 0; q < n; ++q) {
             const stk_mg* m = mgs[q];
             const int nl = (int)m->L.size();
             if (d < nl - 1) {
                 jobs.push_back(level_job<T>(m, d, t));
-                jobs.back().first = first_sweep(m, d + 1);
+                LevelJob<T>& J = jobs.back();
+                J.first = first_sweep(m, d + 1);
+                if (P->pair && d + 1 < nl - 1) {  // the next level's pass starts from v
+                    J.cwx = J.cvx;
+                    J.cwy = J.cvy;
+                }
+                pp.push_back(pp.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny));
                 pf.push_back(pf.back() + blocks_of(m->L[d].nx, m->L[d].ny));
                 pr.push_back(pr.back() + rows::workgroups(m->L[d].nx, m->L[d].ny));
                 pc.push_back(pc.back() + blocks_of(m->L[d + 1].nx, m->L[d + 1].ny));
@@ -476,6 +498,11 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 const void* dpt = nullptr;
                 STK_TRY(upload(P, pt, &dpt, s));
                 P->fine_t[d] = Batch{dj, (const int*)dpt, (int)jobs.size(), pt.back()};
+            }
+            if (d >= 1 && P->pair) {
+                const void* dpp = nullptr;
+                STK_TRY(upload(P, pp, &dpp, s));
+                P->fine_p[d] = Batch{dj, (const int*)dpp, (int)jobs.size(), pp.back()};
             }
             if (d == 0) {  // the finest level is matrix-free: row-streaming smoothing and residual
                 const void* dpr = nullptr;
@@ -721,6 +748,8 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu1, false, &done));
             STK_TRY(mg_residual<T>(ctx, P.fine0w));
+        } else if (d >= 1 && P.pair) {
+            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, false));
         } else {
             STK_TRY(d == 0 ? smooth_stage<T>(ctx, F, o, nu1)
                            : coarse_stage<T>(ctx, F, P.fine_t[d], o, nu1, first_sweep_done(o, nu1)));
@@ -743,6 +772,8 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
             STK_TRY(mg_prolong<T>(ctx, P.fine0w));
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu2, true, &done));
+        } else if (d >= 1 && P.pair) {
+            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, true));
         } else if (d >= 1 && o.coarse_smoother != 1 && nu2 >= 1) {
             // the prolongation and the first post-sweep in one pass (v + P e -> w)
             STK_TRY(mg_jacobi_prolonged<T>(ctx, F, o.omega));

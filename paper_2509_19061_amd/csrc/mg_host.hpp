@@ -48,6 +48,10 @@ struct PlanT {
     // (coarse RAS smoothing); relaxed coarsest levels of truncated hierarchies
     // (block and tile prefixes)
     std::vector<Batch> fine_t, relax, relax_t;
+    // coarse levels smoothed by two sweeps each way: both in one pass (a prefix
+    // over its tiles); the restriction's first sweep then goes to v
+    bool pair = false;
+    std::vector<Batch> fine_p;
     std::vector<int> l0nx, l0ny;
     std::vector<int64_t> l0ld;
     struct RasK {

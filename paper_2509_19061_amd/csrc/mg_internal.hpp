@@ -30,7 +30,8 @@ struct LevelJob {
     gptr<const T> st;  // stored Galerkin stencil (coarse levels), nullptr on the finest
     int64_t plane;     // elements per stencil plane
     // the restriction also takes the coarse level's first smoothing sweep from 0
-    // (damped Jacobi, written to cw*) when `first`; cst / cplane: its stencil
+    // (damped Jacobi, written to cw*: where that level's next pass reads it) when
+    // `first`; cst / cplane: its stencil
     int first;
     gptr<const T> cst;
     int64_t cplane;
@@ -104,6 +105,11 @@ template <typename T> int mg_prolong(stk_ctx* ctx, const Batch& b);
 // Stored-stencil levels: v + P e_c, then one Jacobi sweep of it into w, in one
 // pass (v itself is left as it was)
 template <typename T> int mg_jacobi_prolonged(stk_ctx* ctx, const Batch& b, double omega);
+// Stored-stencil levels smoothed by two sweeps, one pass each way (mg_pair.hip;
+// b's prefix counts mg_pair_tiles per instance): down w <- the second
+// pre-sweep of v, r <- its residual; up v <- two sweeps of w + P e_c.
+template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up);
+int mg_pair_tiles(int nx, int ny);
 template <typename T> int mg_coarse(stk_ctx* ctx, const void* jobs, int n, int max_unknowns);
 
 // Galerkin setup of one coarse level from the next finer one (galerkin.hip).

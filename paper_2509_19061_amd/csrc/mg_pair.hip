@@ -1,0 +1,158 @@
+// Two applications of a stored Galerkin stencil in one pass: on the way down a
+// coarse level's second pre-smoothing sweep and its residual, on the way up the
+// prolongation and both post-smoothing sweeps.
+//
+// A level's stored stencil is four fifths of the bytes of a sweep (32 planes
+// against 6 of vectors), and on the small levels a launch costs more than its
+// bytes; applied separately, each of the four passes of a V(2, 2)-cycle reads
+// the planes again.  Here a workgroup takes a region of RX x RY positions.  Each
+// of its threads owns one row of the operator (a position and a component),
+// loads its 31 coefficients once and keeps them in registers for both
+// applications; the velocities are staged in LDS.  The first application is
+// computed on the whole region, into a second window, the second on the region
+// without its two-cell rim, which is what the workgroup owns.
+//
+// Why this region: the coefficients (62 VGPRs in FP64) must fit 128 VGPRs at 16
+// waves, so a workgroup holds 512 positions; 32 x 16 leaves 28 x 12 = 66 % of
+// them owned (64 x 8 would leave 47 %).  The rim's coefficients are the
+// neighbours' own and come from L2.
+//
+// The row sums run in the slot order of stencil_av_l on the same operands, and
+// the updates are the shared ones, so the values are the bits of the separate
+// kernels.
+#include "coarse_stencil.hpp"
+#include "mg_internal.hpp"
+#include "mg_transfer.hpp"
+#include "wave.hpp"
+
+namespace stk {
+namespace {
+
+constexpr int RX = 32, RY = 16, NPOS = RX * RY, NTH = 2 * NPOS;
+constexpr int RIM = 2;                                // reach of the stencil
+constexpr int OX = RX - 2 * RIM, OY = RY - 2 * RIM;   // owned positions
+constexpr int WX = RX + 2 * RIM, WY = RY + 2 * RIM;   // window of the first application
+constexpr int DIAG[2] = {7, 23};                      // slots of the diagonals
+static_assert(offset_slot(0, 0, 0, 0) == DIAG[0] && offset_slot(1, 1, 0, 0) == DIAG[1], "diagonal slots");
+
+__device__ __forceinline__ int find_pair_inst(const int* __restrict__ pre, int n, int b) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (pre[mid] <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The 31 coefficients of row (A, i, j).  Planes are read through buffer
+// resources of one plane: a neighbour above or below the box is out of its
+// range and reads 0; one left or right of it is in the padding or in column
+// nx (the host requires ld >= nx + 2), which hold 0.  in = false: no loads.
+template <typename T, int A>
+__device__ __forceinline__ void load_row(const LevelJob<T>& J, int i, int j, bool in, T (&cf)[NCOEF]) {
+    const unsigned es = sizeof(T), size = (unsigned)((J.ny + 1) * J.ld) * es;
+    const int at = (int)(((int64_t)j * J.ld + i) * es);
+#pragma unroll
+    for (int q = 0; q < NCOEF; ++q) {
+        const SlotSrc s = slot_src(A, q);
+        const int off = at + (s.ndy * (int)J.ld + s.ndx) * (int)es;
+        cf[q] = buf_load<T>(buf_rsrc((const T*)(J.st + s.plane * J.plane), size), in ? (unsigned)off : OOB);
+    }
+}
+// (A v) of the row at window element `e` of component planes of `stride` and
+// row length W: the slot order of stencil_av_l.
+template <typename T, int A, int W>
+__device__ __forceinline__ T row_sum(const T (&cf)[NCOEF], const T* win, int stride, int e) {
+    T s = T(0);
+#pragma unroll
+    for (int q = 0; q < NCOEF; ++q) {
+        const T v = win[slot_comp(A, q) * stride + e + slot_dy(A, q) * W + slot_dx(A, q)];
+        s += cf[q] * v;
+    }
+    return s;
+}
+
+// UP = false: v holds the first sweep; w <- the second, r <- its residual.
+// UP = true: v <- two sweeps of w + P e_c.
+template <typename T, bool UP>
+__global__ __launch_bounds__(NTH) void k_mg_pair(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
+                                                 int n, T omega) {
+    __shared__ T win[2 * WX * WY], mid[2 * NPOS];
+    const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int inst = find_pair_inst(pre, n, b);
+    const LevelJob<T>& J = jobs[inst];
+    const int nx = J.nx, ny = J.ny, lb = b - pre[inst], ntx = (nx + 1 + OX - 1) / OX;
+    const int i0 = (lb % ntx) * OX - RIM, j0 = (lb / ntx) * OY - RIM;  // position of region element (0, 0)
+    const int64_t ld = J.ld;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int comp = wave / (NPOS / 64), e = (int)threadIdx.x & (NPOS - 1), x = e % RX, y = e / RX;
+    const int i = i0 + x, j = j0 + y;
+    const bool unk = comp == 0 ? is_vx_unknown(nx, ny, i, j) : is_vy_unknown(nx, ny, i, j);
+    const int64_t k = (int64_t)j * ld + i;
+    T cf[NCOEF];
+    if (comp == 0) load_row<T, 0>(J, i, j, unk, cf);
+    else load_row<T, 1>(J, i, j, unk, cf);
+    const T rhs = unk ? (comp == 0 ? J.bx : J.by)[k] : T(0);
+    for (int q = threadIdx.x; q < 2 * WX * WY; q += NTH) {
+        const int c = q / (WX * WY), r = (q / WX) % WY, ii = i0 - RIM + q % WX, jj = j0 - RIM + r;
+        T val;
+        if constexpr (UP) {
+            val = T(0);
+            const int64_t kk = (int64_t)jj * ld + ii;
+            if (c == 0 && is_vx_unknown(nx, ny, ii, jj)) val = J.wx[kk] + T(prolong_sx(J, ii, jj));
+            else if (c == 1 && is_vy_unknown(nx, ny, ii, jj)) val = J.wy[kk] + T(prolong_sy(J, ii, jj));
+        } else {
+            val = c == 0 ? ldvx<T>(J.vx, ld, nx, ny, ii, jj) : ldvy<T>(J.vy, ld, nx, ny, ii, jj);
+        }
+        win[q] = val;
+    }
+    __syncthreads();
+    const int we = (y + RIM) * WX + x + RIM;
+    T u = T(0), g = T(0);
+    if (comp == 0) {
+        const T av = row_sum<T, 0, WX>(cf, win, WX * WY, we);
+        g = omega / cf[DIAG[0]];
+        u = jac_step<T>(win[we], g, rhs, -av);
+    } else {
+        const T av = row_sum<T, 1, WX>(cf, win, WX * WY, we);
+        g = omega / cf[DIAG[1]];
+        u = jac_step<T>(win[WX * WY + we], g, rhs, -av);
+    }
+    u = unk ? u : T(0);
+    mid[comp * NPOS + e] = u;
+    __syncthreads();
+    const bool own = x >= RIM && x < RX - RIM && y >= RIM && y < RY - RIM &&
+                     (comp == 0 ? (i <= nx && j < ny) : (i < nx && j <= ny));
+    if (!own) return;
+    const T av = comp == 0 ? row_sum<T, 0, RX>(cf, mid, NPOS, e) : row_sum<T, 1, RX>(cf, mid, NPOS, e);
+    if constexpr (UP) {
+        const T o = jac_step<T>(u, g, rhs, -av);
+        (comp == 0 ? J.vx : J.vy)[k] = unk ? o : T(0);
+    } else {
+        (comp == 0 ? J.wx : J.wy)[k] = u;
+        (comp == 0 ? J.rx : J.ry)[k] = unk ? rhs + av : T(0);
+    }
+}
+
+}  // namespace
+
+int mg_pair_tiles(int nx, int ny) { return ((nx + 1 + OX - 1) / OX) * ((ny + 1 + OY - 1) / OY); }
+
+template <typename T>
+int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up) {
+    if (!b.n) return STK_OK;
+    const dim3 grid((unsigned)b.blocks), block(NTH);
+    if (up)
+        hipLaunchKernelGGL((k_mg_pair<T, true>), grid, block, 0, ctx->stream, static_cast<const LevelJob<T>*>(b.jobs),
+                           b.pre, b.n, T(omega));
+    else
+        hipLaunchKernelGGL((k_mg_pair<T, false>), grid, block, 0, ctx->stream, static_cast<const LevelJob<T>*>(b.jobs),
+                           b.pre, b.n, T(omega));
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+template int mg_pair<double>(stk_ctx*, const Batch&, double, bool);
+template int mg_pair<float>(stk_ctx*, const Batch&, double, bool);
+
+}  // namespace stk
