@@ -30,13 +30,10 @@ __global__ __launch_bounds__(64 * WPB, pipe_occupancy<T>(K)) void k_jacobi_pipe(
     const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
     const unsigned col = (unsigned)i * (unsigned)sizeof(T);
     const unsigned s_x = own ? col : OOB, s_y = own && ycol ? col : OOB;
-    walk<T, K, SQ>(L, y0, sh.seg, i, g.omega, g.idx, g.idy, [&](int j, T ux, T uy) {
-        const bool in = j >= y0 && j < y1;
-        const int64_t o = (int64_t)j * g.ld;
-        const bool xu = xcol && j <= ny - 1, yu = ycol && j >= 1 && j <= ny - 1;
-        buf_store(xu ? ux : T(0), buf_rsrc(ox + o, in && j <= ny - 1 ? (size_t)(nx + 1) * sizeof(T) : 0), s_x);
-        buf_store(yu ? uy : T(0), buf_rsrc(oy + o, in ? (size_t)nx * sizeof(T) : 0), s_y);
-    });
+    walk<T, K, SQ, false, ring_rows<T>(K)>(
+        L, y0 - K, y0 + sh.seg + K, nx, ny, i, g.omega, g.idx, g.idy, [](int, int, rows::Row<T>&) {},
+        [&](int j, T ux, T uy) { store_row<T>(ox, oy, g.ld, nx, ny, y0, y1, j, xcol, ycol, ux, uy, s_x, s_y); },
+        [](int, int, T, T) {});
 }
 
 // Time of one step of one wave that has the SIMD to itself, in us: about 217

@@ -67,12 +67,12 @@ struct State {
     T vx, vy, S, Q, ey;
 };
 
-// Level update at row j from the state (row j) and the new row j + 1 of the
+// The operator at row j from the state (row j) and the new row j + 1 of the
 // level below (nx, ny); c: the coefficients of row j, nR: N(i + 1, j), Ab:
-// A(i, j - 1), Nt: N(i, j + 1).
+// A(i, j - 1), Nt: N(i, j + 1).  m: (M v) at row j, v: the level below there.
 template <typename T, bool SQ>
 __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c, T nR, T Ab, T Nt, const Scale<T>& sc,
-                                      T& ux, T& uy) {
+                                      T& mx, T& my, T& vx, T& vy) {
     const T a = nx - s.vx;
     const T d = ny - wave_shift<DPP_FROM_PREV>(ny);
     const T S1 = SQ ? a + d : fmaT(sc.ry, a, d);
@@ -81,7 +81,7 @@ __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c,
     const T ex = wave_shift<DPP_FROM_NEXT>(s.vx) - s.vx;
     const T exl = wave_shift<DPP_FROM_PREV>(ex);
     const T Qr = wave_shift<DPP_FROM_NEXT>(s.Q);
-    T mx = c.A * ex;
+    mx = c.A * ex;
     mx = fmaT(-c.aL, exl, mx);
     mx = fmaT(Nt, S1, mx);
     mx = fmaT(-c.N, s.S, mx);
@@ -94,12 +94,12 @@ __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c,
         B = coef_b(c.A, sk);
         Bb = coef_b(Ab, sk);
     }
-    T my = B * ey;
+    my = B * ey;
     my = fmaT(-Bb, s.ey, my);
     my = fmaT(nR, Qr, my);
     my = fmaT(-c.N, s.Q, my);
-    ux = jac_step<T>(s.vx, c.gx, c.bx, mx);
-    uy = jac_step<T>(s.vy, c.gy, c.by, my);
+    vx = s.vx;
+    vy = s.vy;
     s.vx = nx;
     s.vy = ny;
     s.S = S1;
@@ -107,38 +107,42 @@ __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c,
     s.ey = ey;
 }
 
-// K sweeps of the wave's strip and segment; put(j, ux, uy) receives row j of
-// the last level for y0 <= j < y0 + seg, rows past the grid included.
-// SQ: square cells (ry = rx = kap = 1 exactly, so B = A and the two strains
-// are the same sum).
-template <typename T, int K, bool SQ, typename PUT>
-__device__ __forceinline__ void walk(const rows::Loader<T>& L, int y0, int seg, int i, T omega, T idx, T idy,
-                                     const PUT& put) {
-    constexpr int R = ring_rows<T>(K), U = R, PFD = ahead<T>();
+// K sweeps of the rows that load(r) delivers for r0 <= r < r1 (at column i of each
+// lane; arrive(u, r, row) may change the row's velocity when it arrives), and,
+// with RES, the residual b - M v of their result.  put(j, ux, uy) receives row
+// j = r - K of the last sweep, putr(u, j, rx, ry) row j = r - K - 1 of the residual
+// (0 off the unknowns); both get every row, in order, and keep what is theirs.
+// u: the step within the unrolled trip of R steps (a compile-time value).
+// SQ: square cells (ry = rx = kap = 1 exactly, so B = A and the two strains are
+// the same sum).
+template <typename T, int K, bool SQ, bool RES, int R, typename LD, typename ARR, typename PUT, typename PUTR>
+__device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny, int i, T omega, T idx, T idy,
+                                     const ARR& arrive, const PUT& put, const PUTR& putr) {
+    constexpr int PFD = ahead<T>(), NL = K + (RES ? 1 : 0);
+    static_assert(R >= NL + 2 && R % PFD == 0, "the ring holds NL + 2 rows and the load queue rotates by renaming");
     // many FP64 sweeps on cells that are not square: N(i + 1, j) is taken again
     // by each level rather than kept in the ring, so that 256 registers do
-    constexpr bool KEEP_NR = SQ || sizeof(T) == 4 || K <= 5;
-    const int nx = L.nx, ny = L.ny;
+    constexpr bool KEEP_NR = SQ || sizeof(T) == 4 || NL <= 5;
     const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
     const Scale<T> sv = stencil_scale(idx, idy);
     const Scale<T> sc{wave_uniform(sv.a), wave_uniform(sv.n), wave_uniform(sv.kap), wave_uniform(sv.ry),
                       wave_uniform(sv.rx)};
-    State<T> st[K];
+    State<T> st[NL];
     Coef<T> cf[R];
 #pragma unroll
-    for (int s = 0; s < K; ++s) st[s] = State<T>{T(0), T(0), T(0), T(0), T(0)};
+    for (int s = 0; s < NL; ++s) st[s] = State<T>{T(0), T(0), T(0), T(0), T(0)};
 #pragma unroll
     for (int q = 0; q < R; ++q) cf[q] = Coef<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
-    const int r0 = y0 - K, r1 = y0 + seg + K;  // rows loaded: r0 .. r1 - 1
     rows::Row<T> q[PFD];
 #pragma unroll
     for (int p = 0; p < PFD; ++p) q[p] = L.load(r0 + p);
-    for (int rb = r0; rb < r1; rb += U) {
+    for (int rb = r0; rb < r1; rb += R) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < R; ++u) {
             const int r = rb + u;
-            const rows::Row<T> w = q[u % PFD];
+            rows::Row<T> w = q[u % PFD];
             q[u % PFD] = L.load(r + PFD);
+            arrive(u, r, w);
             Coef<T>& c0 = cf[u];                 // row r
             Coef<T>& c1 = cf[(u + R - 1) % R];   // row r - 1
             const Coef<T>& c2 = cf[(u + R - 2) % R];
@@ -150,8 +154,8 @@ __device__ __forceinline__ void walk(const rows::Loader<T>& L, int y0, int seg, 
             c0.by = w.by;
             {  // the factors of row r - 1, whose upper shear coefficient is now here
                 const int j = r - 1;
-                const T dx = SQ ? (c1.N + c0.N) + (c1.aL + c1.A) : diagx_scaled<T>(c1.aL, c1.A, c1.N, c0.N, sc.ry);
                 const T nR = KEEP_NR ? c1.nR : wave_shift<DPP_FROM_NEXT>(c1.N);
+                const T dx = SQ ? (c1.N + c0.N) + (c1.aL + c1.A) : diagx_scaled<T>(c1.aL, c1.A, c1.N, c0.N, sc.ry);
                 const T dy = SQ ? (c1.N + nR) + (c2.A + c1.A)
                                 : diagy_scaled<T>(coef_b(c2.A, sc), coef_b(c1.A, sc), c1.N, nR, sc.rx);
                 const T gx = jac_factor(omega, dx), gy = jac_factor(omega, dy);
@@ -160,18 +164,37 @@ __device__ __forceinline__ void walk(const rows::Loader<T>& L, int y0, int seg, 
             }
             T ux = w.vx, uy = w.vy;
 #pragma unroll
-            for (int s = 1; s <= K; ++s) {  // level s: row r - s
+            for (int s = 1; s <= NL; ++s) {  // level s: row r - s
                 const Coef<T>& c = cf[(u + 2 * R - s) % R];
                 const T Ab = cf[(u + 2 * R - s - 1) % R].A, Nt = cf[(u + 2 * R - s + 1) % R].N;
                 const T nR = KEEP_NR ? c.nR : wave_shift<DPP_FROM_NEXT>(c.N);
-                T vx, vy;
-                level<T, SQ>(st[s - 1], ux, uy, c, nR, Ab, Nt, sc, vx, vy);
-                ux = vx;
-                uy = vy;
+                T mx, my, vx, vy;
+                level<T, SQ>(st[s - 1], ux, uy, c, nR, Ab, Nt, sc, mx, my, vx, vy);
+                if (RES && s == NL) {
+                    const int j = r - NL;
+                    putr(u, j, (xcol && j >= 0 && j <= ny - 1) ? c.bx - mx : T(0),
+                         (ycol && j >= 1 && j <= ny - 1) ? c.by - my : T(0));
+                } else {
+                    ux = jac_step<T>(vx, c.gx, c.bx, mx);
+                    uy = jac_step<T>(vy, c.gy, c.by, my);
+                    if (s == K) put(r - K, ux, uy);
+                }
             }
-            put(r - K, ux, uy);
         }
     }
+}
+
+// Stores of a finished velocity row j at this lane's column, walls 0, where the row
+// is one of y0 .. y1 - 1 (s_x, s_y: the lane's offsets in vx and vy rows, OOB for a
+// lane that owns none).
+template <typename T>
+__device__ __forceinline__ void store_row(T* ox, T* oy, int64_t ld, int nx, int ny, int y0, int y1, int j, bool xcol,
+                                          bool ycol, T ux, T uy, unsigned s_x, unsigned s_y) {
+    const bool in = j >= y0 && j < y1;
+    const int64_t o = (int64_t)j * ld;
+    const bool xu = xcol && j <= ny - 1, yu = ycol && j >= 1 && j <= ny - 1;
+    buf_store(xu ? ux : T(0), buf_rsrc(ox + o, in && j <= ny - 1 ? (size_t)(nx + 1) * sizeof(T) : 0), s_x);
+    buf_store(yu ? uy : T(0), buf_rsrc(oy + o, in ? (size_t)nx * sizeof(T) : 0), s_y);
 }
 
 }  // namespace pipe

@@ -412,6 +412,18 @@ static bool takes_pairs(stk_mg* const* mgs, int n, int t) {
     return true;
 }
 
+// Does the finest level run in one pass each way (mg_fine.hip)?  With the default
+// smoother (no RAS parameters of its own) and 1 to MG_FINE_MAX sweeps, where its rows
+// are below 2 GiB.
+static bool takes_fused(stk_mg* const* mgs, int n, int t) {
+    const stk_mg_opts& o = mgs[0]->o;
+    if (o.fine_k > 0 || o.fine_halo >= 0 || std::min(o.nu1, o.nu2) < 1 || std::max(o.nu1, o.nu2) > MG_FINE_MAX)
+        return false;
+    for (int q = 0; q < n; ++q)
+        if (((int64_t)mgs[q]->L[0].nx + 1) * (t ? 4 : 8) >= INT32_MAX) return false;
+    return true;
+}
+
 template <typename T>
 static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, bool z32) {
     hipStream_t s = ctx->stream;
@@ -532,6 +544,20 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 STK_TRY(upload(P, sw, &dsw, s));
                 P->fine0w = P->fine[d];
                 P->fine0w.jobs = dsw;
+                P->fused = takes_fused(mgs, n, t);
+                P->square = true;
+                for (const LevelJob<T>& J : jobs) P->square = P->square && J.idx == J.idy;
+                for (int up = 0; P->fused && up < 2; ++up) {
+                    std::vector<FineShape> fs;
+                    std::vector<int> fp;
+                    mg_fine_shape(ctx, (int)sizeof(T), P->l0nx.data(), P->l0ny.data(), (int)jobs.size(),
+                                  up ? o0.nu2 : o0.nu1, up, &fs, &fp);
+                    const void *dfs = nullptr, *dfp = nullptr;
+                    STK_TRY(upload(P, fs, &dfs, s));
+                    STK_TRY(upload(P, fp, &dfp, s));
+                    (up ? P->fine_up : P->fine_dn) = Batch{dj, (const int*)dfp, (int)jobs.size(), fp.back()};
+                    (up ? P->up_shapes : P->dn_shapes) = static_cast<const FineShape*>(dfs);
+                }
             }
         }
         if (!cj.empty()) {
@@ -720,13 +746,13 @@ static int fine_ras_stage(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, in
 }
 
 template <typename T>
-static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
-    // Finest level: pre-smoothing v -> w and post-smoothing w -> v as RAS outer
-    // iterations (the iterate is in w in between), when the streaming kernel
-    // takes the instances; else Jacobi sweeps (exactly the same values when
-    // the overlap is the default).
+static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const FineIo& io) {
+    // Finest level: one pass each way when the plan is fused; else pre-smoothing
+    // v -> w and post-smoothing w -> v as RAS outer iterations (the iterate is in
+    // w in between), when the streaming kernel takes the instances; else Jacobi
+    // sweeps (exactly the same values when the overlap is the default).
     const bool paper_fine = o.fine_halo >= 0 || o.fine_k > 0;  // a smoother other than Jacobi
-    bool ras0 = P.ras_jobs[0] && o.nu1 >= 1 && o.nu2 >= 1;
+    bool ras0 = !P.fused && P.ras_jobs[0] && o.nu1 >= 1 && o.nu2 >= 1;
     if (ras0) {  // both stages must fit, checked before anything is launched
         const stk_dtype dt = sizeof(T) == 8 ? STK_F64 : STK_F32;
         for (int nu : {o.nu1, o.nu2}) {
@@ -744,7 +770,10 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
         const Batch& F = P.fine[d];
         if (!F.n) break;
         const int nu1 = level_sweeps(o.nu1, o.sweep_growth, d);
-        if (d == 0 && ras0) {
+        const bool fused = d == 0 && P.fused;
+        if (fused) {
+            STK_TRY(mg_fine<T>(ctx, P.fine_dn, P.dn_shapes, nu1, P.square, o.omega, false, io));
+        } else if (d == 0 && ras0) {
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu1, false, &done));
             STK_TRY(mg_residual<T>(ctx, P.fine0w));
@@ -755,7 +784,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
                            : coarse_stage<T>(ctx, F, P.fine_t[d], o, nu1, first_sweep_done(o, nu1)));
             STK_TRY(mg_residual<T>(ctx, F));
         }
-        STK_TRY(mg_restrict<T>(ctx, P.crs[d], o.omega));
+        if (!fused) STK_TRY(mg_restrict<T>(ctx, P.crs[d], o.omega));
         if (d + 1 < (int)P.cjobs.size()) {
             STK_TRY(mg_coarse<T>(ctx, P.cjobs[d + 1], P.ncj[d + 1], P.maxcn));
             if (P.relax[d + 1].n) {  // truncated hierarchies: the last level relaxed from 0
@@ -768,7 +797,9 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
         const Batch& F = P.fine[d];
         if (!F.n) continue;
         const int nu2 = level_sweeps(o.nu2, o.sweep_growth, d);
-        if (d == 0 && ras0) {
+        if (d == 0 && P.fused) {
+            STK_TRY(mg_fine<T>(ctx, P.fine_up, P.up_shapes, nu2, P.square, o.omega, true, io));
+        } else if (d == 0 && ras0) {
             STK_TRY(mg_prolong<T>(ctx, P.fine0w));
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu2, true, &done));
@@ -786,8 +817,8 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o) {
     return STK_OK;
 }
 
-int run_vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, int t) {
-    return t ? vcycle<float>(ctx, P, o) : vcycle<double>(ctx, P, o);
+int run_vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, int t, const FineIo& io) {
+    return t ? vcycle<float>(ctx, P, o, io) : vcycle<double>(ctx, P, o, io);
 }
 
 int read_states(stk_ctx* ctx, const PlanT& P, std::vector<FcgState>& h) {
@@ -1026,6 +1057,14 @@ int stk_mg_vcycle(stk_mg* m, stk_dtype dt, void* vx, void* vy, const void* bx, c
     if (!m->plan[t]) STK_TRY(make_plan(ctx, &self, 1, t, &m->plan[t]));
     const size_t es = t ? 4 : 8;
     const int64_t ld0 = m->L[0].ld;
+    if (m->plan[t]->fused && m->user_ld == ld0) {  // the finest level's passes read and write the caller's arrays
+        FineIo io;
+        io.vx = vx;
+        io.vy = vy;
+        io.bx = bx;
+        io.by = by;
+        return run_vcycle(ctx, *m->plan[t], m->o, t, io);
+    }
     STK_TRY(copy_vel_in(m, vx, vy, m->user_ld, m->ks[t][VS_Z].x, m->ks[t][VS_Z].y, ld0, es));
     STK_TRY(copy_vel_in(m, bx, by, m->user_ld, m->ks[t][VS_R].x, m->ks[t][VS_R].y, ld0, es));
     STK_TRY(run_vcycle(ctx, *m->plan[t], m->o, t));

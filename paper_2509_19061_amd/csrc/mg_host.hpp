@@ -52,6 +52,11 @@ struct PlanT {
     // over its tiles); the restriction's first sweep then goes to v
     bool pair = false;
     std::vector<Batch> fine_p;
+    // default smoothing: the finest level in one pass each way (mg_fine.hip), with
+    // the launch shapes of the instances; square: all have square cells
+    bool fused = false, square = false;
+    Batch fine_dn, fine_up;
+    const FineShape *dn_shapes = nullptr, *up_shapes = nullptr;
     std::vector<int> l0nx, l0ny;
     std::vector<int64_t> l0ld;
     struct RasK {
@@ -81,8 +86,9 @@ struct PlanT {
 // z32 (FP64 plans): the Krylov Z slot is the FP32 V-cycle's output vector.
 int make_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT** out, bool z32 = false);
 void free_plan(PlanT*& P);
-// One V-cycle on the level-0 binding (v = Z slot, b = R slot) of every instance of P.
-int run_vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, int t);
+// One V-cycle on the level-0 binding (v = Z slot, b = R slot) of every instance of P;
+// io: fused plans only (P.fused), other arrays for v and b, or v = 0 at the start.
+int run_vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, int t, const FineIo& io = FineIo());
 int read_states(stk_ctx* ctx, const PlanT& P, std::vector<FcgState>& h);
 int write_states(stk_ctx* ctx, const PlanT& P, const std::vector<FcgState>& h);
 // 2D copy of the used extents of a velocity pair between two row strides

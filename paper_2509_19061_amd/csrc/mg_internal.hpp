@@ -110,6 +110,26 @@ template <typename T> int mg_jacobi_prolonged(stk_ctx* ctx, const Batch& b, doub
 // pre-sweep of v, r <- its residual; up v <- two sweeps of w + P e_c.
 template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up);
 int mg_pair_tiles(int nx, int ny);
+// Finest level in one pass each way (mg_fine.hip), K = 1 .. MG_FINE_MAX sweeps.
+// down: w <- K sweeps of v; the residual of w restricted to the coarse
+// right-hand side, and the coarse iterate 0 or (jobs with `first`) its first
+// sweep.  up: v <- K sweeps of w + P e_c.  b's prefix counts the workgroups of
+// mg_fine_shape.  io: arrays to use in place of the jobs' v and b (one
+// instance; nullptr: the jobs'), and zero: v is 0 and not read.
+struct FineShape {
+    int nstrip, nseg, seg;
+};
+struct FineIo {
+    void *vx = nullptr, *vy = nullptr;
+    const void *bx = nullptr, *by = nullptr;
+    int zero = 0;
+};
+constexpr int MG_FINE_MAX = 3;
+void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, int K, bool up,
+                   std::vector<FineShape>* shapes, std::vector<int>* pre);
+template <typename T>
+int mg_fine(stk_ctx* ctx, const Batch& b, const FineShape* shapes, int K, bool square, double omega, bool up,
+            const FineIo& io);
 template <typename T> int mg_coarse(stk_ctx* ctx, const void* jobs, int n, int max_unknowns);
 
 // Galerkin setup of one coarse level from the next finer one (galerkin.hip).
@@ -137,7 +157,8 @@ enum VecOp {
     OP_XPBY,        // p = z + beta p
     OP_FNORM,       // acc0 += f^2/d
     OP_INIT_P,      // p = z; acc0 += r.z
-    OP_ZERO_Z       // z = 0
+    OP_ZERO_Z,      // z = 0
+    OP_UPDATE_KEEP  // OP_UPDATE without z = 0
 };
 // phases of the scalar update: PH_NF sets N_f and the stop threshold
 // tol2 * N_f, PH_NV ends a CG iteration (stop below the threshold or when the
@@ -160,8 +181,8 @@ int fcg_reduce(stk_ctx* ctx, const Batch& red, const double* part, double* sums,
                FcgState* out = nullptr);
 
 // Entry of the FP32 V-cycle preconditioner (active instances): r32 = (float)
-// r64 and z32 = 0 (its initial guess) in one pass.  Its output z32 is read in
-// place by the FP64 Krylov operations.
+// r64 and, with `zero`, z32 = 0 (its initial guess) in one pass.  Its output z32
+// is read in place by the FP64 Krylov operations.
 struct XCastJob {
     int nx, ny;
     int64_t ld;
@@ -169,7 +190,7 @@ struct XCastJob {
     gptr<float> r32[2];
     gptr<float> z32[2];
 };
-int prec_cast(stk_ctx* ctx, const Batch& b, const FcgState* st);
+int prec_cast(stk_ctx* ctx, const Batch& b, const FcgState* st, bool zero);
 // FP64 FCG, finest level: Q = A P and the block partials of P . Q (apply: the
 // operator batch with its row-streaming prefix; summed over its reduction
 // chunks by fcg_reduce)

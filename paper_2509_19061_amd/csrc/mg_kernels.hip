@@ -571,6 +571,7 @@ __global__ __launch_bounds__(NT) void k_vec(const VecJob* __restrict__ jobs, con
             T* Q = (T*)(J.v[VS_Q][c]);
             switch (op) {
                 case OP_UPDATE:
+                case OP_UPDATE_KEEP:
                     if (u) {
                         X[k] = T((double)X[k] + al * (double)P[k]);
                         const T r = T((double)R[k] + al * (double)Q[k]);
@@ -579,7 +580,8 @@ __global__ __launch_bounds__(NT) void k_vec(const VecJob* __restrict__ jobs, con
                     }
                     // the next V-cycle's initial guess (OP_ZERO_Z), when Z is this plan's own
                     // FP64 slot; the FP32 one is zeroed by the cast that starts that V-cycle
-                    if constexpr (std::is_same<ZT, T>::value) Z[k] = ZT(0);
+                    if constexpr (std::is_same<ZT, T>::value)
+                        if (op == OP_UPDATE) Z[k] = ZT(0);
                     break;
                 case OP_XPBY:
                     P[k] = u ? T((double)Z[k] + be * (double)P[k]) : T(0);
@@ -656,16 +658,16 @@ __global__ __launch_bounds__(64 * rows::WPB) void k_fcg_apply_rows(const LevelJo
     }
 }
 
-// r32 = (float) r64 and z32 = 0, walls included
+// r32 = (float) r64 and, with `zero`, z32 = 0, walls included
 __global__ __launch_bounds__(NT) void k_prec_cast(const XCastJob* __restrict__ jobs, const int* __restrict__ pre,
-                                                  int n, const FcgState* __restrict__ st) {
+                                                  int n, const FcgState* __restrict__ st, int zero) {
     STK_BATCH_INDEX(jobs, pre, n, FINE_NX, FINE_NY)
     if (i > J.nx || j > J.ny || !st[inst].active) return;
     const int64_t k = (int64_t)j * J.ld + i;
     for (int c = 0; c < 2; ++c) {
         if (c == 0 ? j >= J.ny : i >= J.nx) continue;
         J.r32[c][k] = (float)J.r64[c][k];
-        J.z32[c][k] = 0.0f;
+        if (zero) J.z32[c][k] = 0.0f;
     }
 }
 
@@ -923,10 +925,10 @@ int fcg_apply_pq(stk_ctx* ctx, const Batch& apply, const FcgState* st, double* p
     return STK_OK;
 }
 
-int prec_cast(stk_ctx* ctx, const Batch& b, const FcgState* st) {
+int prec_cast(stk_ctx* ctx, const Batch& b, const FcgState* st, bool zero) {
     if (!b.n) return STK_OK;
     hipLaunchKernelGGL(k_prec_cast, dim3(b.blocks), dim3(NT), 0, ctx->stream, static_cast<const XCastJob*>(b.jobs),
-                       b.pre, b.n, st);
+                       b.pre, b.n, st, zero ? 1 : 0);
     STK_LAUNCH_CHECK();
     return STK_OK;
 }

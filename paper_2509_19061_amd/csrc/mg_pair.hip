@@ -28,7 +28,7 @@
 namespace stk {
 namespace {
 
-constexpr int RX = 32, RY = 16, NPOS = RX * RY, NTH = 2 * NPOS;
+constexpr int RX = 16, RY = 16, NPOS = RX * RY, NTH = 2 * NPOS;
 constexpr int RIM = 2;                                // reach of the stencil
 constexpr int OX = RX - 2 * RIM, OY = RY - 2 * RIM;   // owned positions
 constexpr int WX = RX + 2 * RIM, WY = RY + 2 * RIM;   // window of the first application
@@ -76,7 +76,7 @@ __device__ __forceinline__ T row_sum(const T (&cf)[NCOEF], const T* win, int str
 // UP = false: v holds the first sweep; w <- the second, r <- its residual.
 // UP = true: v <- two sweeps of w + P e_c.
 template <typename T, bool UP>
-__global__ __launch_bounds__(NTH) void k_mg_pair(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
+__global__ __launch_bounds__(NTH, 4) void k_mg_pair(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
                                                  int n, T omega) {
     __shared__ T win[2 * WX * WY], mid[2 * NPOS];
     const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);

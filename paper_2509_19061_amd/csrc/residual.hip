@@ -46,7 +46,7 @@ __global__ __launch_bounds__(64 * WPB) void k_residual(int nx, int ny, int64_t l
 }
 
 // The FP64 residual r = b - M v rounded to FP32 for an FP32 V-cycle from
-// zero: r32 <- (float) r, z32 <- 0 (FP32 arrays with the grid's row stride).
+// zero: r32 <- (float) r, z32 <- 0 unless null (FP32 arrays with the grid's row stride).
 // The same rows and values as k_residual<double> followed by a rounding pass.
 __global__ __launch_bounds__(64 * WPB) void k_residual_to32(int nx, int ny, int64_t ld, double idx, double idy,
                                                             const double* __restrict__ vx,
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64 * WPB) void k_residual_to32(int nx, int ny, int6
         const Res<double> r = residual_row<double, double>(a, b, c, p != nullptr, idx, idy);
         const bool ux = xcol && j <= ny - 1, uy = ycol && j >= 1 && j <= ny - 1;
         store_pair<float>(r32x, r32y, ld, nx, ny, j, ux ? (float)r.rx : 0.0f, uy ? (float)r.ry : 0.0f, s_x, s_y);
-        store_pair<float>(z32x, z32y, ld, nx, ny, j, 0.0f, 0.0f, s_x, s_y);
+        if (z32x) store_pair<float>(z32x, z32y, ld, nx, ny, j, 0.0f, 0.0f, s_x, s_y);
     });
 }
 

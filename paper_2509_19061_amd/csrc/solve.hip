@@ -47,17 +47,24 @@ struct Slot {
 };
 
 // Z = V-cycle(R) from zero for every active instance of P, in FP64 (P32 ==
-// nullptr) or in FP32 between the casts R -> R32 and Z32 -> Z.  z_zeroed: the
-// FP64 Z is already 0 (OP_UPDATE clears it).
+// nullptr) or in FP32 from R rounded to FP32.  A fused plan starts from zero by
+// itself; the others need Z cleared (z_zeroed: an FP64 Z already is, by
+// update_op).
 int precondition(stk_ctx* ctx, const PlanT& P, const PlanT* P32, const stk_mg_opts& o, bool z_zeroed) {
+    FineIo io;
     if (!P32) {
-        if (!z_zeroed) STK_TRY(vec_op<double>(ctx, P.vec, OP_ZERO_Z, P.st, P.part));
-        return run_vcycle(ctx, P, o, 0);
+        io.zero = P.fused;
+        if (!P.fused && !z_zeroed) STK_TRY(vec_op<double>(ctx, P.vec, OP_ZERO_Z, P.st, P.part));
+        return run_vcycle(ctx, P, o, 0, io);
     }
-    // r32 = (float) r and z32 = 0, the FP32 V-cycle, whose z32 the Krylov steps read in place
-    STK_TRY(prec_cast(ctx, P32->xcast, P.st));
-    return run_vcycle(ctx, *P32, o, 1);
+    // r32 = (float) r (and z32 = 0), the FP32 V-cycle, whose z32 the Krylov steps read in place
+    io.zero = P32->fused;
+    STK_TRY(prec_cast(ctx, P32->xcast, P.st, !P32->fused));
+    return run_vcycle(ctx, *P32, o, 1, io);
 }
+
+// The iterate's update, which also clears an FP64 Z for a plan that needs it.
+int update_op(const PlanT& P) { return P.fused ? OP_UPDATE_KEEP : OP_UPDATE; }
 
 }  // namespace
 }  // namespace stk
@@ -258,7 +265,7 @@ int iterate_phase(stk_batch* b, int iters) {
         STK_TRY(fcg_apply_pq(ctx, P.apply, P.st, P.part));  // Q = A P and P . Q
         STK_TRY(fcg_reduce(ctx, P.applyr, P.part, P.sums, P.st, PH_ALPHA));
         // (the Z slot's dtype selects the kernel: OP_UPDATE clears an FP64 Z)
-        STK_TRY(vec_op<double>(ctx, P.vec, OP_UPDATE, P.st, P.part, P.vec_z32));
+        STK_TRY(vec_op<double>(ctx, P.vec, update_op(P), P.st, P.part, P.vec_z32));
         // stop below tol or at the end of the budget
         if (b->lookahead) {
             // The states go to the host while the rest of the iteration is queued behind

@@ -297,10 +297,13 @@ int mixed_correction(stk_mg* m, const stk_grid* g, double* vx, double* vy, const
     float* z32y = static_cast<float*>(m->ks[1][VS_Z].y);
     const int64_t cnt = (int64_t)(g->ny + 1) * g->ld;
     const dim3 eg((unsigned)((cnt + 255) / 256)), eb(256);
-    // r32 = (float)(f - G p - M v) and z32 = 0 in one pass
+    // r32 = (float)(f - G p - M v) and, unless the V-cycle starts from zero by itself, z32 = 0 in one pass
+    FineIo io;
+    io.zero = m->plan[1]->fused;
     STK_TRY(launch_residual_to32(ctx, g, vx, vy, p, ec, en, fx, fy, static_cast<float*>(m->ks[1][VS_R].x),
-                                 static_cast<float*>(m->ks[1][VS_R].y), z32x, z32y));
-    STK_TRY(run_vcycle(ctx, *m->plan[1], m->o, 1));
+                                 static_cast<float*>(m->ks[1][VS_R].y), io.zero ? nullptr : z32x,
+                                 io.zero ? nullptr : z32y));
+    STK_TRY(run_vcycle(ctx, *m->plan[1], m->o, 1, io));
     hipLaunchKernelGGL(k_add_z, eg, eb, 0, ctx->stream, g->nx, g->ny, g->ld, (const float*)z32x, (const float*)z32y,
                        vx, vy);
     STK_HIP(hipGetLastError());
