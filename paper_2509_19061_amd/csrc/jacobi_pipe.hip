@@ -25,15 +25,11 @@ __global__ __launch_bounds__(64 * WPB, pipe_occupancy<T>(K)) void k_jacobi_pipe(
     if (segm >= sh.nseg) return;  // the whole wave
     const int nx = g.nx, ny = g.ny, lane = threadIdx.x & 63;
     const int i = strip_ * strip(K) - K + lane, y0 = segm * sh.seg, y1 = min(y0 + sh.seg, ny + 1);
-    const rows::Loader<T> L = rows::make_loader<T>(vx, vy, g.ec, g.en, g.bx, g.by, nullptr, g.ld, nx, ny, i);
-    const bool own = lane >= K && lane < 64 - K && i <= nx;
-    const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
-    const unsigned col = (unsigned)i * (unsigned)sizeof(T);
-    const unsigned s_x = own ? col : OOB, s_y = own && ycol ? col : OOB;
-    walk<T, K, SQ, false, ring_rows<T>(K)>(
-        L, y0 - K, y0 + sh.seg + K, nx, ny, i, g.omega, g.idx, g.idy, [](int, int, rows::Row<T>&) {},
-        [&](int j, T ux, T uy) { store_row<T>(ox, oy, g.ld, nx, ny, y0, y1, j, xcol, ycol, ux, uy, s_x, s_y); },
-        [](int, int, T, T) {});
+    const int r0 = y0 - K, r1 = y0 + sh.seg + K;
+    const PipeRows<T> L(vx, vy, g.ec, g.en, g.bx, g.by, g.ld, nx, ny, i, r0, r1 - r0 + ahead<T>(), false);
+    const PipeStore<T> put(ox, oy, g.ld, nx, ny, y0, y1, i, lane >= K && lane < 64 - K);
+    walk<T, K, SQ, false, ring_rows<T>(K)>(L, r0, r1, nx, ny, i, g.omega, g.idx, g.idy, [](int, int, rows::Row<T>&) {},
+                                           put, [](int, int, T, T) {});
 }
 
 // Time of one step of one wave that has the SIMD to itself, in us: about 217
@@ -49,13 +45,14 @@ double step_us(int K) { return sizeof(T) == 8 ? 2.2e-3 * (30 + 27 * K) : 1.6e-3 
 // some of them unused (FP64 x 1.1, FP32 x 1.35: 2048^2, K = 7, one or two
 // waves per SIMD, 69 / 66 us and 56 / 45 us).  *us: that time.
 template <typename T>
-Shape pipe_shape(const stk_ctx* ctx, int nx, int ny, int K, double* us) {
+Shape pipe_shape(const stk_ctx* ctx, int nx, int ny, int64_t ld, int K, double* us) {
     const int U = ring_rows<T>(K);
     const int64_t ns = (nx + 1 + strip(K) - 1) / strip(K), cu4 = (int64_t)std::max(ctx->num_cu, 1) * 4;
     Shape best{K, (int)ns, 0, 0};
     double cost = 1e300;
     for (int w = 1; w <= pipe_occupancy<T>(K); ++w) {
-        const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(w * cu4 / ns, ny + 1));
+        const int64_t most = max_rows(ld, (int)sizeof(T)) - 2 * K;  // rows of a segment that a window can address
+        const int64_t segs = std::max<int64_t>((ny + most) / most, std::min<int64_t>(w * cu4 / ns, ny + 1));
         const int steps = ((int)((ny + 1 + segs - 1) / segs) + 2 * K + U - 1) / U * U, H = steps - 2 * K;
         const int64_t nseg = (ny + 1 + H - 1) / H, per_simd = (ns * nseg + cu4 - 1) / cu4;
         const double c = (steps + 4) * std::max(sizeof(T) == 8 ? 1.1 : 1.35, (double)per_simd);
@@ -85,7 +82,7 @@ int pick_sweeps(const stk_ctx* ctx, const stk_grid* g, int left) {
         if (K == last) continue;
         last = K;
         double us = 0.0;
-        pipe_shape<T>(ctx, g->nx, g->ny, K, &us);
+        pipe_shape<T>(ctx, g->nx, g->ny, g->ld, K, &us);
         const double c = m * (std::max(us, mem) + 3.0);
         if (c < cost) {
             cost = c;
@@ -98,7 +95,7 @@ int pick_sweeps(const stk_ctx* ctx, const stk_grid* g, int left) {
 
 template <typename T, int K>
 int launch_k(stk_ctx* ctx, const Grid<T>& g, const T* vx, const T* vy, T* ox, T* oy) {
-    const Shape sh = pipe_shape<T>(ctx, g.nx, g.ny, K, nullptr);
+    const Shape sh = pipe_shape<T>(ctx, g.nx, g.ny, g.ld, K, nullptr);
     const dim3 grid((unsigned)(((int64_t)sh.nstrip * sh.nseg + WPB - 1) / WPB)), block(64 * WPB);
     if (g.idx == g.idy)
         hipLaunchKernelGGL((k_jacobi_pipe<T, K, true>), grid, block, 0, ctx->stream, g, vx, vy, ox, oy, sh);
@@ -133,7 +130,7 @@ int launch_t(stk_ctx* ctx, const stk_grid* g, const FieldPtrs& f, double omega, 
 }  // namespace
 
 bool jacobi_pipe_takes(stk_dtype dt, const stk_grid* g) {
-    return ((int64_t)g->nx + 1) * (int64_t)elem_size(dt) < INT32_MAX && g->ny < INT32_MAX - 4096;
+    return pipe::max_rows(g->ld, (int)elem_size(dt)) >= 128 && g->ny < INT32_MAX - 4096;
 }
 
 int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int left) {

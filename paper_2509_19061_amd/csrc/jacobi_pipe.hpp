@@ -27,7 +27,10 @@
 // of the same planes reaches), then vector issue.  Against the LDS pipeline
 // with one wave per level that ran these sweeps before (4096^2): FP64 k = 4
 // 0.238 -> 0.232 ms a pass, and 0.246 ms for K = 7 (480 GLUP/s against 284);
-// FP32 0.156 ms for k = 4 -> 0.122, and 0.156 for K = 8 (860 against 520).
+// FP32 0.156 ms for k = 4 -> 0.122, and 0.145 for K = 8 (920 against 520).  Where
+// few waves share a SIMD, a step's scalar instructions count as much as its vector
+// ones: with rows addressed by one scalar offset (RowSpan) 20 sweeps of 2048^2 take
+// 175 us instead of 205 in FP64 and 115 instead of 131 in FP32.
 #pragma once
 
 #include "rowstream.hpp"
@@ -47,10 +50,88 @@ template <typename T>
 constexpr int ring_rows(int K) { return (K + 1 + ahead<T>()) / ahead<T>() * ahead<T>(); }
 __host__ __device__ constexpr int strip(int K) { return 64 - 2 * K; }
 
+// Most rows a window may have (RowSpan), with the rows loaded ahead.
+inline int max_rows(int64_t ld, int es) {
+    const int64_t n = (int64_t)UINT32_MAX / (ld * es) - 64;
+    return (int)(n < 0 ? 0 : n > INT32_MAX / 2 ? INT32_MAX / 2 : n);
+}
+
 // Launch geometry of one grid: strips x segments waves of `seg` rows each
 // (seg + 2K is a multiple of the unrolled trip).
 struct Shape {
     int K, nstrip, nseg, seg;
+};
+
+// A wave's window of consecutive rows of an array: row r of [r0, r0 + n) starts
+// (r - r0) row bytes beyond a base that is formed once.  A row is then one scalar
+// offset for every array of the window, where a buffer resource per row and array
+// took about ten scalar instructions each, issue slots that a wave alone on its
+// SIMD does not have.  The host keeps n row bytes below 2^32.
+struct RowSpan {
+    int r0;
+    unsigned rowb, bytes;
+    __device__ __forceinline__ RowSpan(int r0_, int n, int64_t ld, int es)
+        : r0(r0_), rowb((unsigned)(ld * es)), bytes((unsigned)n * rowb) {}
+    __device__ __forceinline__ unsigned at(int r) const { return (unsigned)(r - r0) * rowb; }
+    template <typename P>
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t of(P p, int64_t ld, bool ok) const {
+        return buf_rsrc(p + (int64_t)r0 * ld, ok ? bytes : 0);
+    }
+};
+
+// Rows of velocity, viscosities and right-hand side at this lane's column, walls and
+// everything outside the arrays 0 (the rows of rows::Loader).  zero: the velocity is
+// 0 and not read.
+template <typename T>
+struct PipeRows {
+    const T *vx, *vy, *ec, *en, *bx, *by;
+    int64_t ld;
+    int ny;
+    unsigned o_inner, o_cell;
+    RowSpan span;
+    bool zero;
+    __device__ __forceinline__ PipeRows(const T* vx_, const T* vy_, const T* ec_, const T* en_, const T* bx_,
+                                        const T* by_, int64_t ld_, int nx, int ny_, int i, int r0, int n, bool zero_)
+        : vx(vx_), vy(vy_), ec(ec_), en(en_), bx(bx_), by(by_), ld(ld_), ny(ny_),
+          o_inner(i >= 1 && i <= nx - 1 ? (unsigned)i * (unsigned)sizeof(T) : OOB),
+          o_cell(i >= 0 && i <= nx - 1 ? (unsigned)i * (unsigned)sizeof(T) : OOB), span(r0, n, ld_, (int)sizeof(T)),
+          zero(zero_) {}
+    __device__ __forceinline__ rows::Row<T> load(int r) const {
+        const bool x = r >= 0 && r <= ny - 1, y = r >= 1 && r <= ny - 1;
+        const unsigned o = span.at(r);
+        rows::Row<T> q;
+        q.vx = buf_load_at<T>(span.of(vx, ld, x && !zero), o_inner, o);
+        q.vy = buf_load_at<T>(span.of(vy, ld, y && !zero), o_cell, o);
+        q.ec = buf_load_at<T>(span.of(ec, ld, x), o_cell, o);
+        q.en = buf_load_at<T>(span.of(en, ld, y), o_inner, o);
+        q.bx = buf_load_at<T>(span.of(bx, ld, x), o_inner, o);
+        q.by = buf_load_at<T>(span.of(by, ld, y), o_cell, o);
+        q.p = T(0);
+        return q;
+    }
+};
+
+// Stores of finished velocity rows y0 <= j < y1 at this lane's column, walls 0 (own:
+// the lane owns its column).
+template <typename T>
+struct PipeStore {
+    T *ox, *oy;
+    int64_t ld;
+    int ny, y0, y1;
+    unsigned s_x, s_y;
+    bool xcol;
+    RowSpan span;
+    __device__ __forceinline__ PipeStore(T* ox_, T* oy_, int64_t ld_, int nx, int ny_, int y0_, int y1_, int i, bool own)
+        : ox(ox_), oy(oy_), ld(ld_), ny(ny_), y0(y0_), y1(y1_),
+          s_x(own && i <= nx ? (unsigned)i * (unsigned)sizeof(T) : OOB),
+          s_y(own && i < nx ? (unsigned)i * (unsigned)sizeof(T) : OOB), xcol(i >= 1 && i <= nx - 1),
+          span(y0_, y1_ - y0_, ld_, (int)sizeof(T)) {}
+    __device__ __forceinline__ void operator()(int j, T ux, T uy) const {
+        const bool in = j >= y0 && j < y1;
+        const unsigned o = span.at(j);
+        buf_store_at(xcol ? ux : T(0), span.of(ox, ld, in && j <= ny - 1), s_x, o);
+        buf_store_at(j >= 1 && j <= ny - 1 ? uy : T(0), span.of(oy, ld, in), s_y, o);
+    }
 };
 
 // One row's coefficients at the lane's column: A = 2 eta_c idx^2 at (i, j) and
@@ -140,8 +221,17 @@ __device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny
 #pragma unroll
         for (int u = 0; u < R; ++u) {
             const int r = rb + u;
+            if (!KEEP_NR) {  // never taken: a block of its own per step, or the compiler keeps the N(i + 1, j)
+                             // of all the ring's rows after all
+                int never = 0;
+                asm volatile("" : "+s"(never));
+                if (never) __builtin_amdgcn_s_sleep(0);
+            }
             rows::Row<T> w = q[u % PFD];
             q[u % PFD] = L.load(r + PFD);
+            // FP64 steps stay apart, or the compiler mixes them and delays the loads (20 sweeps at
+            // 2048^2: 219 us, 175 us with the barrier; FP32 1501 x 1100 is 73 us without, 81 us with)
+            if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
             arrive(u, r, w);
             Coef<T>& c0 = cf[u];                 // row r
             Coef<T>& c1 = cf[(u + R - 1) % R];   // row r - 1
@@ -182,19 +272,6 @@ __device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny
             }
         }
     }
-}
-
-// Stores of a finished velocity row j at this lane's column, walls 0, where the row
-// is one of y0 .. y1 - 1 (s_x, s_y: the lane's offsets in vx and vy rows, OOB for a
-// lane that owns none).
-template <typename T>
-__device__ __forceinline__ void store_row(T* ox, T* oy, int64_t ld, int nx, int ny, int y0, int y1, int j, bool xcol,
-                                          bool ycol, T ux, T uy, unsigned s_x, unsigned s_y) {
-    const bool in = j >= y0 && j < y1;
-    const int64_t o = (int64_t)j * ld;
-    const bool xu = xcol && j <= ny - 1, yu = ycol && j >= 1 && j <= ny - 1;
-    buf_store(xu ? ux : T(0), buf_rsrc(ox + o, in && j <= ny - 1 ? (size_t)(nx + 1) * sizeof(T) : 0), s_x);
-    buf_store(yu ? uy : T(0), buf_rsrc(oy + o, in ? (size_t)nx * sizeof(T) : 0), s_y);
 }
 
 }  // namespace pipe

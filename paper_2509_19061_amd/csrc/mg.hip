@@ -413,14 +413,13 @@ static bool takes_pairs(stk_mg* const* mgs, int n, int t) {
 }
 
 // Does the finest level run in one pass each way (mg_fine.hip)?  With the default
-// smoother (no RAS parameters of its own) and 1 to MG_FINE_MAX sweeps, where its rows
-// are below 2 GiB.
+// smoother (no RAS parameters of its own) and 1 to MG_FINE_MAX sweeps.
 static bool takes_fused(stk_mg* const* mgs, int n, int t) {
     const stk_mg_opts& o = mgs[0]->o;
     if (o.fine_k > 0 || o.fine_halo >= 0 || std::min(o.nu1, o.nu2) < 1 || std::max(o.nu1, o.nu2) > MG_FINE_MAX)
         return false;
     for (int q = 0; q < n; ++q)
-        if (((int64_t)mgs[q]->L[0].nx + 1) * (t ? 4 : 8) >= INT32_MAX) return false;
+        if (!mg_fine_takes(t ? 4 : 8, mgs[q]->L[0].ld)) return false;
     return true;
 }
 
@@ -446,6 +445,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     P->relax.assign(maxl, Batch{});
     P->relax_t.assign(maxl, Batch{});
     P->fine_p.assign(maxl, Batch{});
+    P->small_p.assign(maxl, 0);
     const stk_mg_opts& o0 = mgs[0]->o;
     const bool cras = o0.coarse_smoother == 1;
     P->pair = takes_pairs(mgs, n, t);
@@ -461,7 +461,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     };
     for (int d = 0; d < maxl; ++d) {
         std::vector<LevelJob<T>> jobs, rj;
-        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, pp{0}, rpf{0}, rpt{0};
+        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, pp{0}, ps{0}, rpf{0}, rpt{0};
         std::vector<CoarseJob<T>> cj;
         for (int q = 0; q < n; ++q) {
             const stk_mg* m = mgs[q];
@@ -474,7 +474,8 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     J.cwx = J.cvx;
                     J.cwy = J.cvy;
                 }
-                pp.push_back(pp.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny));
+                pp.push_back(pp.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, false));
+                ps.push_back(ps.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, true));
                 pf.push_back(pf.back() + blocks_of(m->L[d].nx, m->L[d].ny));
                 pr.push_back(pr.back() + rows::workgroups(m->L[d].nx, m->L[d].ny));
                 pc.push_back(pc.back() + blocks_of(m->L[d + 1].nx, m->L[d + 1].ny));
@@ -513,8 +514,11 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
             }
             if (d >= 1 && P->pair) {
                 const void* dpp = nullptr;
+                const bool small = ps.back() <= ctx->num_cu;
+                if (small) pp = ps;
                 STK_TRY(upload(P, pp, &dpp, s));
                 P->fine_p[d] = Batch{dj, (const int*)dpp, (int)jobs.size(), pp.back()};
+                P->small_p[d] = small;
             }
             if (d == 0) {  // the finest level is matrix-free: row-streaming smoothing and residual
                 const void* dpr = nullptr;
@@ -550,7 +554,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 for (int up = 0; P->fused && up < 2; ++up) {
                     std::vector<FineShape> fs;
                     std::vector<int> fp;
-                    mg_fine_shape(ctx, (int)sizeof(T), P->l0nx.data(), P->l0ny.data(), (int)jobs.size(),
+                    mg_fine_shape(ctx, (int)sizeof(T), P->l0nx.data(), P->l0ny.data(), P->l0ld.data(), (int)jobs.size(),
                                   up ? o0.nu2 : o0.nu1, up, &fs, &fp);
                     const void *dfs = nullptr, *dfp = nullptr;
                     STK_TRY(upload(P, fs, &dfs, s));
@@ -778,7 +782,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu1, false, &done));
             STK_TRY(mg_residual<T>(ctx, P.fine0w));
         } else if (d >= 1 && P.pair) {
-            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, false));
+            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, false, P.small_p[d]));
         } else {
             STK_TRY(d == 0 ? smooth_stage<T>(ctx, F, o, nu1)
                            : coarse_stage<T>(ctx, F, P.fine_t[d], o, nu1, first_sweep_done(o, nu1)));
@@ -804,7 +808,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu2, true, &done));
         } else if (d >= 1 && P.pair) {
-            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, true));
+            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, true, P.small_p[d]));
         } else if (d >= 1 && o.coarse_smoother != 1 && nu2 >= 1) {
             // the prolongation and the first post-sweep in one pass (v + P e -> w)
             STK_TRY(mg_jacobi_prolonged<T>(ctx, F, o.omega));

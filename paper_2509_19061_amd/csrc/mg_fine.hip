@@ -51,31 +51,6 @@ __device__ __forceinline__ int find_fine_inst(const int* __restrict__ pre, int n
     return lo;
 }
 
-// Rows of the finest level: velocity (vx, vy), viscosities, right-hand side.
-// zero: the velocity is 0, and not read (rows of no extent).
-template <typename T>
-struct FineRows {
-    const T *vx, *vy, *ec, *en, *bx, *by;
-    int64_t ld;
-    int nx, ny;
-    unsigned o_inner, o_cell;
-    bool zero;
-    __device__ __forceinline__ rows::Row<T> load(int r) const {
-        const size_t w = (size_t)(nx + 1) * sizeof(T);
-        const size_t wx = (r >= 0 && r <= ny - 1) ? w : 0, wy = (r >= 1 && r <= ny - 1) ? w : 0;
-        const int64_t o = (int64_t)r * ld;
-        rows::Row<T> q;
-        q.vx = buf_load<T>(buf_rsrc(vx + o, zero ? 0 : wx), o_inner);
-        q.vy = buf_load<T>(buf_rsrc(vy + o, zero ? 0 : wy), o_cell);
-        q.ec = buf_load<T>(buf_rsrc(ec + o, wx), o_cell);
-        q.en = buf_load<T>(buf_rsrc(en + o, wy), o_inner);
-        q.bx = buf_load<T>(buf_rsrc(bx + o, wx), o_inner);
-        q.by = buf_load<T>(buf_rsrc(by + o, wy), o_cell);
-        q.p = T(0);
-        return q;
-    }
-};
-
 template <typename T, int K, bool SQ>
 __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 3) void k_fine_down(const LevelJob<T>* __restrict__ jobs,
                                                                                const int* __restrict__ pre,
@@ -91,15 +66,13 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 3) void k_fine_down(
     const int nx = J.nx, ny = J.ny, NX = J.cnx, NY = J.cny, lane = threadIdx.x & 63;
     constexpr int M = down_left(K), SWD = down_strip(K);
     const int i = strip_ * SWD - M + lane, y0 = segm * sh.seg, y1 = min(y0 + sh.seg, ny + 1);
-    const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
-    const unsigned col = (unsigned)i * (unsigned)sizeof(T);
-    const FineRows<T> L{io.vx ? (const T*)io.vx : (const T*)J.vx, io.vy ? (const T*)io.vy : (const T*)J.vy,
-                        (const T*)J.ec, (const T*)J.en, io.bx ? (const T*)io.bx : (const T*)J.bx,
-                        io.by ? (const T*)io.by : (const T*)J.by, J.ld, nx, ny, xcol ? col : OOB, ycol ? col : OOB,
-                        io.zero != 0};
     const bool own = lane >= M && lane < M + SWD && i <= nx;
-    const unsigned s_x = own ? col : OOB, s_y = own && ycol ? col : OOB;
-    T *wx = J.wx, *wy = J.wy;
+    const int r0 = y0 - K - 2, r1 = y1 + K + 3;
+    const PipeRows<T> L(io.vx ? (const T*)io.vx : (const T*)J.vx, io.vy ? (const T*)io.vy : (const T*)J.vy,
+                        (const T*)J.ec, (const T*)J.en, io.bx ? (const T*)io.bx : (const T*)J.bx,
+                        io.by ? (const T*)io.by : (const T*)J.by, J.ld, nx, ny, i, r0, r1 - r0 + DOWN_RING + 4,
+                        io.zero != 0);
+    const PipeStore<T> put((T*)J.wx, (T*)J.wy, J.ld, nx, ny, y0, y1, i, own);
     // coarse column of an even lane; weights along x of the vy terms (mirrored at the walls)
     const int I = i >> 1;
     const bool cown = own && (i & 1) == 0;
@@ -112,22 +85,19 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 3) void k_fine_down(
     T *cbx = J.cbx, *cby = J.cby, *ox = J.first ? J.cwx : J.cvx, *oy = J.first ? J.cwy : J.cvy;
     const int64_t cld = J.cld;
     const bool first = J.first != 0;
+    const RowSpan cs(y0 >> 1, (y1 - y0) / 2 + 2, cld, (int)sizeof(T));  // the segment's coarse rows
 
     T rx[4], ry[4];  // residual rows by row modulo 4 (relative to the walk)
 #pragma unroll
     for (int q = 0; q < 4; ++q) rx[q] = ry[q] = T(0);
     auto diag = [&](int jc, T& dx, T& dy) {  // the coarse level's diagonals of coarse row jc
-        const int64_t o = (int64_t)jc * cld;
-        const size_t in = first && jc >= 0 && jc <= NY ? (size_t)(NX + 1) * sizeof(T) : 0;
-        dx = buf_load<T>(buf_rsrc(dgx + o, in), c_x);
-        dy = buf_load<T>(buf_rsrc(dgy + o, in), c_y);
+        const bool in = first && 2 * jc >= y0 && 2 * jc < y1;
+        dx = buf_load_at<T>(cs.of(dgx, cld, in), c_x, cs.at(jc));
+        dy = buf_load_at<T>(cs.of(dgy, cld, in), c_y, cs.at(jc));
     };
-    const int r0 = y0 - K - 2;
-    T dx, dy;
-    diag((y0 >> 1) - 1, dx, dy);
+    T dx = T(0), dy = T(0);
     walk<T, K, SQ, true, DOWN_RING>(
-        L, r0, y1 + K + 3, nx, ny, i, omega, J.idx, J.idy, [](int, int, rows::Row<T>&) {},
-        [&](int j, T ux, T uy) { store_row<T>(wx, wy, J.ld, nx, ny, y0, y1, j, xcol, ycol, ux, uy, s_x, s_y); },
+        L, r0, r1, nx, ny, i, omega, J.idx, J.idy, [](int, int, rows::Row<T>&) {}, put,
         [&](int u, int j, T px, T py) {
             rx[u & 3] = px;
             ry[u & 3] = py;
@@ -168,13 +138,11 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 3) void k_fine_down(
             const T bx = ux ? T(sx) : T(0), by = uy ? T(sy) : T(0);
             const T fx = first && ux ? jac_step<T>(T(0), omega / ex, bx, -T(0)) : T(0);
             const T fy = first && uy ? jac_step<T>(T(0), omega / ey, by, -T(0)) : T(0);
-            const int64_t o = (int64_t)jc * cld;
-            const size_t wx_ = in && jc < NY ? (size_t)(NX + 1) * sizeof(T) : 0;
-            const size_t wy_ = in && jc <= NY ? (size_t)NX * sizeof(T) : 0;
-            buf_store(bx, buf_rsrc(cbx + o, wx_), c_x);
-            buf_store(fx, buf_rsrc(ox + o, wx_), c_x);
-            buf_store(by, buf_rsrc(cby + o, wy_), c_y);
-            buf_store(fy, buf_rsrc(oy + o, wy_), c_y);
+            const unsigned o = cs.at(jc);
+            buf_store_at(bx, cs.of(cbx, cld, in && jc < NY), c_x, o);
+            buf_store_at(fx, cs.of(ox, cld, in && jc < NY), c_x, o);
+            buf_store_at(by, cs.of(cby, cld, in), c_y, o);
+            buf_store_at(fy, cs.of(oy, cld, in), c_y, o);
         });
 }
 
@@ -202,13 +170,12 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 4) void k_fine_up(co
     static_assert(R % 2 == 0, "row parity is that of the step");
     const int i = strip_ * SWU - M + lane, y0 = segm * sh.seg, y1 = min(y0 + sh.seg, ny + 1);
     const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
-    const unsigned col = (unsigned)i * (unsigned)sizeof(T);
-    const FineRows<T> L{(const T*)J.wx, (const T*)J.wy, (const T*)J.ec, (const T*)J.en,
+    const int r0 = y0 - K, r1 = y1 + K;
+    const PipeRows<T> L((const T*)J.wx, (const T*)J.wy, (const T*)J.ec, (const T*)J.en,
                         io.bx ? (const T*)io.bx : (const T*)J.bx, io.by ? (const T*)io.by : (const T*)J.by, J.ld, nx,
-                        ny, xcol ? col : OOB, ycol ? col : OOB, false};
-    const bool own = lane >= M && lane < M + SWU && i <= nx;
-    const unsigned s_x = own ? col : OOB, s_y = own && ycol ? col : OOB;
-    T *vx = io.vx ? (T*)io.vx : (T*)J.vx, *vy = io.vy ? (T*)io.vy : (T*)J.vy;
+                        ny, i, r0, r1 - r0 + R + 4, false);
+    const PipeStore<T> put(io.vx ? (T*)io.vx : (T*)J.vx, io.vy ? (T*)io.vy : (T*)J.vy, J.ld, nx, ny, y0, y1, i,
+                           lane >= M && lane < M + SWU);
     const T *ex = J.cvx, *ey = J.cvy;
     const int64_t cld = J.cld;
     const int I = i >> 1;
@@ -219,13 +186,12 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 4) void k_fine_up(co
     const int nb = odd ? I + 1 : I - 1;
     const bool mirror = nb < 0 || nb >= NX;
     const double a0 = odd ? 0.5 : 1.0, a1 = odd ? 0.5 : 0.0, b0 = mirror ? 1.0 : 0.75, b1 = mirror ? 0.0 : 0.25;
+    const int m0 = r0 >> 1;
+    const RowSpan cs(m0 - 1, (r1 - r0 + R) / 2 + 6, cld, (int)sizeof(T));
     auto cload = [&](int jc, T& x, T& y) {
-        const int64_t o = (int64_t)jc * cld;
-        const size_t w = (size_t)(NX + 1) * sizeof(T);
-        x = buf_load<T>(buf_rsrc(ex + o, jc >= 0 && jc < NY ? w : 0), c_x);
-        y = buf_load<T>(buf_rsrc(ey + o, jc >= 1 && jc <= NY - 1 ? w : 0), c_y);
+        x = buf_load_at<T>(cs.of(ex, cld, jc >= 0 && jc < NY), c_x, cs.at(jc));
+        y = buf_load_at<T>(cs.of(ey, cld, jc >= 1 && jc <= NY - 1), c_y, cs.at(jc));
     };
-    const int r0 = y0 - K, m0 = r0 >> 1;
     CoarseRows<T> c;
     T drop;
     cload(m0 - 1, c.x0, drop);
@@ -233,7 +199,7 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 4) void k_fine_up(co
     cload(m0 + 1, c.x2, c.y2);
     cload(m0 + 2, c.x3, c.y3);
     walk<T, K, SQ, false, R>(
-        L, r0, y1 + K, nx, ny, i, omega, J.idx, J.idy,
+        L, r0, r1, nx, ny, i, omega, J.idx, J.idy,
         [&](int u, int r, rows::Row<T>& w) {  // row r of w arrives: + P e_c on its unknowns
             const bool rodd = (u + K) & 1;    // y0 is even
             const int m = r >> 1;
@@ -271,14 +237,14 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 4) void k_fine_up(co
                 cload(m + 3, c.x3, c.y3);
             }
         },
-        [&](int j, T ux, T uy) { store_row<T>(vx, vy, J.ld, nx, ny, y0, y1, j, xcol, ycol, ux, uy, s_x, s_y); },
-        [](int, int, T, T) {});
+        put, [](int, int, T, T) {});
 }
 
 // Rows per wave (even), shared by the instances of a batch: the launch is modelled as
 // (waves per SIMD, at least 1.2, whole ones beyond those that fit at once) x (rows
 // walked, `fill` of them to fill the pipeline, in whole trips).
-int fine_rows(const stk_ctx* ctx, const int* nx, const int* ny, int n, int strip_, int fill, int trip, int per_simd) {
+int fine_rows(const stk_ctx* ctx, const int* nx, const int* ny, int n, int strip_, int fill, int trip, int per_simd,
+              int most) {
     const int64_t cu4 = (int64_t)std::max(ctx->num_cu, 1) * 4;
     int best = 2;
     double cost = 1e300;
@@ -286,7 +252,7 @@ int fine_rows(const stk_ctx* ctx, const int* nx, const int* ny, int n, int strip
     for (int q = 0; q < n; ++q) maxny = std::max(maxny, ny[q]);
     for (int steps = trip; steps < maxny + 2 + fill + trip; steps += trip) {
         const int H = (steps - fill) / 2 * 2;
-        if (H < 2) continue;
+        if (H < 2 || H > most) continue;
         int64_t waves = 0;
         for (int q = 0; q < n; ++q)
             waves += (int64_t)((nx[q] + strip_) / strip_) * ((ny[q] + H) / H);
@@ -315,11 +281,15 @@ int launch_fine(stk_ctx* ctx, const Batch& b, const FineShape* shapes, double om
 
 }  // namespace
 
-void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, int K, bool up,
+bool mg_fine_takes(int es, int64_t ld) { return max_rows(ld, es) >= 128; }
+
+void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, const int64_t* ld, int n, int K, bool up,
                    std::vector<FineShape>* shapes, std::vector<int>* pre) {
     const int sw = up ? up_strip(K) : down_strip(K), fill = up ? 2 * K : 2 * K + 5;
     const int trip = up ? (es == 8 ? ring_rows<double>(K) : ring_rows<float>(K)) : DOWN_RING;
-    const int H = fine_rows(ctx, nx, ny, n, sw, fill, trip, es == 8 ? 2 : 3);
+    int most = INT32_MAX;
+    for (int q = 0; q < n; ++q) most = std::min(most, max_rows(ld[q], es) - 64);
+    const int H = fine_rows(ctx, nx, ny, n, sw, fill, trip, es == 8 ? 2 : 3, most);
     shapes->clear();
     pre->assign(1, 0);
     for (int q = 0; q < n; ++q) {

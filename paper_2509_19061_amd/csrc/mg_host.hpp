@@ -52,6 +52,7 @@ struct PlanT {
     // over its tiles); the restriction's first sweep then goes to v
     bool pair = false;
     std::vector<Batch> fine_p;
+    std::vector<char> small_p;  // its smaller regions
     // default smoothing: the finest level in one pass each way (mg_fine.hip), with
     // the launch shapes of the instances; square: all have square cells
     bool fused = false, square = false;

@@ -108,8 +108,9 @@ template <typename T> int mg_jacobi_prolonged(stk_ctx* ctx, const Batch& b, doub
 // Stored-stencil levels smoothed by two sweeps, one pass each way (mg_pair.hip;
 // b's prefix counts mg_pair_tiles per instance): down w <- the second
 // pre-sweep of v, r <- its residual; up v <- two sweeps of w + P e_c.
-template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up);
-int mg_pair_tiles(int nx, int ny);
+// small: the smaller regions, for batches of at most about one per CU.
+template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, bool small);
+int mg_pair_tiles(int nx, int ny, bool small);
 // Finest level in one pass each way (mg_fine.hip), K = 1 .. MG_FINE_MAX sweeps.
 // down: w <- K sweeps of v; the residual of w restricted to the coarse
 // right-hand side, and the coarse iterate 0 or (jobs with `first`) its first
@@ -125,7 +126,8 @@ struct FineIo {
     int zero = 0;
 };
 constexpr int MG_FINE_MAX = 3;
-void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, int K, bool up,
+bool mg_fine_takes(int es, int64_t ld);  // rows short enough for 32-bit offsets in a wave's window
+void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, const int64_t* ld, int n, int K, bool up,
                    std::vector<FineShape>* shapes, std::vector<int>* pre);
 template <typename T>
 int mg_fine(stk_ctx* ctx, const Batch& b, const FineShape* shapes, int K, bool square, double omega, bool up,

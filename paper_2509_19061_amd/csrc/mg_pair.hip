@@ -12,10 +12,15 @@
 // computed on the whole region, into a second window, the second on the region
 // without its two-cell rim, which is what the workgroup owns.
 //
-// Why this region: the coefficients (62 VGPRs in FP64) must fit 128 VGPRs at 16
-// waves, so a workgroup holds 512 positions; 32 x 16 leaves 28 x 12 = 66 % of
-// them owned (64 x 8 would leave 47 %).  The rim's coefficients are the
-// neighbours' own and come from L2.
+// Why these regions: with the coefficients (62 VGPRs in FP64) at most 128 VGPRs
+// a thread allow 16 waves per CU, 512 positions.  A region of 32 x 16 owns 66 %
+// of its positions (64 x 8 would own 47 %) and takes about 10 us, however few
+// there are; one of 16 x 16 owns 56 % and takes 7.5 us, so it serves levels whose
+// regions all run at once (a 128^2 level: 8.3 against 10.9 us; 256^2: 13.4
+// against 12.0; 1024^2: 144 against 136).  The rim's coefficients are the
+// neighbours' own and come from L2.  The large levels are bound by the sum of
+// what a region does in turn: L1 accesses for the coefficients, LDS reads and
+// the row sums.
 //
 // The row sums run in the slot order of stencil_av_l on the same operands, and
 // the updates are the shared ones, so the values are the bits of the separate
@@ -28,10 +33,9 @@
 namespace stk {
 namespace {
 
-constexpr int RX = 16, RY = 16, NPOS = RX * RY, NTH = 2 * NPOS;
-constexpr int RIM = 2;                                // reach of the stencil
-constexpr int OX = RX - 2 * RIM, OY = RY - 2 * RIM;   // owned positions
-constexpr int WX = RX + 2 * RIM, WY = RY + 2 * RIM;   // window of the first application
+constexpr int RIM = 2;  // reach of the stencil
+constexpr int RY = 16, OY = RY - 2 * RIM, WY = RY + 2 * RIM;  // region, owned and first window rows
+constexpr int RX_WIDE = 32, RX_SMALL = 16;
 constexpr int DIAG[2] = {7, 23};                      // slots of the diagonals
 static_assert(offset_slot(0, 0, 0, 0) == DIAG[0] && offset_slot(1, 1, 0, 0) == DIAG[1], "diagonal slots");
 
@@ -75,9 +79,10 @@ __device__ __forceinline__ T row_sum(const T (&cf)[NCOEF], const T* win, int str
 
 // UP = false: v holds the first sweep; w <- the second, r <- its residual.
 // UP = true: v <- two sweeps of w + P e_c.
-template <typename T, bool UP>
-__global__ __launch_bounds__(NTH, 4) void k_mg_pair(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
-                                                 int n, T omega) {
+template <typename T, bool UP, int RX>
+__global__ __launch_bounds__(2 * RX * RY, 4) void k_mg_pair(const LevelJob<T>* __restrict__ jobs,
+                                                            const int* __restrict__ pre, int n, T omega) {
+    constexpr int NPOS = RX * RY, NTH = 2 * NPOS, OX = RX - 2 * RIM, WX = RX + 2 * RIM;
     __shared__ T win[2 * WX * WY], mid[2 * NPOS];
     const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int inst = find_pair_inst(pre, n, b);
@@ -137,22 +142,28 @@ __global__ __launch_bounds__(NTH, 4) void k_mg_pair(const LevelJob<T>* __restric
 
 }  // namespace
 
-int mg_pair_tiles(int nx, int ny) { return ((nx + 1 + OX - 1) / OX) * ((ny + 1 + OY - 1) / OY); }
+int mg_pair_tiles(int nx, int ny, bool small) {
+    const int ox = (small ? RX_SMALL : RX_WIDE) - 2 * RIM;
+    return ((nx + 1 + ox - 1) / ox) * ((ny + 1 + OY - 1) / OY);
+}
 
 template <typename T>
-int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up) {
+int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, bool small) {
     if (!b.n) return STK_OK;
-    const dim3 grid((unsigned)b.blocks), block(NTH);
-    if (up)
-        hipLaunchKernelGGL((k_mg_pair<T, true>), grid, block, 0, ctx->stream, static_cast<const LevelJob<T>*>(b.jobs),
-                           b.pre, b.n, T(omega));
+    const auto* jobs = static_cast<const LevelJob<T>*>(b.jobs);
+    const dim3 grid((unsigned)b.blocks), block(2 * (small ? RX_SMALL : RX_WIDE) * RY);
+    if (up && small)
+        hipLaunchKernelGGL((k_mg_pair<T, true, RX_SMALL>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
+    else if (up)
+        hipLaunchKernelGGL((k_mg_pair<T, true, RX_WIDE>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
+    else if (small)
+        hipLaunchKernelGGL((k_mg_pair<T, false, RX_SMALL>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
     else
-        hipLaunchKernelGGL((k_mg_pair<T, false>), grid, block, 0, ctx->stream, static_cast<const LevelJob<T>*>(b.jobs),
-                           b.pre, b.n, T(omega));
+        hipLaunchKernelGGL((k_mg_pair<T, false, RX_WIDE>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
-template int mg_pair<double>(stk_ctx*, const Batch&, double, bool);
-template int mg_pair<float>(stk_ctx*, const Batch&, double, bool);
+template int mg_pair<double>(stk_ctx*, const Batch&, double, bool, bool);
+template int mg_pair<float>(stk_ctx*, const Batch&, double, bool, bool);
 
 }  // namespace stk

@@ -82,8 +82,8 @@ int launch_residual_to32(stk_ctx* ctx, const stk_grid* g, const double* vx, cons
 // PIPE_MAX_SWEEPS), out of place; every velocity entry of the used extents is
 // written (walls 0).
 constexpr int PIPE_MAX_SWEEPS = 10;
-// Its rows are addressed through 32-bit buffer offsets: false where a row is
-// 2 GiB or longer.
+// A wave addresses its rows by 32-bit offsets: false where 192 rows are 4 GiB or
+// more (rows of 22 MB).
 bool jacobi_pipe_takes(stk_dtype dt, const stk_grid* g);
 // Sweeps of the next pass when `left` are to be done.
 int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int left);

@@ -34,6 +34,22 @@ __device__ __forceinline__ float buf_load<float>(__amdgpu_buffer_rsrc_t r, unsig
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
+// The same loads and stores at a uniform offset `s` beyond the lane's: a lane is out
+// of range by its own offset alone, and an array of no extent (bytes = 0) reads 0.
+template <typename T>
+__device__ __forceinline__ T buf_load_at(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned s) {
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)s, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)s, 0));
+}
+__device__ __forceinline__ void buf_store_at(double v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned s) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, (int)s, 0);
+}
+__device__ __forceinline__ void buf_store_at(float v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned s) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, (int)s, 0);
+}
+
 // Neighbour exchange inside a wave whose lane is a grid column: lane i gets
 // the value of lane i + 1 (DPP wave_shl:1) or of lane i - 1 (wave_shr:1); a
 // lane whose source is outside the wave gets 0.
