@@ -118,6 +118,7 @@ int stk_ctx_destroy(stk_ctx* ctx) {
     for (int s = 0; s < stk_ctx::S_NSLOT; ++s)
         if (ctx->slot[s]) (void)hipFree(ctx->slot[s]);
     if (ctx->host_red) (void)hipHostFree(ctx->host_red);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     delete ctx;
     return STK_OK;
 }

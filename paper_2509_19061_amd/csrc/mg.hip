@@ -51,16 +51,33 @@ static int pdalloc(PlanT* P, size_t bytes, void** out, hipStream_t s) {
     *out = p;
     return STK_OK;
 }
+// Room for h in the plan's blocks (upload_blocks fills it); an array starts on a
+// 256-byte boundary.
 template <typename V>
-static int upload(PlanT* P, const std::vector<V>& h, const void** out, hipStream_t s) {
-    void* d = nullptr;
-    STK_TRY(pdalloc(P, std::max<size_t>(1, h.size()) * sizeof(V), &d, s));
-    if (!h.empty()) {  // the host copy stays alive until the plan's final synchronisation
-        const auto* b = reinterpret_cast<const unsigned char*>(h.data());
-        P->stage.emplace_back(b, b + h.size() * sizeof(V));
-        STK_HIP(hipMemcpyAsync(d, P->stage.back().data(), P->stage.back().size(), hipMemcpyHostToDevice, s));
+static int upload(PlanT* P, const std::vector<V>& h, const void** out) {
+    constexpr size_t BLOCK = 64 << 10, ALIGN = 256;
+    const size_t bytes = h.size() * sizeof(V), need = (std::max<size_t>(1, bytes) + ALIGN - 1) / ALIGN * ALIGN;
+    if (P->blocks.empty() || P->blocks.back().size - P->blocks.back().used < need) {
+        const size_t size = std::max(BLOCK, need);
+        void* d = nullptr;
+        hipError_t e = hipMalloc(&d, size);
+        if (e != hipSuccess) return set_error(STK_ENOMEM, "hipMalloc(%zu) failed: %s", size, hipGetErrorString(e));
+        P->mem.push_back(d);
+        P->blocks.push_back(PlanT::Block{static_cast<unsigned char*>(d), size, 0, {}});
     }
-    *out = d;
+    PlanT::Block& B = P->blocks.back();
+    const size_t at = B.used;
+    B.used += need;
+    B.image.resize(B.used);  // zeros where the array ends before its room does
+    if (bytes) std::memcpy(B.image.data() + at, h.data(), bytes);
+    *out = B.dev + at;
+    return STK_OK;
+}
+static int upload_blocks(PlanT* P, hipStream_t s) {
+    for (PlanT::Block& B : P->blocks)
+        STK_HIP(hipMemcpyAsync(B.dev, B.image.data(), B.used, hipMemcpyHostToDevice, s));
+    STK_HIP(hipStreamSynchronize(s));  // the images are freed
+    P->blocks.clear();
     return STK_OK;
 }
 
@@ -493,36 +510,36 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
         }
         if (!rj.empty()) {
             const void *dj = nullptr, *dpf = nullptr, *dpt = nullptr;
-            STK_TRY(upload(P, rj, &dj, s));
-            STK_TRY(upload(P, rpf, &dpf, s));
-            STK_TRY(upload(P, rpt, &dpt, s));
+            STK_TRY(upload(P, rj, &dj));
+            STK_TRY(upload(P, rpf, &dpf));
+            STK_TRY(upload(P, rpt, &dpt));
             P->relax[d] = Batch{dj, (const int*)dpf, (int)rj.size(), rpf.back()};
             P->relax_t[d] = Batch{dj, (const int*)dpt, (int)rj.size(), rpt.back()};
         }
         if (!jobs.empty()) {
             const void* dj = nullptr;
             const void *dpf = nullptr, *dpc = nullptr;
-            STK_TRY(upload(P, jobs, &dj, s));
-            STK_TRY(upload(P, pf, &dpf, s));
-            STK_TRY(upload(P, pc, &dpc, s));
+            STK_TRY(upload(P, jobs, &dj));
+            STK_TRY(upload(P, pf, &dpf));
+            STK_TRY(upload(P, pc, &dpc));
             P->fine[d] = Batch{dj, (const int*)dpf, (int)jobs.size(), pf.back()};
             P->crs[d] = Batch{dj, (const int*)dpc, (int)jobs.size(), pc.back()};
             if (d >= 1 && cras) {
                 const void* dpt = nullptr;
-                STK_TRY(upload(P, pt, &dpt, s));
+                STK_TRY(upload(P, pt, &dpt));
                 P->fine_t[d] = Batch{dj, (const int*)dpt, (int)jobs.size(), pt.back()};
             }
             if (d >= 1 && P->pair) {
                 const void* dpp = nullptr;
                 const bool small = ps.back() <= ctx->num_cu;
                 if (small) pp = ps;
-                STK_TRY(upload(P, pp, &dpp, s));
+                STK_TRY(upload(P, pp, &dpp));
                 P->fine_p[d] = Batch{dj, (const int*)dpp, (int)jobs.size(), pp.back()};
                 P->small_p[d] = small;
             }
             if (d == 0) {  // the finest level is matrix-free: row-streaming smoothing and residual
                 const void* dpr = nullptr;
-                STK_TRY(upload(P, pr, &dpr, s));
+                STK_TRY(upload(P, pr, &dpr));
                 P->fine[d].rpre = (const int*)dpr;
                 P->fine[d].rblocks = pr.back();
                 // RAS smoothing v -> w -> v, and the level jobs with v and w exchanged
@@ -542,10 +559,10 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     P->l0ny.push_back(J.ny);
                     P->l0ld.push_back(J.ld);
                 }
-                STK_TRY(upload(P, vw, &P->ras_jobs[0], s));
-                STK_TRY(upload(P, wv, &P->ras_jobs[1], s));
+                STK_TRY(upload(P, vw, &P->ras_jobs[0]));
+                STK_TRY(upload(P, wv, &P->ras_jobs[1]));
                 const void* dsw = nullptr;
-                STK_TRY(upload(P, sw, &dsw, s));
+                STK_TRY(upload(P, sw, &dsw));
                 P->fine0w = P->fine[d];
                 P->fine0w.jobs = dsw;
                 P->fused = takes_fused(mgs, n, t);
@@ -557,15 +574,15 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     mg_fine_shape(ctx, (int)sizeof(T), P->l0nx.data(), P->l0ny.data(), P->l0ld.data(), (int)jobs.size(),
                                   up ? o0.nu2 : o0.nu1, up, &fs, &fp);
                     const void *dfs = nullptr, *dfp = nullptr;
-                    STK_TRY(upload(P, fs, &dfs, s));
-                    STK_TRY(upload(P, fp, &dfp, s));
+                    STK_TRY(upload(P, fs, &dfs));
+                    STK_TRY(upload(P, fp, &dfp));
                     (up ? P->fine_up : P->fine_dn) = Batch{dj, (const int*)dfp, (int)jobs.size(), fp.back()};
                     (up ? P->up_shapes : P->dn_shapes) = static_cast<const FineShape*>(dfs);
                 }
             }
         }
         if (!cj.empty()) {
-            STK_TRY(upload(P, cj, &P->cjobs[d], s));
+            STK_TRY(upload(P, cj, &P->cjobs[d]));
             P->ncj[d] = (int)cj.size();
         }
     }
@@ -612,19 +629,19 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
         xj.push_back(X);
     }
     const void *daj = nullptr, *dpa = nullptr, *dvj = nullptr, *dxj = nullptr;
-    STK_TRY(upload(P, aj, &daj, s));
-    STK_TRY(upload(P, pa, &dpa, s));
-    STK_TRY(upload(P, vj, &dvj, s));
+    STK_TRY(upload(P, aj, &daj));
+    STK_TRY(upload(P, pa, &dpa));
+    STK_TRY(upload(P, vj, &dvj));
     P->apply = Batch{daj, (const int*)dpa, n, pa.back()};
     {  // row-streaming prefix of the operator batch and its reduction chunks
         const void* dpra = nullptr;
-        STK_TRY(upload(P, pra, &dpra, s));
+        STK_TRY(upload(P, pra, &dpra));
         P->apply.rpre = (const int*)dpra;
         P->apply.rblocks = pra.back();
         std::vector<int> cp{0};
         for (int q = 0; q < n; ++q) cp.push_back(cp.back() + (pra[q + 1] - pra[q] + SUM_CHUNK - 1) / SUM_CHUNK);
         const void* dcp = nullptr;
-        STK_TRY(upload(P, cp, &dcp, s));
+        STK_TRY(upload(P, cp, &dcp));
         P->applyr = Batch{nullptr, (const int*)dpra, n, pra.back()};
         P->applyr.cpre = static_cast<const int*>(dcp);
     }
@@ -633,23 +650,22 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
         std::vector<int> cp{0};
         for (int q = 0; q < n; ++q) cp.push_back(cp.back() + (pa[q + 1] - pa[q] + SUM_CHUNK - 1) / SUM_CHUNK);
         const void* dcp = nullptr;
-        STK_TRY(upload(P, cp, &dcp, s));
+        STK_TRY(upload(P, cp, &dcp));
         P->vec.cpre = static_cast<const int*>(dcp);
     }
     if (t == 1) {  // casts between the FP64 Krylov slots and this plan's FP32 V-cycle slots
-        STK_TRY(upload(P, xj, &dxj, s));
+        STK_TRY(upload(P, xj, &dxj));
         P->xcast = Batch{dxj, (const int*)dpa, n, pa.back()};
     }
-    void *st = nullptr, *part = nullptr, *sums = nullptr;
-    STK_TRY(pdalloc(P, sizeof(FcgState) * n, &st, s));
-    STK_TRY(pdalloc(P, sizeof(double) * 2 * (size_t)pa.back(), &part, s));
-    STK_TRY(pdalloc(P, sizeof(double) * 2 * (size_t)n, &sums, s));
-    P->st = static_cast<FcgState*>(st);
-    P->part = static_cast<double*>(part);
-    P->sums = static_cast<double*>(sums);
-    STK_HIP(hipStreamSynchronize(s));
-    P->stage.clear();
-    return STK_OK;
+    // partials of the reductions, per-instance sums and states
+    static_assert(sizeof(FcgState) % 8 == 0, "the states follow arrays of doubles");
+    const size_t np = 2 * (size_t)pa.back(), nsum = 2 * (size_t)n;
+    void* scratch = nullptr;
+    STK_TRY(pdalloc(P, sizeof(double) * (np + nsum) + sizeof(FcgState) * n, &scratch, s));
+    P->part = static_cast<double*>(scratch);
+    P->sums = P->part + np;
+    P->st = reinterpret_cast<FcgState*>(P->sums + nsum);
+    return upload_blocks(P, s);
 }
 
 int make_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT** out, bool z32) {

@@ -87,14 +87,7 @@ struct stk_batch {
     // iteration ahead made a serving loop that sets requests up on another
     // stream meanwhile 35 % slower.
     bool lookahead = false;
-    // pinned host copy of the member states, read once per iteration; the reduction
-    // kernel that updates them writes it on the solve's stream (a copy-engine
-    // transfer would queue behind unrelated uploads: requests being set up on
-    // another stream while the batch runs)
-    FcgState* pin = nullptr;
-    FcgState* pin_dev = nullptr;  // its device-side address
-    int npin = 0;
-    hipEvent_t ev = nullptr;  // marks that copy in the stream
+    hipEvent_t ev = nullptr;  // marks the copy of the member states (ctx->pin) in the stream
 };
 
 namespace stk {
@@ -114,18 +107,23 @@ int plans_for(stk_batch* b, const std::vector<int>& ids, PlanT** P, PlanT** P32)
     return STK_OK;
 }
 
+// The pinned host copy of the member states, read once per iteration; the reduction
+// kernel that updates them writes it on the solve's stream (a copy-engine transfer
+// would queue behind unrelated uploads: requests being set up on another stream while
+// the batch runs).  The context keeps it (allocating and freeing it took 0.1 ms a
+// solve): only stk_mg_solve_batch uses it, which runs to its end in one call.
 int ensure_pinned(stk_batch* b, int n) {
+    stk_ctx* ctx = b->ctx;
     if (!b->ev) STK_HIP(hipEventCreateWithFlags(&b->ev, hipEventDisableTiming));
-    if (b->npin >= n) return STK_OK;
-    if (b->pin) STK_HIP(hipHostFree(b->pin));
-    b->pin = b->pin_dev = nullptr;
-    b->npin = 0;
-    STK_HIP(hipHostMalloc(reinterpret_cast<void**>(&b->pin), sizeof(FcgState) * (size_t)n, hipHostMallocCoherent));
-    STK_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&b->pin_dev), b->pin, 0));
-    b->npin = n;
+    if (ctx->npin >= n) return STK_OK;
+    if (ctx->pin) STK_HIP(hipHostFree(ctx->pin));
+    ctx->pin = ctx->pin_dev = nullptr;
+    ctx->npin = 0;
+    STK_HIP(hipHostMalloc(&ctx->pin, sizeof(FcgState) * (size_t)n, hipHostMallocCoherent));
+    STK_HIP(hipHostGetDevicePointer(&ctx->pin_dev, ctx->pin, 0));
+    ctx->npin = n;
     return STK_OK;
 }
-
 
 // Write the solution to the caller's arrays and fill the report (the true
 // residual of the slot's last CHECK is in its state).
@@ -142,6 +140,7 @@ int finish(stk_batch* b, int id, stk_report* rep) {
     rep->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - s.t0).count();
     m->busy = false;
     s = Slot{};
+    b->members.clear();  // the main plan names this slot's arrays
     b->dirty = true;
     return STK_OK;
 }
@@ -153,11 +152,16 @@ int start_phase(stk_batch* b, int* done, stk_report* reps, int* ndone) {
         if (b->slots[i].state == SL_NEW || b->slots[i].state == SL_CHECK) ids.push_back(i);
     if (ids.empty()) return STK_OK;
     stk_ctx* ctx = b->ctx;
-    PlanT *Q = nullptr, *Q32 = nullptr;
-    STK_TRY(plans_for(b, ids, &Q, &Q32));
+    // The main plan serves slots that are exactly its members, so a solve that starts,
+    // iterates and ends with the same slots builds one plan and not three.
+    const bool own = ids != b->members;
+    PlanT *Q = b->P, *Q32 = b->P32;
+    if (own) STK_TRY(plans_for(b, ids, &Q, &Q32));
     auto fail = [&](int rc) {
-        free_plan(Q);
-        free_plan(Q32);
+        if (own) {
+            free_plan(Q);
+            free_plan(Q32);
+        }
         return rc;
     };
     const int n = (int)ids.size();
@@ -214,9 +218,21 @@ int start_phase(stk_batch* b, int* done, stk_report* reps, int* ndone) {
             b->dirty = true;
         }
     }
-    free_plan(Q);
-    free_plan(Q32);
-    return STK_OK;
+    std::vector<int> iter;
+    for (int i = 0; i < (int)b->slots.size(); ++i)
+        if (b->slots[i].state == SL_ITER) iter.push_back(i);
+    if (iter == ids) {  // they all go on, alone
+        if (own) {
+            free_plan(b->P);
+            free_plan(b->P32);
+            b->P = Q;
+            b->P32 = Q32;
+            b->members = ids;
+        }
+        b->dirty = false;
+        return STK_OK;
+    }
+    return fail(STK_OK);
 }
 
 // Up to `iters` CG iterations of every ITER slot, all in the same launches.
@@ -228,9 +244,13 @@ int iterate_phase(stk_batch* b, int iters) {
         b->members.clear();
         for (int i = 0; i < (int)b->slots.size(); ++i)
             if (b->slots[i].state == SL_ITER) b->members.push_back(i);
+        if (!b->members.empty()) {
+            if (int rc = plans_for(b, b->members, &b->P, &b->P32)) {
+                b->members.clear();  // no plan: the next step builds it
+                return rc;
+            }
+        }
         b->dirty = false;
-        if (b->members.empty()) return STK_OK;
-        STK_TRY(plans_for(b, b->members, &b->P, &b->P32));
     }
     if (b->members.empty()) return STK_OK;
     const PlanT& P = *b->P;
@@ -272,7 +292,7 @@ int iterate_phase(stk_batch* b, int iters) {
             // them: the GPU does not wait for the host between iterations.  An instance
             // that stopped here is skipped by the Krylov kernels, and its preconditioner
             // output is recomputed before it is used again.
-            STK_TRY(fcg_reduce(ctx, P.vec, P.part, P.sums, P.st, PH_NV, b->pin_dev));
+            STK_TRY(fcg_reduce(ctx, P.vec, P.part, P.sums, P.st, PH_NV, static_cast<FcgState*>(ctx->pin_dev)));
             STK_HIP(hipEventRecord(b->ev, ctx->stream));
         } else {
             STK_TRY(fcg_reduce(ctx, P.vec, P.part, P.sums, P.st, PH_NV));
@@ -285,7 +305,7 @@ int iterate_phase(stk_batch* b, int iters) {
         STK_TRY(vec_op<double>(ctx, P.vec, OP_XPBY, P.st, P.part, P.vec_z32));
         if (b->lookahead) {
             STK_HIP(hipEventSynchronize(b->ev));
-            if (!take(b->pin)) break;
+            if (!take(static_cast<const FcgState*>(ctx->pin))) break;
         }
     }
     STK_TRY(read_states(ctx, P, h));
@@ -319,7 +339,6 @@ int stk_batch_destroy(stk_batch* b) {
         if (s.m) s.m->busy = false;
     free_plan(b->P);
     free_plan(b->P32);
-    if (b->pin) (void)hipHostFree(b->pin);
     if (b->ev) (void)hipEventDestroy(b->ev);
     delete b;
     return STK_OK;

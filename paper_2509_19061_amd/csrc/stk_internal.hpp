@@ -21,6 +21,10 @@ struct stk_ctx {
     void* slot[S_NSLOT] = {};
     size_t slot_bytes[S_NSLOT] = {};
     double* host_red = nullptr;  // pinned host landing buffer for reductions
+    // pinned host landing buffer for the states of a solve's instances (solve.hip), its
+    // device-side address and its capacity in instances
+    void *pin = nullptr, *pin_dev = nullptr;
+    int npin = 0;
 };
 
 namespace stk {
