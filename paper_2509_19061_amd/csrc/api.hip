@@ -49,6 +49,26 @@ int scratch(stk_ctx* ctx, int s, size_t bytes, void** out) {
     return STK_OK;
 }
 
+// Can red-black Gauss-Seidel take the pipelined passes?  They are out of place; its
+// half-sweeps are in place and need no scratch, so they stay for what the passes cannot
+// do: rows too long, no memory left for the scratch arrays, or a stream being captured
+// (where none may be allocated) with a context that does not hold them yet.
+bool rbgs_has_scratch(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, size_t bytes, int passes) {
+    if (!jacobi_pipe_takes(dt, g)) return false;
+    constexpr int slots[] = {stk_ctx::S_VX, stk_ctx::S_VY, stk_ctx::S_VX2, stk_ctx::S_VY2};
+    for (int q = 0; q < (passes >= 3 ? 4 : 2); ++q) {
+        if (ctx->slot_bytes[slots[q]] >= bytes) continue;
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        void* p = nullptr;
+        if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone ||
+            scratch(ctx, slots[q], bytes, &p) != STK_OK) {
+            (void)hipGetLastError();
+            return false;
+        }
+    }
+    return true;
+}
+
 int check_grid(const stk_grid* g) {
     if (!g) return set_error(STK_EINVAL, "grid is NULL");
     if (g->nx < 2 || g->ny < 2) return set_error(STK_EINVAL, "nx, ny must be >= 2 (got %d, %d)", g->nx, g->ny);
@@ -224,7 +244,8 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
         f.bx = bx;
         f.by = by;
     }
-    if (variant == STK_RBGS) {
+    const int kr = rbgs_pipe_sweeps(sweeps);
+    if (variant == STK_RBGS && !rbgs_has_scratch(ctx, dt, g, vbytes, (sweeps + kr - 1) / kr)) {
         STK_TRY(launch_zero_walls(ctx, dt, g, vx, vy));
         for (int s = 0; s < sweeps; ++s) STK_TRY(launch_rbgs(ctx, dt, g, f, omega, vx, vy));
         return STK_OK;
@@ -232,10 +253,10 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
 
     // Jacobi in either form, and RAS whose overlap covers its sweeps, are all exactly
     // `total` Jacobi sweeps: passes of as many sweeps as the pipelined kernel runs best.
-    const bool ras = variant == STK_RAS_JACOBI;
+    const bool ras = variant == STK_RAS_JACOBI, rbgs = variant == STK_RBGS;
     const int total = ras && !o.last_partial ? nouter * o.k : sweeps;
-    const bool piped = jacobi_pipe_takes(dt, g) && (!ras || (ctx->ras_kernel == 0 && h >= o.k - 1));
-    const int kp = piped ? jacobi_pipe_sweeps(ctx, dt, g, total) : 0;
+    const bool piped = rbgs || (jacobi_pipe_takes(dt, g) && (!ras || (ctx->ras_kernel == 0 && h >= o.k - 1)));
+    const int kp = rbgs ? kr : piped ? jacobi_pipe_sweeps(ctx, dt, g, total) : 0;
 
     // Out-of-place steps: the first reads the caller's arrays, the last writes them, and the
     // ones between alternate over two scratch pairs, so no copy is needed for n >= 2 steps
@@ -261,7 +282,8 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
         }
         if (piped) {
             const int kt = (left + (n - t) - 1) / (n - t);  // equal passes
-            STK_TRY(launch_jacobi_pipe(ctx, dt, g, f, omega, kt, cx, cy, dx, dy));
+            if (rbgs) STK_TRY(launch_rbgs_pipe(ctx, dt, g, f, omega, kt, cx, cy, dx, dy));
+            else STK_TRY(launch_jacobi_pipe(ctx, dt, g, f, omega, kt, cx, cy, dx, dy));
             left -= kt;
         } else if (!ras) {
             STK_TRY(launch_jacobi_split(ctx, dt, g, f, omega, cx, cy, dx, dy));

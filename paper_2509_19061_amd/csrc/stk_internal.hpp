@@ -97,6 +97,11 @@ int launch_jacobi_split(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const Fie
                         const void* vx, const void* vy, void* ox, void* oy);
 int launch_zero_walls(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy);
 int launch_rbgs(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, void* vx, void* vy);
+// `sweeps` red-black Gauss-Seidel sweeps in one pass, out of place (what jacobi_pipe_takes);
+// rbgs_pipe_sweeps: those of the next pass when `left` are to be done.
+int rbgs_pipe_sweeps(int left);
+int launch_rbgs_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int sweeps,
+                     const void* vx, const void* vy, void* ox, void* oy);
 // RAS outer iteration; returns STK_EUNSUPPORTED when the tile does not fit.
 int ras_lds_bytes(stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, size_t* bytes);
 int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int tile_x,
