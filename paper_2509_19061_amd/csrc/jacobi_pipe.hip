@@ -11,10 +11,6 @@ namespace {
 
 using namespace pipe;
 
-// Waves per SIMD the registers must leave room for.
-template <typename T>
-constexpr int pipe_occupancy(int K) { return sizeof(T) == 8 ? (K <= 3 ? 3 : K <= 7 ? 2 : 1) : (K <= 4 ? 4 : K <= 8 ? 3 : 2); }
-
 template <typename T, int K, bool SQ>
 __global__ __launch_bounds__(64 * WPB, pipe_occupancy<T>(K)) void k_jacobi_pipe(Grid<T> g, const T* __restrict__ vx,
                                                                                const T* __restrict__ vy,
@@ -28,15 +24,9 @@ __global__ __launch_bounds__(64 * WPB, pipe_occupancy<T>(K)) void k_jacobi_pipe(
     const int r0 = y0 - K, r1 = y0 + sh.seg + K;
     const PipeRows<T> L(vx, vy, g.ec, g.en, g.bx, g.by, g.ld, nx, ny, i, r0, r1 - r0 + ahead<T>(), false);
     const PipeStore<T> put(ox, oy, g.ld, nx, ny, y0, y1, i, lane >= K && lane < 64 - K);
-    walk<T, K, SQ, false, ring_rows<T>(K)>(L, r0, r1, nx, ny, i, g.omega, g.idx, g.idy, [](int, int, rows::Row<T>&) {},
-                                           put, [](int, int, T, T) {});
+    walk<T, K, SQ, false, ring_rows<T>(K)>(L, r0, r1, AllCells(nx, ny, i), g.omega, g.idx, g.idy,
+                                           [](int, int, rows::Row<T>&) {}, put, [](int, int, T, T) {});
 }
-
-// Time of one step of one wave that has the SIMD to itself, in us: about 217
-// (FP64, K = 7) or 180 (FP32, K = 8) vector instructions; measured 0.48 and
-// 0.30 (2048^2, two waves per SIMD).
-template <typename T>
-double step_us(int K) { return sizeof(T) == 8 ? 2.2e-3 * (30 + 27 * K) : 1.6e-3 * (44 + 17 * K); }
 
 // Launch shape: about w waves per SIMD, w = 1, 2, ..., each a segment of equal
 // rows (rounded so that the walk is a whole number of unrolled trips).  The

@@ -62,6 +62,16 @@ struct Shape {
     int K, nstrip, nseg, seg;
 };
 
+// Waves per SIMD the registers of K sweeps must leave room for.
+template <typename T>
+constexpr int pipe_occupancy(int K) { return sizeof(T) == 8 ? (K <= 3 ? 3 : K <= 7 ? 2 : 1) : (K <= 4 ? 4 : K <= 8 ? 3 : 2); }
+
+// Time of one step of one wave that has the SIMD to itself, in us: about 217
+// (FP64, K = 7) or 180 (FP32, K = 8) vector instructions; measured 0.48 and
+// 0.30 (2048^2, two waves per SIMD).
+template <typename T>
+inline double step_us(int K) { return sizeof(T) == 8 ? 2.2e-3 * (30 + 27 * K) : 1.6e-3 * (44 + 17 * K); }
+
 // A wave's window of consecutive rows of an array: row r of [r0, r0 + n) starts
 // (r - r0) row bytes beyond a base that is formed once.  A row is then one scalar
 // offset for every array of the window, where a buffer resource per row and array
@@ -126,8 +136,8 @@ struct PipeStore {
           s_x(own && i <= nx ? (unsigned)i * (unsigned)sizeof(T) : OOB),
           s_y(own && i < nx ? (unsigned)i * (unsigned)sizeof(T) : OOB), xcol(i >= 1 && i <= nx - 1),
           span(y0_, y1_ - y0_, ld_, (int)sizeof(T)) {}
-    __device__ __forceinline__ void operator()(int j, T ux, T uy) const {
-        const bool in = j >= y0 && j < y1;
+    __device__ __forceinline__ void operator()(int j, T ux, T uy) const { store(j, j >= y0 && j < y1, ux, uy); }
+    __device__ __forceinline__ void store(int j, bool in, T ux, T uy) const {
         const unsigned o = span.at(j);
         buf_store_at(xcol ? ux : T(0), span.of(ox, ld, in && j <= ny - 1), s_x, o);
         buf_store_at(j >= 1 && j <= ny - 1 ? uy : T(0), span.of(oy, ld, in), s_y, o);
@@ -188,6 +198,20 @@ __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c,
     s.ey = ey;
 }
 
+// The cells a wave relaxes: does this lane's column have vx, vy unknowns, and does row r.
+// All others keep their value through every sweep.  SELECT: by a select, where a factor
+// omega / d of 0 would let a non-finite neighbour through to them; the walls and what lies
+// beyond have no neighbour but the unknowns beside them, which that neighbour reaches first.
+struct AllCells {
+    static constexpr bool SELECT = false;
+    bool x, y;
+    int ny;
+    __device__ __forceinline__ AllCells(int nx, int ny_, int i)
+        : x(i >= 1 && i <= nx - 1), y(i >= 0 && i <= nx - 1), ny(ny_) {}
+    __device__ __forceinline__ bool row_x(int r) const { return r >= 0 && r <= ny - 1; }
+    __device__ __forceinline__ bool row_y(int r) const { return r >= 1 && r <= ny - 1; }
+};
+
 // K sweeps of the rows that load(r) delivers for r0 <= r < r1 (at column i of each
 // lane; arrive(u, r, row) may change the row's velocity when it arrives), and,
 // with RES, the residual b - M v of their result.  put(j, ux, uy) receives row
@@ -196,24 +220,28 @@ __device__ __forceinline__ void level(State<T>& s, T nx, T ny, const Coef<T>& c,
 // u: the step within the unrolled trip of R steps (a compile-time value).
 // SQ: square cells (ry = rx = kap = 1 exactly, so B = A and the two strains are
 // the same sum).
-template <typename T, int K, bool SQ, bool RES, int R, typename LD, typename ARR, typename PUT, typename PUTR>
-__device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny, int i, T omega, T idx, T idy,
+template <typename T, int K, bool SQ, bool RES, int R, typename LD, typename CELLS, typename ARR, typename PUT,
+          typename PUTR>
+__device__ __forceinline__ void walk(const LD& L, int r0, int r1, const CELLS& relax, T omega, T idx, T idy,
                                      const ARR& arrive, const PUT& put, const PUTR& putr) {
     constexpr int PFD = ahead<T>(), NL = K + (RES ? 1 : 0);
     static_assert(R >= NL + 2 && R % PFD == 0, "the ring holds NL + 2 rows and the load queue rotates by renaming");
     // many FP64 sweeps on cells that are not square: N(i + 1, j) is taken again
     // by each level rather than kept in the ring, so that 256 registers do
     constexpr bool KEEP_NR = SQ || sizeof(T) == 4 || NL <= 5;
-    const bool xcol = i >= 1 && i <= nx - 1, ycol = i >= 0 && i <= nx - 1;
     const Scale<T> sv = stencil_scale(idx, idy);
     const Scale<T> sc{wave_uniform(sv.a), wave_uniform(sv.n), wave_uniform(sv.kap), wave_uniform(sv.ry),
                       wave_uniform(sv.rx)};
     State<T> st[NL];
     Coef<T> cf[R];
+    bool takes_x[R], takes_y[R];  // SELECT: this lane relaxes the row
 #pragma unroll
     for (int s = 0; s < NL; ++s) st[s] = State<T>{T(0), T(0), T(0), T(0), T(0)};
 #pragma unroll
-    for (int q = 0; q < R; ++q) cf[q] = Coef<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    for (int q = 0; q < R; ++q) {
+        cf[q] = Coef<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+        takes_x[q] = takes_y[q] = false;
+    }
     rows::Row<T> q[PFD];
 #pragma unroll
     for (int p = 0; p < PFD; ++p) q[p] = L.load(r0 + p);
@@ -249,8 +277,15 @@ __device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny
                 const T dy = SQ ? (c1.N + nR) + (c2.A + c1.A)
                                 : diagy_scaled<T>(coef_b(c2.A, sc), coef_b(c1.A, sc), c1.N, nR, sc.rx);
                 const T gx = jac_factor(omega, dx), gy = jac_factor(omega, dy);
-                c1.gx = (xcol && j >= 0 && j <= ny - 1) ? gx : T(0);
-                c1.gy = (ycol && j >= 1 && j <= ny - 1) ? gy : T(0);
+                if constexpr (CELLS::SELECT) {
+                    takes_x[(u + R - 1) % R] = relax.x & relax.row_x(j);
+                    takes_y[(u + R - 1) % R] = relax.y & relax.row_y(j);
+                    c1.gx = gx;
+                    c1.gy = gy;
+                } else {
+                    c1.gx = (relax.x && relax.row_x(j)) ? gx : T(0);
+                    c1.gy = (relax.y && relax.row_y(j)) ? gy : T(0);
+                }
             }
             T ux = w.vx, uy = w.vy;
 #pragma unroll
@@ -262,11 +297,16 @@ __device__ __forceinline__ void walk(const LD& L, int r0, int r1, int nx, int ny
                 level<T, SQ>(st[s - 1], ux, uy, c, nR, Ab, Nt, sc, mx, my, vx, vy);
                 if (RES && s == NL) {
                     const int j = r - NL;
-                    putr(u, j, (xcol && j >= 0 && j <= ny - 1) ? c.bx - mx : T(0),
-                         (ycol && j >= 1 && j <= ny - 1) ? c.by - my : T(0));
+                    putr(u, j, (relax.x && relax.row_x(j)) ? c.bx - mx : T(0),
+                         (relax.y && relax.row_y(j)) ? c.by - my : T(0));
                 } else {
                     ux = jac_step<T>(vx, c.gx, c.bx, mx);
                     uy = jac_step<T>(vy, c.gy, c.by, my);
+                    if constexpr (CELLS::SELECT) {
+                        asm volatile("" : "+v"(ux), "+v"(uy));  // or the compiler makes branches of the selects
+                        ux = takes_x[(u + 2 * R - s) % R] ? ux : vx;
+                        uy = takes_y[(u + 2 * R - s) % R] ? uy : vy;
+                    }
                     if (s == K) put(r - K, ux, uy);
                 }
             }

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 3) void k_fine_down(
     };
     T dx = T(0), dy = T(0);
     walk<T, K, SQ, true, DOWN_RING>(
-        L, r0, r1, nx, ny, i, omega, J.idx, J.idy, [](int, int, rows::Row<T>&) {}, put,
+        L, r0, r1, AllCells(nx, ny, i), omega, J.idx, J.idy, [](int, int, rows::Row<T>&) {}, put,
         [&](int u, int j, T px, T py) {
             rx[u & 3] = px;
             ry[u & 3] = py;
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(64 * WPB, sizeof(T) == 8 ? 2 : 4) void k_fine_up(co
     cload(m0 + 1, c.x2, c.y2);
     cload(m0 + 2, c.x3, c.y3);
     walk<T, K, SQ, false, R>(
-        L, r0, r1, nx, ny, i, omega, J.idx, J.idy,
+        L, r0, r1, AllCells(nx, ny, i), omega, J.idx, J.idy,
         [&](int u, int r, rows::Row<T>& w) {  // row r of w arrives: + P e_c on its unknowns
             const bool rodd = (u + K) & 1;    // y0 is even
             const int m = r >> 1;

@@ -335,6 +335,8 @@ int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f
     // full overlap is exactly kt Jacobi sweeps, wherever the tiles are cut
     if (ctx->ras_kernel == 0 && kt >= 1 && kt <= PIPE_MAX_SWEEPS && halo >= kt - 1 && jacobi_pipe_takes(dt, g))
         return launch_jacobi_pipe(ctx, dt, g, f, omega, kt, vx, vy, ox, oy);
+    if (ctx->ras_kernel == 0 && ras_pipe_takes(ctx, dt, g, tile_x, tile_y, halo, kt))
+        return launch_ras_pipe(ctx, dt, g, f, omega, tile_x, tile_y, halo, kt, sx, sy, vx, vy, ox, oy);
     if (ctx->ras_kernel != 1) {
         bool done = false;
         STK_TRY(launch_ras_stream(ctx, dt, g, f, omega, tile_x, tile_y, halo, kt, sx, sy, vx, vy, ox, oy, &done));
