@@ -6,13 +6,15 @@
 //           N_f = sum f^2/d.
 //
 // Both stream rows like the fused Jacobi kernel: a wave owns a strip of
-// SW = 62 columns and seg_rows rows, its 64 lanes hold the strip and one neighbour
+// SW = 62 columns and walk_length rows, its 64 lanes hold the strip and one neighbour
 // column on each side, each row of every field is loaded once (coalesced
 // buffer loads; walls and outside read as 0), three rows stay in registers
 // and the columns i +- 1 come from neighbouring lanes (DPP).  The energy sums
 // accumulate per lane row by row, then over the wave's lanes (shuffles), one
 // triple per wave; one workgroup adds the triples in a fixed order, so the
-// result is bitwise reproducible.
+// result is bitwise reproducible.  The two quotients by a diagonal share its
+// reciprocal, and the sum of r_p^2 eta_c is divided once: with five FP64
+// divisions a cell the FP32 norm was bound by them (4096^2: 160 us, now 113).
 #include "rowstream.hpp"
 #include "stk_internal.hpp"
 
@@ -20,6 +22,27 @@ namespace stk {
 namespace {
 
 using namespace rows;
+
+// Rows a wave walks: 16.  Short segments, whose waves come and go on a busy chip and
+// leave no long last round, gain more than the two rows around each that are read again
+// cost (they are in L2).  4096^2 FP64, 64-row and 16-row segments: residual 316 and 286 us,
+// energy 186 and 162 us.  Fewer waves than FEW (16 per CU of a 256-CU chip) walk 8, where
+// the walk's latency decides (500 x 700 FP64: residual 11.4 and 8.1 us with the call; at
+// 4096^2 the energy's sums per wave would cost 16 us).  32 and 64 keep a grid's waves, and
+// with them the partial sums of its norms, below MOST (3 doubles each: 8 MiB).
+constexpr int64_t FEW = 4096, MOST = ((int64_t)1 << 20) / 3;
+__host__ __device__ inline int walk_length(int nx, int ny) {
+    const int64_t n = strips(nx);
+    if (n * ((ny + 1 + 15) / 16) < FEW) return 8;
+    int r = 16;
+    while (r < 64 && n * ((ny + 1 + r - 1) / r) > MOST) r <<= 1;
+    return r;
+}
+int64_t waves(int nx, int ny) {
+    const int r = walk_length(nx, ny);
+    return (int64_t)strips(nx) * ((ny + 1 + r - 1) / r);
+}
+unsigned walk_workgroups(int nx, int ny) { return (unsigned)((waves(nx, ny) + WPB - 1) / WPB); }
 
 template <typename T>
 __global__ __launch_bounds__(64 * WPB) void k_residual(int nx, int ny, int64_t ld, T idx, T idy,
@@ -29,7 +52,7 @@ __global__ __launch_bounds__(64 * WPB) void k_residual(int nx, int ny, int64_t l
                                                        const T* __restrict__ fy, T* __restrict__ rx,
                                                        T* __restrict__ ry, T* __restrict__ rp) {
     const int wv = xcd_tile((int)blockIdx.x, (int)gridDim.x) * WPB + wave_in_group();
-    const Place q = place(wv, nx, ny);
+    const Place q = place(wv, nx, ny, walk_length(nx, ny));
     if (q.y0 >= q.y1) return;  // the whole wave
     const int i = q.i;
     const Loader<T> L = make_loader<T>(vx, vy, ec, en, fx, fy, p, ld, nx, ny, i);
@@ -59,7 +82,7 @@ __global__ __launch_bounds__(64 * WPB) void k_residual_to32(int nx, int ny, int6
                                                             float* __restrict__ r32y, float* __restrict__ z32x,
                                                             float* __restrict__ z32y) {
     const int wv = xcd_tile((int)blockIdx.x, (int)gridDim.x) * WPB + wave_in_group();
-    const Place q = place(wv, nx, ny);
+    const Place q = place(wv, nx, ny, walk_length(nx, ny));
     if (q.y0 >= q.y1) return;  // the whole wave
     const int i = q.i;
     const Loader<double> L = make_loader<double>(vx, vy, ec, en, fx, fy, p, ld, nx, ny, i);
@@ -89,7 +112,7 @@ __global__ __launch_bounds__(64 * WPB) void k_energy(int nx, int ny, int64_t ld,
                                                      const T* __restrict__ fx, const T* __restrict__ fy,
                                                      double* __restrict__ part) {
     const int wv = xcd_tile((int)blockIdx.x, (int)gridDim.x) * WPB + wave_in_group();
-    const Place q = place(wv, nx, ny);
+    const Place q = place(wv, nx, ny, walk_length(nx, ny));
     if (q.y0 >= q.y1) return;  // the whole wave (no triple: it is past the last one)
     const Loader<T> L = make_loader<T>(vx, vy, ec, en, fx, fy, p, ld, nx, ny, q.i);
     const int i = q.i;
@@ -98,19 +121,19 @@ __global__ __launch_bounds__(64 * WPB) void k_energy(int nx, int ny, int64_t ld,
     walk_rows<T>(L, q.y0, q.y1, [&](const Row<T>& a, const Row<T>& b, const Row<T>& c, int j) {
         const Res<double> r = residual_row<T, double>(a, b, c, p != nullptr, idx, idy);
         if (xcol && j <= ny - 1) {
-            const double f = b.bx;
-            nv += r.rx * r.rx / r.dx_;
-            nf += f * f / r.dx_;
+            const double f = b.bx, g = jac_factor(1.0, r.dx_);
+            nv += r.rx * r.rx * g;
+            nf += f * f * g;
         }
         if (ycol && j >= 1 && j <= ny - 1) {
-            const double f = b.by;
-            nv += r.ry * r.ry / r.dy_;
-            nf += f * f / r.dy_;
+            const double f = b.by, g = jac_factor(1.0, r.dy_);
+            nv += r.ry * r.ry * g;
+            nf += f * f * g;
         }
-        if (ycol && j <= ny - 1) np += r.rp * r.rp * double(b.ec) / sp;
+        if (ycol && j <= ny - 1) np += r.rp * r.rp * double(b.ec);
     });
     nv = wave_sum(nv);
-    np = wave_sum(np);
+    np = wave_sum(np) / sp;
     nf = wave_sum(nf);
     if ((threadIdx.x & 63) == 0) {
         part[3 * (int64_t)wv + 0] = nv;
@@ -153,7 +176,7 @@ __global__ __launch_bounds__(1024) void k_reduce_triples(const double* __restric
 int launch_residual(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                     const void* eta_c, const void* eta_n, const void* fx, const void* fy, void* rx, void* ry,
                     void* rp) {
-    const dim3 grid((unsigned)workgroups(g->nx, g->ny)), block(64 * WPB);
+    const dim3 grid(walk_workgroups(g->nx, g->ny)), block(64 * WPB);
     if (dt == STK_F64)
         hipLaunchKernelGGL(k_residual<double>, grid, block, 0, ctx->stream, g->nx, g->ny, g->ld, 1.0 / g->dx,
                            1.0 / g->dy, (const double*)vx, (const double*)vy, (const double*)p,
@@ -171,14 +194,14 @@ int launch_residual(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* v
 int launch_residual_to32(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
                          const double* eta_c, const double* eta_n, const double* fx, const double* fy, float* r32x,
                          float* r32y, float* z32x, float* z32y) {
-    hipLaunchKernelGGL(k_residual_to32, dim3((unsigned)workgroups(g->nx, g->ny)), dim3(64 * WPB), 0, ctx->stream,
+    hipLaunchKernelGGL(k_residual_to32, dim3(walk_workgroups(g->nx, g->ny)), dim3(64 * WPB), 0, ctx->stream,
                        g->nx, g->ny, g->ld, 1.0 / g->dx, 1.0 / g->dy, vx, vy, p, eta_c, eta_n, fx, fy, r32x, r32y,
                        z32x, z32y);
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
 
-int64_t energy_partials(const stk_grid* g) { return (int64_t)strips(g->nx) * segments(g->nx, g->ny); }
+int64_t energy_partials(const stk_grid* g) { return waves(g->nx, g->ny); }
 
 int launch_energy(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                   const void* eta_c, const void* eta_n, const void* fx, const void* fy, double* dst) {
@@ -190,21 +213,21 @@ int launch_energy(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx,
 int launch_energy_into(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                        const void* eta_c, const void* eta_n, const void* fx, const void* fy, double* part,
                        double* dst, bool finish) {
-    const int nwg = workgroups(g->nx, g->ny);
-    const int64_t waves = energy_partials(g);  // one triple each (the rest leave at once)
+    const unsigned nwg = walk_workgroups(g->nx, g->ny);
+    const int64_t triples = energy_partials(g);  // one per wave (the rest leave at once)
     const double idx = 1.0 / g->dx, idy = 1.0 / g->dy, sp = 2.0 * idx * idx + 2.0 * idy * idy;
     const dim3 block(64 * WPB);
     if (dt == STK_F64)
-        hipLaunchKernelGGL(k_energy<double>, dim3((unsigned)nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
+        hipLaunchKernelGGL(k_energy<double>, dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
                            idy, sp, (const double*)vx, (const double*)vy, (const double*)p,
                            (const double*)eta_c, (const double*)eta_n, (const double*)fx, (const double*)fy,
                            (double*)part);
     else
-        hipLaunchKernelGGL(k_energy<float>, dim3((unsigned)nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
+        hipLaunchKernelGGL(k_energy<float>, dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
                            idy, sp, (const float*)vx, (const float*)vy, (const float*)p,
                            (const float*)eta_c, (const float*)eta_n, (const float*)fx, (const float*)fy,
                            (double*)part);
-    hipLaunchKernelGGL(k_reduce_triples, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, waves, dst,
+    hipLaunchKernelGGL(k_reduce_triples, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, triples, dst,
                        finish ? 1 : 0);
     STK_HIP(hipGetLastError());
     return STK_OK;

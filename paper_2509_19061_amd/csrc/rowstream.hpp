@@ -97,9 +97,9 @@ struct Place {
     int i, y0, y1;
     bool own;  // lane inside the strip and the grid
 };
-__device__ __forceinline__ Place place(int wv, int nx, int ny) {
+__device__ __forceinline__ Place place(int wv, int nx, int ny, int sr) {
     Place q;
-    const int sr = seg_rows(nx, ny), nstrip = strips(nx), nseg = (ny + 1 + sr - 1) / sr, lane = threadIdx.x & 63;
+    const int nstrip = strips(nx), nseg = (ny + 1 + sr - 1) / sr, lane = threadIdx.x & 63;
     const int strip = wv % nstrip, seg = wv / nstrip;
     q.i = strip * SW - 1 + lane;
     q.y0 = seg * sr;
@@ -107,6 +107,7 @@ __device__ __forceinline__ Place place(int wv, int nx, int ny) {
     q.own = lane >= 1 && lane <= SW && q.i <= nx;
     return q;
 }
+__device__ __forceinline__ Place place(int wv, int nx, int ny) { return place(wv, nx, ny, seg_rows(nx, ny)); }
 // this wave's index within its workgroup (uniform)
 __device__ __forceinline__ int wave_in_group() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
