@@ -83,6 +83,7 @@ static int upload_blocks(PlanT* P, hipStream_t s) {
 
 static size_t level_field_bytes(const MgLevel& l, int t) { return (size_t)(l.ny + 1) * l.ld * (t ? 4 : 8); }
 static int blocks_of(int nx, int ny) { return ((nx + 1 + 63) / 64) * ((ny + 1 + 3) / 4); }
+static int restrict_blocks(int nx, int ny) { return ((nx + 1 + 63) / 64) * ((ny + 1 + 1) / 2); }
 
 // ---- host operator for the coarsest level (same discretisation as the device stencil)
 struct HostGrid {
@@ -495,7 +496,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 ps.push_back(ps.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, true));
                 pf.push_back(pf.back() + blocks_of(m->L[d].nx, m->L[d].ny));
                 pr.push_back(pr.back() + rows::workgroups(m->L[d].nx, m->L[d].ny));
-                pc.push_back(pc.back() + blocks_of(m->L[d + 1].nx, m->L[d + 1].ny));
+                pc.push_back(pc.back() + restrict_blocks(m->L[d + 1].nx, m->L[d + 1].ny));
                 pt.push_back(pt.back() + mg_ras_tiles(m->L[d].nx, m->L[d].ny, o0.coarse_tile));
             } else if (d == nl - 1 && m->relaxed) {  // relaxed, not solved
                 rj.push_back(level_job<T>(m, d, t));

@@ -281,13 +281,13 @@ __global__ __launch_bounds__(NT) void k_mg_residual(const LevelJob<T>* __restric
 // --------------------------------------------------------------- transfers --
 // coarse rhs = R r = P^T r / 4, gathered per coarse unknown from the fine
 // unknowns that prolongate from it; the coarse iterate is set to 0 in the same
-// pass (the coarse problem is solved for the correction from 0).  The fine
-// values of a coarse unknown's 3 x 4 window are loaded first, all at once
-// (rows or columns outside the grid clamped onto it), and the terms whose
-// weights are nonzero are then added in window order, so a thread waits for
-// one round trip instead of one per term.
-// rf(c, fi, fj): the fine residual of component c (as double); (i, j) inside
-// the coarse (cnx+1) x (cny+1) box.
+// pass (the coarse problem is solved for the correction from 0).  Bound by latency on
+// every level it runs on, so a thread takes one unknown of one component (a block: 64
+// columns x 2 rows x 2 components), loads its 3 x 4 window of fine values (rows or
+// columns outside the grid clamped onto it) and its diagonal all at once, and adds the
+// terms in window order: 4.7 us a level for
+// 7.8 (both components in turn, a round trip each and one for the diagonal) from 64^2 to
+// 512^2, and 20 us off a V-cycle of 1024^2 (FP64, 197 us) or 1280 x 960 (FP32, 174 us).
 //
 // J.first: the coarse level's first smoothing sweep is taken here.  That
 // sweep starts from the zero iterate, so A v = 0 and each new value depends
@@ -296,96 +296,42 @@ __global__ __launch_bounds__(NT) void k_mg_residual(const LevelJob<T>* __restric
 // operands as in k_mg_jacobi (which sums the zero terms to +0).  It is written
 // to w, where that sweep writes, and v is not cleared (the next sweep, w -> v,
 // or the odd-count copy overwrites it before anything reads it).
-template <typename T, typename RF>
-__device__ __forceinline__ void restrict_from(const LevelJob<T>& J, int i, int j, const RF& rf, T omega) {
-    const int NX = J.cnx, NY = J.cny, nx = J.nx, ny = J.ny;
-    const int64_t cld = J.cld, k = (int64_t)j * cld + i;
-    if (j < NY) {  // coarse vx(I=i, J=j): fine columns 2i-1..2i+1 (normal), rows 2j-1..2j+2 (tangential)
-        double s = 0.0;
-        if (i >= 1 && i <= NX - 1) {
-            double rv[3][4];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    rv[a][b] = rf(0, 2 * i - 1 + a, min(max(2 * j - 1 + b, 0), ny - 1));
-                }
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int fi = 2 * i - 1 + a;
-                int ci[2];
-                double wi[2];
-                const int nci = w_normal(fi, ci, wi);
-                double wn = 0.0;
-                for (int q = 0; q < nci; ++q) wn += ci[q] == i ? wi[q] : 0.0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int fj = 2 * j - 1 + b;
-                    if (fj < 0 || fj >= ny) continue;
-                    int cj[2];
-                    double wj[2];
-                    const int ncj = w_tangent(fj, NY, cj, wj);
-                    double wt = 0.0;
-                    for (int q = 0; q < ncj; ++q) wt += cj[q] == j ? wj[q] : 0.0;
-                    if (wn != 0.0 && wt != 0.0) s += 0.25 * wn * wt * rv[a][b];
-                }
-            }
-        }
-        const T bc = T(s);
-        J.cbx[k] = bc;
-        if (J.first)
-            J.cwx[k] = (i >= 1 && i <= NX - 1) ? jac_step<T>(T(0), omega / J.cst[k], bc, -T(0)) : T(0);
-        else
-            J.cvx[k] = T(0);
-    }
-    if (i < NX) {  // coarse vy(I=i, J=j): fine rows 2j-1..2j+1 (normal), columns 2i-1..2i+2 (tangential)
-        double s = 0.0;
-        if (j >= 1 && j <= NY - 1) {
-            double rv[3][4];
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    rv[b][a] = rf(1, min(max(2 * i - 1 + a, 0), nx - 1), 2 * j - 1 + b);
-                }
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const int fj = 2 * j - 1 + b;
-                int cj[2];
-                double wj[2];
-                const int ncj = w_normal(fj, cj, wj);
-                double wn = 0.0;
-                for (int q = 0; q < ncj; ++q) wn += cj[q] == j ? wj[q] : 0.0;
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const int fi = 2 * i - 1 + a;
-                    if (fi < 0 || fi >= nx) continue;
-                    int ci[2];
-                    double wi[2];
-                    const int nci = w_tangent(fi, NX, ci, wi);
-                    double wt = 0.0;
-                    for (int q = 0; q < nci; ++q) wt += ci[q] == i ? wi[q] : 0.0;
-                    if (wn != 0.0 && wt != 0.0) s += 0.25 * wn * wt * rv[b][a];
-                }
-            }
-        }
-        const T bc = T(s);
-        J.cby[k] = bc;
-        if (J.first)
-            J.cwy[k] = (j >= 1 && j <= NY - 1) ? jac_step<T>(T(0), omega / J.cst[PL_VY * J.cplane + k], bc, -T(0))
-                                               : T(0);
-        else
-            J.cvy[k] = T(0);
-    }
-}
 template <typename T>
 __global__ __launch_bounds__(NT) void k_mg_restrict(const LevelJob<T>* __restrict__ jobs, const int* __restrict__ pre,
                                                     int n, T omega) {
-    STK_BATCH_INDEX_XCD(jobs, pre, n, COARSE_NX, COARSE_NY)
-    if (i > J.cnx || j > J.cny) return;
-    const int64_t ld = J.ld;
-    restrict_from<T>(
-        J, i, j, [&](int c, int fi, int fj) { return (double)(c == 0 ? J.rx : J.ry)[(int64_t)fj * ld + fi]; }, omega);
+    const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x), inst = find_inst(pre, n, b);
+    const LevelJob<T>& J = jobs[inst];
+    const int NX = J.cnx, NY = J.cny, lb = b - pre[inst], gxb = (NX + 1 + BX - 1) / BX;
+    const int comp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NT / 2));
+    const int i = lb % gxb * BX + (int)threadIdx.x % BX, j = lb / gxb * 2 + (int)threadIdx.x / BX % 2;
+    if (comp == 0 ? i > NX || j >= NY : i >= NX || j > NY) return;
+    // normal: fine faces 2 N - 1 .. 2 N + 1 of the coarse face N with 1/2, 1, 1/2; tangential: fine
+    // rows 2 M - 1 .. 2 M + 2 of the coarse row M < E with 1/4, 3/4, 3/4, 1/4, mirrored at the walls
+    const int N = comp == 0 ? i : j, M = comp == 0 ? j : i, E = comp == 0 ? NY : NX, F = comp == 0 ? NX : NY;
+    const int64_t ld = J.ld, k = (int64_t)j * J.cld + i, sn = comp == 0 ? 1 : ld, st = comp == 0 ? ld : 1;
+    const auto* r = comp == 0 ? J.rx : J.ry;
+    const bool unk = N >= 1 && N <= F - 1;
+    T rv[3][4];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            rv[a][q] = r[min(max(2 * N - 1 + a, 0), 2 * F) * sn + min(max(2 * M - 1 + q, 0), 2 * E - 1) * st];
+    const T d = J.first ? J.cst[comp * PL_VY * J.cplane + k] : T(1);
+    const bool lo = M > 0, hi = M < E - 1;
+    const double wt[4] = {0.25, lo ? 0.75 : 1.0, hi ? 0.75 : 1.0, 0.25};
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double t = s + (a == 1 ? 0.25 : 0.125) * wt[q] * (double)rv[a][q];
+            s = (q == 0 && !lo) || (q == 3 && !hi) ? s : t;
+        }
+    const T bc = unk ? T(s) : T(0);
+    (comp == 0 ? J.cbx : J.cby)[k] = bc;
+    if (J.first) (comp == 0 ? J.cwx : J.cwy)[k] = unk ? jac_step<T>(T(0), omega / d, bc, -T(0)) : T(0);
+    else (comp == 0 ? J.cvx : J.cvy)[k] = T(0);
 }
 
 // v += P e_c on the fine unknowns.
@@ -458,11 +404,11 @@ __global__ __launch_bounds__(NT) void k_mg_jacobi_prolonged(const LevelJob<T>* _
 // instance (grid y); its CW x CR threads each sum a contiguous chunk of the
 // columns for one row, and the chunk sums are added in chunk order.  The
 // inverse is stored column by column, so the rows of a workgroup are one
-// 128-byte line per column.  It is bound by the latency of the chunk's loads:
-// CL columns are loaded at once, and the rows are spread over many CUs (1984
-// unknowns of a 32^2 level, 31 MB: 64 rows per workgroup with eight loads in
-// flight used 31 CUs and took 29 us, 16 rows with 32 in flight 11 us).
-constexpr int CW = 16, CR = 16, CL = 32;
+// 128-byte line per column.  It is bound by round trips: the CL columns of a step and
+// the CG right-hand side entries of a thread are loaded at once, through the index map in
+// two trips and not two per entry (1984 unknowns of a 32^2 level 17.6 -> 15.7 us,
+// 4000 unknowns 41 -> 34 us).  64 columns a step or 8 rows a workgroup are no faster.
+constexpr int CW = 16, CR = 16, CL = 32, CG = 16;
 template <typename T>
 __global__ __launch_bounds__(CW* CR) void k_mg_coarse(const CoarseJob<T>* __restrict__ jobs) {
     extern __shared__ double csh[];  // CW x CR chunk sums, then the right-hand side
@@ -479,28 +425,39 @@ __global__ __launch_bounds__(CW* CR) void k_mg_coarse(const CoarseJob<T>* __rest
 #pragma unroll
         for (int u = 0; u < CL; ++u) a[u] = col[(int64_t)min(c + u, nu - 1) * nu];
     };
-    fetch(c0);  // in flight while the right-hand side is gathered
-    for (int r = threadIdx.x; r < nu; r += CW * CR) {
-        const int code = J.map[r];  // (component << 30) | (j * ld + i) offset
-        const int off = code & 0x3fffffff;
-        rhs[r] = -(double)((code >> 30) ? J.by[off] : J.bx[off]);
+    fetch(c0);                 // in flight while the right-hand side is gathered
+    const int out = J.map[q];  // (component << 30) | (j * ld + i) offset
+    for (int r0 = threadIdx.x; r0 < nu; r0 += CW * CR * CG) {
+        int code[CG];
+        T b[CG];
+#pragma unroll
+        for (int u = 0; u < CG; ++u) code[u] = J.map[min(r0 + u * CW * CR, nu - 1)];
+#pragma unroll
+        for (int u = 0; u < CG; ++u) b[u] = ((code[u] >> 30) ? J.by : J.bx)[code[u] & 0x3fffffff];
+#pragma unroll
+        for (int u = 0; u < CG; ++u)
+            if (r0 + u * CW * CR < nu) rhs[r0 + u * CW * CR] = -(double)b[u];
     }
     __syncthreads();
     double s = 0.0;
     for (int c = c0; c < c1; c += CL) {
         if (c > c0) fetch(c);
+        double h[CL];
 #pragma unroll
-        for (int u = 0; u < CL; ++u)
-            if (c + u < c1) s += a[u] * rhs[c + u];
+        for (int u = 0; u < CL; ++u) h[u] = rhs[min(c + u, nu - 1)];
+#pragma unroll
+        for (int u = 0; u < CL; ++u) {
+            const double t = s + a[u] * h[u];
+            s = c + u < c1 ? t : s;
+        }
     }
     part[w * CR + row] = s;
     __syncthreads();
     if (w == 0 && (int)blockIdx.x * CR + row < nu) {
         double t = part[row];
         for (int u = 1; u < CW; ++u) t += part[u * CR + row];
-        const int code = J.map[q];
-        const int off = code & 0x3fffffff;
-        if (code >> 30) J.vy[off] = T(t); else J.vx[off] = T(t);
+        const int off = out & 0x3fffffff;
+        if (out >> 30) J.vy[off] = T(t); else J.vx[off] = T(t);
     }
 }
 
