@@ -80,6 +80,10 @@ __global__ __launch_bounds__(UX* UY) void k_pressure_update(int nx, int ny, int6
     if (threadIdx.x == 0 && threadIdx.y == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
+// The sum down a column is a serial chain, so a wave is bound by the round trips of its
+// loads: LB rows are in flight while the LB before them are added and stored.  With a
+// load per step 2048^2 took 536 us with the mean's removal, now 95; 1024^2 143, now 49.
+constexpr int LB = 32;
 __global__ __launch_bounds__(UX) void k_litho(int nx, int ny, int64_t ld, double dy, const double* __restrict__ fy,
                                               double* __restrict__ p, double* __restrict__ part) {
     const int i = (int)blockIdx.x * UX + (int)threadIdx.x;
@@ -87,10 +91,26 @@ __global__ __launch_bounds__(UX) void k_litho(int nx, int ny, int64_t ld, double
     if (i < nx) {
         double q = 0.0;  // top row; the constant is removed afterwards
         p[(int64_t)(ny - 1) * ld + i] = q;
-        for (int j = ny - 1; j >= 1; --j) {
-            q = q + fy[(int64_t)j * ld + i] * dy;
-            p[(int64_t)(j - 1) * ld + i] = q;
-            s += q;
+        double f[2][LB];
+        auto load = [&](double (&d)[LB], int j) {  // rows j, j - 1, ... (none below 1)
+#pragma unroll
+            for (int u = 0; u < LB; ++u) d[u] = fy[(int64_t)max(j - u, 1) * ld + i];
+        };
+        auto add = [&](const double (&d)[LB], int j) {
+#pragma unroll
+            for (int u = 0; u < LB; ++u) {
+                if (j - u < 1) return;
+                q = q + d[u] * dy;
+                p[(int64_t)(j - u - 1) * ld + i] = q;
+                s += q;
+            }
+        };
+        load(f[0], ny - 1);
+        for (int j = ny - 1; j >= 1; j -= 2 * LB) {
+            load(f[1], j - LB);
+            add(f[0], j);
+            load(f[0], j - 2 * LB);
+            add(f[1], j - LB);
         }
     }
     s = wave_sum64(s);
