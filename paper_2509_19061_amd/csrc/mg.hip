@@ -464,6 +464,9 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     P->relax_t.assign(maxl, Batch{});
     P->fine_p.assign(maxl, Batch{});
     P->small_p.assign(maxl, 0);
+    P->walk_p.assign(maxl, Batch{});
+    P->walk_shapes.assign(maxl, nullptr);
+    P->walk_up.assign(maxl, 0);
     const stk_mg_opts& o0 = mgs[0]->o;
     const bool cras = o0.coarse_smoother == 1;
     P->pair = takes_pairs(mgs, n, t);
@@ -537,6 +540,23 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 STK_TRY(upload(P, pp, &dpp));
                 P->fine_p[d] = Batch{dj, (const int*)dpp, (int)jobs.size(), pp.back()};
                 P->small_p[d] = small;
+                // The walk from 6 (down) and 16 (up) of the smaller regions per CU on: a 512^2
+                // level has 1849, 1024^2 7310, where both sides are measured (mg_pair.hip)
+                if (ps.back() >= 6 * ctx->num_cu) {
+                    std::vector<int> wx, wy, pw;
+                    for (const LevelJob<T>& J : jobs) {
+                        wx.push_back(J.nx);
+                        wy.push_back(J.ny);
+                    }
+                    std::vector<FineShape> shapes;
+                    mg_pair_walk_shape(ctx, (int)sizeof(T), wx.data(), wy.data(), (int)wx.size(), &shapes, &pw);
+                    const void *dsh = nullptr, *dpw = nullptr;
+                    STK_TRY(upload(P, shapes, &dsh));
+                    STK_TRY(upload(P, pw, &dpw));
+                    P->walk_p[d] = Batch{dj, (const int*)dpw, (int)jobs.size(), pw.back()};
+                    P->walk_shapes[d] = static_cast<const FineShape*>(dsh);
+                    P->walk_up[d] = ps.back() >= 16 * ctx->num_cu;
+                }
             }
             if (d == 0) {  // the finest level is matrix-free: row-streaming smoothing and residual
                 const void* dpr = nullptr;
@@ -718,6 +738,14 @@ static int smooth_stage(stk_ctx* ctx, const Batch& F, const stk_mg_opts& o, int 
     return STK_OK;
 }
 
+// Both sweeps of a coarse level's stage in one pass.
+template <typename T>
+static int pair_stage(stk_ctx* ctx, const PlanT& P, int d, double omega, bool up) {
+    if (P.walk_p[d].n && (!up || P.walk_up[d]))
+        return mg_pair_walk<T>(ctx, P.walk_p[d], P.walk_shapes[d], omega, up);
+    return mg_pair<T>(ctx, P.fine_p[d], omega, up, P.small_p[d]);
+}
+
 // The restriction into a coarse level took its first sweep (see first_sweep
 // in build_plan): the pre-smoothing of a level d >= 1 smoothed by Jacobi with
 // nu1 >= 1, or the relaxation of a relaxed last level.
@@ -799,7 +827,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu1, false, &done));
             STK_TRY(mg_residual<T>(ctx, P.fine0w));
         } else if (d >= 1 && P.pair) {
-            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, false, P.small_p[d]));
+            STK_TRY(pair_stage<T>(ctx, P, d, o.omega, false));
         } else {
             STK_TRY(d == 0 ? smooth_stage<T>(ctx, F, o, nu1)
                            : coarse_stage<T>(ctx, F, P.fine_t[d], o, nu1, first_sweep_done(o, nu1)));
@@ -825,7 +853,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
             bool done = false;
             STK_TRY(fine_ras_stage<T>(ctx, P, o, nu2, true, &done));
         } else if (d >= 1 && P.pair) {
-            STK_TRY(mg_pair<T>(ctx, P.fine_p[d], o.omega, true, P.small_p[d]));
+            STK_TRY(pair_stage<T>(ctx, P, d, o.omega, true));
         } else if (d >= 1 && o.coarse_smoother != 1 && nu2 >= 1) {
             // the prolongation and the first post-sweep in one pass (v + P e -> w)
             STK_TRY(mg_jacobi_prolonged<T>(ctx, F, o.omega));

@@ -53,6 +53,9 @@ struct PlanT {
     bool pair = false;
     std::vector<Batch> fine_p;
     std::vector<char> small_p;  // its smaller regions
+    std::vector<Batch> walk_p;  // large levels: by a walk of these shapes, down, or both ways
+    std::vector<const FineShape*> walk_shapes;
+    std::vector<char> walk_up;
     // default smoothing: the finest level in one pass each way (mg_fine.hip), with
     // the launch shapes of the instances; square: all have square cells
     bool fused = false, square = false;

@@ -132,6 +132,12 @@ void mg_fine_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, con
 template <typename T>
 int mg_fine(stk_ctx* ctx, const Batch& b, const FineShape* shapes, int K, bool square, double omega, bool up,
             const FineIo& io);
+// The two sweeps of mg_pair by a walk (mg_pair.hip); b's prefix counts the workgroups of
+// mg_pair_walk_shape.
+void mg_pair_walk_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, std::vector<FineShape>* shapes,
+                        std::vector<int>* pre);
+template <typename T>
+int mg_pair_walk(stk_ctx* ctx, const Batch& b, const FineShape* shapes, double omega, bool up);
 template <typename T> int mg_coarse(stk_ctx* ctx, const void* jobs, int n, int max_unknowns);
 
 // Galerkin setup of one coarse level from the next finer one (galerkin.hip).

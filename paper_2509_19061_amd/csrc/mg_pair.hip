@@ -25,6 +25,8 @@
 // The row sums run in the slot order of stencil_av_l on the same operands, and
 // the updates are the shared ones, so the values are the bits of the separate
 // kernels.
+#include <algorithm>
+
 #include "coarse_stencil.hpp"
 #include "mg_internal.hpp"
 #include "mg_transfer.hpp"
@@ -140,6 +142,129 @@ __global__ __launch_bounds__(2 * RX * RY, 4) void k_mg_pair(const LevelJob<T>* _
     }
 }
 
+// The same two applications by a walk up a strip of 64 positions, 60 of them owned, for
+// levels that fill the chip several times over.  The workgroup's waves hold RG rows of each
+// component at a time.  A step takes the first application of RG rows and the second of the
+// RG rows below, whose coefficients have stayed in registers since their own step, and loads
+// those of the RG rows above in their place.  Both windows are rings of RING rows in LDS, one
+// barrier a step.  A region computes half as much again as it owns, the walk a tenth; and of
+// the regions only one fits on a CU, which then either loads or computes, of these workgroups
+// two (FP64: two sets of coefficients, 208 to 240 VGPRs; with a third, to load a step ahead,
+// they spill).  Level of 2048^2, down and up: FP64 497 and 502 us by regions, 375 and 405 by
+// the walk; 1024^2 136, 135 and 103, 113; 512^2 38, 32 and 33, 33; FP32 1024^2 81, 79 and
+// 54, 77, 512^2 25, 21 and 22, 32.  Going up, the walk waits for its prolongation, so it
+// takes over later.
+constexpr int RG = 2, WALK_OWN = 64 - 2 * RIM, WALK_W = 64 + 2 * RIM, RING = 16;
+
+template <typename T, int A>
+__device__ __forceinline__ T ring_sum(const T (&cf)[NCOEF], const T* win, const int (&rb)[5], int x) {
+    T s = T(0);
+#pragma unroll
+    for (int q = 0; q < NCOEF; ++q) {
+        const T v = win[slot_comp(A, q) * RING * WALK_W + rb[slot_dy(A, q) + 2] + x + slot_dx(A, q)];
+        s += cf[q] * v;
+    }
+    return s;
+}
+
+template <typename T, bool UP>
+__global__ __launch_bounds__(128 * RG, sizeof(T) == 4 ? 3 : 2) void k_mg_pair_walk(const LevelJob<T>* __restrict__ jobs,
+                                                             const int* __restrict__ pre,
+                                                             const FineShape* __restrict__ shapes, int n, T omega) {
+    static_assert(2 * RG + 8 <= RING, "the rows in use at a time");
+    __shared__ T win[2 * RING * WALK_W], mid[2 * RING * WALK_W];
+    const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int inst = find_pair_inst(pre, n, b);
+    const LevelJob<T>& J = jobs[inst];
+    const FineShape sh = shapes[inst];
+    const int nx = J.nx, ny = J.ny, lb = b - pre[inst], lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), comp = wave / RG, y = wave % RG;
+    const int x0 = lb % sh.nstrip * WALK_OWN - RIM, i = x0 + lane, x = lane + RIM;  // x: window column of i
+    const int y0 = lb / sh.nstrip * sh.seg, y1 = min(y0 + sh.seg, ny + 1), G = (y1 - y0 + 2 * RIM + RG - 1) / RG;
+    const int64_t ld = J.ld;
+    const bool col = comp == 0 ? i >= 1 && i <= nx - 1 : i >= 0 && i <= nx - 1;
+    const bool own = lane >= RIM && lane < 64 - RIM && (comp == 0 ? i <= nx : i < nx);
+    auto unknown = [&](int j) { return col && (comp == 0 ? j >= 0 && j <= ny - 1 : j >= 1 && j <= ny - 1); };
+    auto bases = [&](int j, int (&rb)[5]) {
+#pragma unroll
+        for (int d = 0; d < 5; ++d) rb[d] = ((j + d - 2) & (RING - 1)) * WALK_W;
+    };
+    // the staged iterate of this wave's component at grid column ii, row jj
+    auto staged = [&](int ii, int jj) {
+        T val = T(0);
+        const int64_t kk = (int64_t)jj * ld + ii;
+        if (comp == 0 ? is_vx_unknown(nx, ny, ii, jj) : is_vy_unknown(nx, ny, ii, jj)) {
+            if constexpr (UP) val = comp == 0 ? J.wx[kk] + T(prolong_sx(J, ii, jj)) : J.wy[kk] + T(prolong_sy(J, ii, jj));
+            else val = (comp == 0 ? J.vx : J.vy)[kk];
+        }
+        return val;
+    };
+    auto put_row = [&](int jj, T a, T c) {
+        T* p = win + (comp * RING + (jj & (RING - 1))) * WALK_W;
+        p[lane] = a;
+        if (lane < 2 * RIM) p[64 + lane] = c;
+    };
+    T cf[2][NCOEF], rhs[2], g[2];
+    auto coefs = [&](T (&c)[NCOEF], T& r, int j) {
+        const bool in = unknown(j);
+        if (comp == 0) load_row<T, 0>(J, i, j, in, c);
+        else load_row<T, 1>(J, i, j, in, c);
+        r = buf_load<T>(buf_rsrc((const T*)(comp == 0 ? J.bx : J.by), (size_t)((ny + 1) * ld) * sizeof(T)),
+                        in ? (unsigned)(((int64_t)j * ld + i) * (int)sizeof(T)) : OOB);
+    };
+    const int j0 = y0 - RIM + y;
+    for (int q = 0; q < RG + 2 * RIM; q += RG)
+        if (y + q < RG + 2 * RIM) {
+            const int jj = y0 - 2 * RIM + y + q;
+            put_row(jj, staged(x0 - RIM + lane, jj), lane < 2 * RIM ? staged(x0 - RIM + 64 + lane, jj) : T(0));
+        }
+    coefs(cf[0], rhs[0], j0);
+    __syncthreads();
+    for (int s0 = 0; s0 <= G; s0 += 2) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int s = s0 + q, j = j0 + s * RG;
+            if (s > G) break;
+            if (s < G) {
+                const int jn = j + RG + RIM;
+                const T na = staged(x0 - RIM + lane, jn);
+                const T nc = lane < 2 * RIM ? staged(x0 - RIM + 64 + lane, jn) : T(0);
+                int rb[5];
+                bases(j, rb);
+                T av;
+                if (comp == 0) {
+                    av = ring_sum<T, 0>(cf[q], win, rb, x);
+                    g[q] = omega / cf[q][DIAG[0]];
+                } else {
+                    av = ring_sum<T, 1>(cf[q], win, rb, x);
+                    g[q] = omega / cf[q][DIAG[1]];
+                }
+                const T v = win[comp * RING * WALK_W + rb[2] + x];
+                const T u = unknown(j) ? jac_step<T>(v, g[q], rhs[q], -av) : T(0);
+                mid[comp * RING * WALK_W + rb[2] + x] = u;
+                if (!UP && own && j >= y0 && j < y1 && (comp == 1 || j < ny))
+                    (comp == 0 ? J.wx : J.wy)[(int64_t)j * ld + i] = u;
+                put_row(jn, na, nc);
+            }
+            __syncthreads();
+            const int jr = j - RG, p = 1 - q;  // the rows below
+            if (own && jr >= y0 && jr < y1 && (comp == 1 || jr < ny)) {
+                int rb[5];
+                bases(jr, rb);
+                const T av = comp == 0 ? ring_sum<T, 0>(cf[p], mid, rb, x) : ring_sum<T, 1>(cf[p], mid, rb, x);
+                const int64_t k = (int64_t)jr * ld + i;
+                if constexpr (UP) {
+                    const T o = jac_step<T>(mid[comp * RING * WALK_W + rb[2] + x], g[p], rhs[p], -av);
+                    (comp == 0 ? J.vx : J.vy)[k] = unknown(jr) ? o : T(0);
+                } else {
+                    (comp == 0 ? J.rx : J.ry)[k] = unknown(jr) ? rhs[p] + av : T(0);
+                }
+            }
+            if (s + 1 < G) coefs(cf[p], rhs[p], j + RG);
+        }
+    }
+}
+
 }  // namespace
 
 int mg_pair_tiles(int nx, int ny, bool small) {
@@ -163,6 +288,48 @@ int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, bool small) {
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
+void mg_pair_walk_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, std::vector<FineShape>* shapes,
+                        std::vector<int>* pre) {
+    const int64_t slots = (int64_t)std::max(ctx->num_cu, 1) * (es == 8 ? 4 : 8) / RG;
+    int best = RG * 4;
+    double cost = 1e300;
+    int tall = 0;
+    for (int q = 0; q < n; ++q) tall = std::max(tall, ny[q] + 1);
+    for (int G = 2 * RIM / RG + 2; RG * (G - 1) - 2 * RIM < tall; ++G) {
+        const int H = RG * G - 2 * RIM;
+        int64_t wg = 0;
+        for (int q = 0; q < n; ++q) wg += (int64_t)((nx[q] + WALK_OWN) / WALK_OWN) * ((ny[q] + H) / H);
+        const double c = (double)((wg + slots - 1) / slots) * (G + 2);
+        if (c < cost) {
+            cost = c;
+            best = H;
+        }
+    }
+    shapes->clear();
+    pre->assign(1, 0);
+    for (int q = 0; q < n; ++q) {
+        shapes->push_back(FineShape{(nx[q] + WALK_OWN) / WALK_OWN, (ny[q] + best) / best, best});
+        pre->push_back(pre->back() + shapes->back().nstrip * shapes->back().nseg);
+    }
+}
+
+template <typename T>
+int mg_pair_walk(stk_ctx* ctx, const Batch& b, const FineShape* shapes, double omega, bool up) {
+    if (!b.n) return STK_OK;
+    const auto* jobs = static_cast<const LevelJob<T>*>(b.jobs);
+    const dim3 grid((unsigned)b.blocks), block(128 * RG);
+    if (up)
+        hipLaunchKernelGGL((k_mg_pair_walk<T, true>), grid, block, 0, ctx->stream, jobs, b.pre, shapes, b.n,
+                           T(omega));
+    else
+        hipLaunchKernelGGL((k_mg_pair_walk<T, false>), grid, block, 0, ctx->stream, jobs, b.pre, shapes, b.n,
+                           T(omega));
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+template int mg_pair_walk<double>(stk_ctx*, const Batch&, const FineShape*, double, bool);
+template int mg_pair_walk<float>(stk_ctx*, const Batch&, const FineShape*, double, bool);
+
 template int mg_pair<double>(stk_ctx*, const Batch&, double, bool, bool);
 template int mg_pair<float>(stk_ctx*, const Batch&, double, bool, bool);
 
