@@ -173,11 +173,9 @@ enum VecOp {
 // budget runs out), PH_TRUE takes a recomputed true residual (stop below the
 // threshold only)
 enum { PH_NF = 0, PH_NV, PH_INIT, PH_ALPHA, PH_BETA, PH_TRUE };
-// Slot dtype T for the slots touched (R, Z, P, Q, X); partial sums land in
-// `part` (2 per block), summed per instance by fcg_reduce.  z32: the batch's Z
-// slot holds FP32 vectors (the FP32 V-cycle's output, read in place by the
-// FP64 Krylov operations).
-template <typename T>
+// FP64 slots; partial sums land in `part` (2 per block), summed per instance by
+// fcg_reduce.  z32: the batch's Z slot holds FP32 vectors (the FP32 V-cycle's
+// output, read in place).
 int vec_op(stk_ctx* ctx, const Batch& b, int op, const FcgState* st, double* part, bool z32 = false);
 // R = B - M X in FP64, block partials of sum R^2 / d in `part`
 int vec_residual64_st(stk_ctx* ctx, const Batch& b, const FcgState* st, double* part);
