@@ -13,7 +13,7 @@
 // What bounds it: vector issue, as for Jacobi, with the stretched cells on top; from
 // about 4096^2 on, the eight planes.  One pass of k = 4 sweeps on 64 x 64 tiles without
 // overlap, before (an LDS pipeline with one wave per level) and now: 1501 x 1100 FP32
-// 32.1 -> 19.9 us, FP64 41.5 -> 30.9; 4096^2 FP32 186 -> 127, FP64 268 -> 238 us.  On
+// 32.1 -> 19.9 us, FP64 41.5 -> 27.0; 4096^2 FP32 186 -> 127, FP64 268 -> 238 us.  On
 // 16 x 16 tiles at 4096^2 FP32 562 -> 137 us; 128 x 128 (one tile per workgroup's LDS)
 // 2.57 ms -> 125 us.
 #include <algorithm>
@@ -120,7 +120,9 @@ Stretch stretch(int T, int h, int s) {
     return {P, T, h, s - T - h - 1, (unsigned)((((uint64_t)1 << 32) + P - 1) / P)};
 }
 
-// Strips and segments, as pipe_shape (jacobi_pipe.hip).
+// Strips and segments, as pipe_shape (jacobi_pipe.hip); a wave alone on its SIMD also waits
+// for the scalar arithmetic of the stretched rows (FP64 k = 4, 64 x 64 tiles, one and two
+// waves per SIMD: 1501 x 1100 30.4 and 27.0 us, 2048^2 57 and 52 us).
 template <typename T>
 RasCut ras_cut(const stk_ctx* ctx, const stk_grid* g, int Tx, int Ty, int h, int K, int sx, int sy) {
     RasCut c{stretch(Tx, h, sx), stretch(Ty, h, sy), 0, 0, 0, 0, 0, 0};
@@ -136,7 +138,7 @@ RasCut ras_cut(const stk_ctx* ctx, const stk_grid* g, int Tx, int Ty, int h, int
         const int64_t segs = std::max<int64_t>((ey + most - 1) / most, std::min<int64_t>(w * cu4 / ns, ey));
         const int steps = ((int)((ey + segs - 1) / segs) + 2 * K + U - 1) / U * U, H = steps - 2 * K;
         const int64_t nseg = (ey + H - 1) / H, per_simd = (ns * nseg + cu4 - 1) / cu4;
-        const double t = (steps + 4) * std::max(sizeof(T) == 8 ? 1.1 : 1.35, (double)per_simd);
+        const double t = (steps + 4) * std::max(1.35, (double)per_simd);
         if (t < cost) {
             cost = t;
             c.nseg = (int)nseg;

@@ -174,7 +174,7 @@ Shape rb_shape(const stk_ctx* ctx, int nx, int ny, int64_t ld, int K) {
         const int64_t segs = std::max<int64_t>((ny + most) / most, std::min<int64_t>(w * cu4 / ns, ny + 1));
         const int steps = ((int)((ny + 1 + segs - 1) / segs) + over + U - 1) / U * U, H = steps - over;
         const int64_t nseg = (ny + 1 + H - 1) / H, per_simd = (ns * nseg + cu4 - 1) / cu4;
-        const double c = (steps + 4) * std::max(sizeof(T) == 8 ? 1.1 : 1.35, (double)per_simd);
+        const double c = (steps + 4) * std::max(sizeof(T) == 8 ? 1.2 : 1.35, (double)per_simd);
         if (c < cost) {
             cost = c;
             best.nseg = (int)nseg;
