@@ -20,7 +20,8 @@ struct stk_ctx {
     enum { S_VX = 0, S_VY, S_VX2, S_VY2, S_BX, S_BY, S_PART, S_RED, S_NSLOT };
     void* slot[S_NSLOT] = {};
     size_t slot_bytes[S_NSLOT] = {};
-    double* host_red = nullptr;  // pinned host landing buffer for reductions
+    double* host_red = nullptr;      // pinned host landing buffer for reductions
+    double* host_red_dev = nullptr;  // its device-side address
     // pinned host landing buffer for the states of a solve's instances (solve.hip), its
     // device-side address and its capacity in instances
     void *pin = nullptr, *pin_dev = nullptr;
