@@ -464,6 +464,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     P->relax_t.assign(maxl, Batch{});
     P->fine_p.assign(maxl, Batch{});
     P->small_p.assign(maxl, 0);
+    P->rest_p.assign(maxl, Batch{});
     P->walk_p.assign(maxl, Batch{});
     P->walk_shapes.assign(maxl, nullptr);
     P->walk_up.assign(maxl, 0);
@@ -482,7 +483,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
     };
     for (int d = 0; d < maxl; ++d) {
         std::vector<LevelJob<T>> jobs, rj;
-        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, pp{0}, ps{0}, rpf{0}, rpt{0};
+        std::vector<int> pf{0}, pc{0}, pr{0}, pt{0}, pp{0}, ps{0}, pe{0}, rpf{0}, rpt{0};
         std::vector<CoarseJob<T>> cj;
         for (int q = 0; q < n; ++q) {
             const stk_mg* m = mgs[q];
@@ -495,8 +496,9 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     J.cwx = J.cvx;
                     J.cwy = J.cvy;
                 }
-                pp.push_back(pp.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, false));
-                ps.push_back(ps.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, true));
+                pp.push_back(pp.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, PAIR_WIDE));
+                ps.push_back(ps.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, PAIR_SMALL));
+                pe.push_back(pe.back() + mg_pair_tiles(m->L[d].nx, m->L[d].ny, PAIR_REST));
                 pf.push_back(pf.back() + blocks_of(m->L[d].nx, m->L[d].ny));
                 pr.push_back(pr.back() + rows::workgroups(m->L[d].nx, m->L[d].ny));
                 pc.push_back(pc.back() + restrict_blocks(m->L[d + 1].nx, m->L[d + 1].ny));
@@ -540,6 +542,11 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                 STK_TRY(upload(P, pp, &dpp));
                 P->fine_p[d] = Batch{dj, (const int*)dpp, (int)jobs.size(), pp.back()};
                 P->small_p[d] = small;
+                if (pe.back() <= ctx->num_cu) {
+                    const void* dpe = nullptr;
+                    STK_TRY(upload(P, pe, &dpe));
+                    P->rest_p[d] = Batch{dj, (const int*)dpe, (int)jobs.size(), pe.back()};
+                }
                 // The walk from 6 (down) and 16 (up) of the smaller regions per CU on: a 512^2
                 // level has 1849, 1024^2 7310, where both sides are measured (mg_pair.hip)
                 if (ps.back() >= 6 * ctx->num_cu) {
@@ -743,7 +750,8 @@ template <typename T>
 static int pair_stage(stk_ctx* ctx, const PlanT& P, int d, double omega, bool up) {
     if (P.walk_p[d].n && (!up || P.walk_up[d]))
         return mg_pair_walk<T>(ctx, P.walk_p[d], P.walk_shapes[d], omega, up);
-    return mg_pair<T>(ctx, P.fine_p[d], omega, up, P.small_p[d]);
+    if (!up && P.rest_p[d].n) return mg_pair<T>(ctx, P.rest_p[d], omega, false, PAIR_REST);
+    return mg_pair<T>(ctx, P.fine_p[d], omega, up, P.small_p[d] ? PAIR_SMALL : PAIR_WIDE);
 }
 
 // The restriction into a coarse level took its first sweep (see first_sweep
@@ -833,7 +841,7 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
                            : coarse_stage<T>(ctx, F, P.fine_t[d], o, nu1, first_sweep_done(o, nu1)));
             STK_TRY(mg_residual<T>(ctx, F));
         }
-        if (!fused) STK_TRY(mg_restrict<T>(ctx, P.crs[d], o.omega));
+        if (!fused && !P.rest_p[d].n) STK_TRY(mg_restrict<T>(ctx, P.crs[d], o.omega));
         if (d + 1 < (int)P.cjobs.size()) {
             STK_TRY(mg_coarse<T>(ctx, P.cjobs[d + 1], P.ncj[d + 1], P.maxcn));
             if (P.relax[d + 1].n) {  // truncated hierarchies: the last level relaxed from 0

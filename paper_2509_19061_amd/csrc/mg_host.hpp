@@ -53,6 +53,7 @@ struct PlanT {
     bool pair = false;
     std::vector<Batch> fine_p;
     std::vector<char> small_p;  // its smaller regions
+    std::vector<Batch> rest_p;  // small levels: down by regions that also restrict
     std::vector<Batch> walk_p;  // large levels: by a walk of these shapes, down, or both ways
     std::vector<const FineShape*> walk_shapes;
     std::vector<char> walk_up;

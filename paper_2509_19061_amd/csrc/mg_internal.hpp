@@ -108,9 +108,11 @@ template <typename T> int mg_jacobi_prolonged(stk_ctx* ctx, const Batch& b, doub
 // Stored-stencil levels smoothed by two sweeps, one pass each way (mg_pair.hip;
 // b's prefix counts mg_pair_tiles per instance): down w <- the second
 // pre-sweep of v, r <- its residual; up v <- two sweeps of w + P e_c.
-// small: the smaller regions, for batches of at most about one per CU.
-template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, bool small);
-int mg_pair_tiles(int nx, int ny, bool small);
+// kind: the regions; PAIR_SMALL for batches of at most about one per CU, PAIR_REST (down) such
+// that also restrict: mg_restrict's results in place of r.
+enum PairKind { PAIR_WIDE, PAIR_SMALL, PAIR_REST };
+template <typename T> int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, PairKind kind);
+int mg_pair_tiles(int nx, int ny, PairKind kind);
 // Finest level in one pass each way (mg_fine.hip), K = 1 .. MG_FINE_MAX sweeps.
 // down: w <- K sweeps of v; the residual of w restricted to the coarse
 // right-hand side, and the coarse iterate 0 or (jobs with `first`) its first

@@ -305,12 +305,11 @@ __global__ __launch_bounds__(NT) void k_mg_restrict(const LevelJob<T>* __restric
     const int comp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NT / 2));
     const int i = lb % gxb * BX + (int)threadIdx.x % BX, j = lb / gxb * 2 + (int)threadIdx.x / BX % 2;
     if (comp == 0 ? i > NX || j >= NY : i >= NX || j > NY) return;
-    // normal: fine faces 2 N - 1 .. 2 N + 1 of the coarse face N with 1/2, 1, 1/2; tangential: fine
-    // rows 2 M - 1 .. 2 M + 2 of the coarse row M < E with 1/4, 3/4, 3/4, 1/4, mirrored at the walls
+    // N, F: the face and the box's last one along the normal; M, E: the row and the rows along
+    // the tangent (restrict_sum)
     const int N = comp == 0 ? i : j, M = comp == 0 ? j : i, E = comp == 0 ? NY : NX, F = comp == 0 ? NX : NY;
     const int64_t ld = J.ld, k = (int64_t)j * J.cld + i, sn = comp == 0 ? 1 : ld, st = comp == 0 ? ld : 1;
     const auto* r = comp == 0 ? J.rx : J.ry;
-    const bool unk = N >= 1 && N <= F - 1;
     T rv[3][4];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -318,20 +317,7 @@ __global__ __launch_bounds__(NT) void k_mg_restrict(const LevelJob<T>* __restric
         for (int q = 0; q < 4; ++q)
             rv[a][q] = r[min(max(2 * N - 1 + a, 0), 2 * F) * sn + min(max(2 * M - 1 + q, 0), 2 * E - 1) * st];
     const T d = J.first ? J.cst[comp * PL_VY * J.cplane + k] : T(1);
-    const bool lo = M > 0, hi = M < E - 1;
-    const double wt[4] = {0.25, lo ? 0.75 : 1.0, hi ? 0.75 : 1.0, 0.25};
-    double s = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const double t = s + (a == 1 ? 0.25 : 0.125) * wt[q] * (double)rv[a][q];
-            s = (q == 0 && !lo) || (q == 3 && !hi) ? s : t;
-        }
-    const T bc = unk ? T(s) : T(0);
-    (comp == 0 ? J.cbx : J.cby)[k] = bc;
-    if (J.first) (comp == 0 ? J.cwx : J.cwy)[k] = unk ? jac_step<T>(T(0), omega / d, bc, -T(0)) : T(0);
-    else (comp == 0 ? J.cvx : J.cvy)[k] = T(0);
+    store_coarse<T>(J, comp, k, N >= 1 && N <= F - 1, restrict_sum<T>(rv, M > 0, M < E - 1), d, omega);
 }
 
 // v += P e_c on the fine unknowns.

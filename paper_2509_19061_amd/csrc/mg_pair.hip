@@ -81,16 +81,25 @@ __device__ __forceinline__ T row_sum(const T (&cf)[NCOEF], const T* win, int str
 
 // UP = false: v holds the first sweep; w <- the second, r <- its residual.
 // UP = true: v <- two sweeps of w + P e_c.
-template <typename T, bool UP, int RX>
-__global__ __launch_bounds__(2 * RX * RY, 4) void k_mg_pair(const LevelJob<T>* __restrict__ jobs,
+// REST (down): the residual is restricted here as well and not stored.  A coarse unknown
+// takes fine values from one position below its own pair to one above, so a region owns two
+// positions less each way, REST_X x REST_Y at an even start: worth it where the regions
+// still run all at once (128^2 FP64: 8.5 us for 7.2 and the restriction's 4.5, and a launch;
+// V-cycle 1280 x 960 FP32 165 -> 159.5 us).
+constexpr int REST_X = RX_SMALL - 2 * RIM - 2, REST_Y = RY - 2 * RIM - 2;
+
+template <typename T, bool UP, int RX, bool REST>
+__global__ __launch_bounds__(2 * RX * RY, REST ? 2 : 4) void k_mg_pair(const LevelJob<T>* __restrict__ jobs,
                                                             const int* __restrict__ pre, int n, T omega) {
-    constexpr int NPOS = RX * RY, NTH = 2 * NPOS, OX = RX - 2 * RIM, WX = RX + 2 * RIM;
+    constexpr int NPOS = RX * RY, NTH = 2 * NPOS, WX = RX + 2 * RIM, LOW = REST ? RIM + 1 : RIM;
+    constexpr int OX = REST ? REST_X : RX - 2 * RIM, OYR = REST ? REST_Y : OY;  // owned, from LOW on
+    static_assert(!REST || (!UP && RX == RX_SMALL), "the restricting form");
     __shared__ T win[2 * WX * WY], mid[2 * NPOS];
     const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int inst = find_pair_inst(pre, n, b);
     const LevelJob<T>& J = jobs[inst];
     const int nx = J.nx, ny = J.ny, lb = b - pre[inst], ntx = (nx + 1 + OX - 1) / OX;
-    const int i0 = (lb % ntx) * OX - RIM, j0 = (lb / ntx) * OY - RIM;  // position of region element (0, 0)
+    const int i0 = (lb % ntx) * OX - LOW, j0 = (lb / ntx) * OYR - LOW;  // position of region element (0, 0)
     const int64_t ld = J.ld;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int comp = wave / (NPOS / 64), e = (int)threadIdx.x & (NPOS - 1), x = e % RX, y = e / RX;
@@ -101,6 +110,14 @@ __global__ __launch_bounds__(2 * RX * RY, 4) void k_mg_pair(const LevelJob<T>* _
     if (comp == 0) load_row<T, 0>(J, i, j, unk, cf);
     else load_row<T, 1>(J, i, j, unk, cf);
     const T rhs = unk ? (comp == 0 ? J.bx : J.by)[k] : T(0);
+    // REST: the coarse unknown of this thread and its diagonal
+    constexpr int CX = REST_X / 2, CY = REST_Y / 2;
+    const int cc = (int)threadIdx.x / (CX * CY), I = (i0 + LOW) / 2 + (int)threadIdx.x % CX;
+    const int Jc = (j0 + LOW) / 2 + (int)threadIdx.x / CX % CY;
+    const int64_t ck = (int64_t)Jc * J.cld + I;
+    const bool cin = REST && cc < 2 && (cc == 0 ? I <= J.cnx && Jc < J.cny : I < J.cnx && Jc <= J.cny);
+    T cd = T(1);
+    if (REST && cin && J.first) cd = J.cst[cc * PL_VY * J.cplane + ck];
     for (int q = threadIdx.x; q < 2 * WX * WY; q += NTH) {
         const int c = q / (WX * WY), r = (q / WX) % WY, ii = i0 - RIM + q % WX, jj = j0 - RIM + r;
         T val;
@@ -129,16 +146,35 @@ __global__ __launch_bounds__(2 * RX * RY, 4) void k_mg_pair(const LevelJob<T>* _
     u = unk ? u : T(0);
     mid[comp * NPOS + e] = u;
     __syncthreads();
-    const bool own = x >= RIM && x < RX - RIM && y >= RIM && y < RY - RIM &&
-                     (comp == 0 ? (i <= nx && j < ny) : (i < nx && j <= ny));
-    if (!own) return;
-    const T av = comp == 0 ? row_sum<T, 0, RX>(cf, mid, NPOS, e) : row_sum<T, 1, RX>(cf, mid, NPOS, e);
+    const bool box = comp == 0 ? i <= nx && j < ny : i < nx && j <= ny;
+    const bool own = box && x >= LOW && x < LOW + OX && y >= LOW && y < LOW + OYR;
+    if (!REST && !own) return;
+    const bool second = x >= RIM && x < RX - RIM && y >= RIM && y < RY - RIM;
+    T av = T(0);
+    if (!REST || second) av = comp == 0 ? row_sum<T, 0, RX>(cf, mid, NPOS, e) : row_sum<T, 1, RX>(cf, mid, NPOS, e);
     if constexpr (UP) {
         const T o = jac_step<T>(u, g, rhs, -av);
         (comp == 0 ? J.vx : J.vy)[k] = unk ? o : T(0);
     } else {
-        (comp == 0 ? J.wx : J.wy)[k] = u;
-        (comp == 0 ? J.rx : J.ry)[k] = unk ? rhs + av : T(0);
+        if (own) (comp == 0 ? J.wx : J.wy)[k] = u;
+        const T r = unk ? rhs + av : T(0);
+        if constexpr (!REST) {
+            (comp == 0 ? J.rx : J.ry)[k] = r;
+        } else {  // the first window is free
+            if (second) win[comp * NPOS + e] = r;
+            __syncthreads();
+            if (!cin) return;
+            const int N = cc == 0 ? I : Jc, M = cc == 0 ? Jc : I, E = cc == 0 ? J.cny : J.cnx, F = cc == 0 ? J.cnx : J.cny;
+            T rv[3][4];
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n = min(max(2 * N - 1 + a, 0), 2 * F), t = min(max(2 * M - 1 + q, 0), 2 * E - 1);
+                    rv[a][q] = win[cc * NPOS + ((cc == 0 ? t : n) - j0) * RX + (cc == 0 ? n : t) - i0];
+                }
+            store_coarse<T>(J, cc, ck, N >= 1 && N <= F - 1, restrict_sum<T>(rv, M > 0, M < E - 1), cd, omega);
+        }
     }
 }
 
@@ -267,27 +303,25 @@ __global__ __launch_bounds__(128 * RG, sizeof(T) == 4 ? 3 : 2) void k_mg_pair_wa
 
 }  // namespace
 
-int mg_pair_tiles(int nx, int ny, bool small) {
-    const int ox = (small ? RX_SMALL : RX_WIDE) - 2 * RIM;
-    return ((nx + 1 + ox - 1) / ox) * ((ny + 1 + OY - 1) / OY);
+int mg_pair_tiles(int nx, int ny, PairKind kind) {
+    const int ox = kind == PAIR_WIDE ? RX_WIDE - 2 * RIM : kind == PAIR_SMALL ? RX_SMALL - 2 * RIM : REST_X;
+    const int oy = kind == PAIR_REST ? REST_Y : OY;
+    return ((nx + 1 + ox - 1) / ox) * ((ny + 1 + oy - 1) / oy);
 }
 
 template <typename T>
-int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, bool small) {
+int mg_pair(stk_ctx* ctx, const Batch& b, double omega, bool up, PairKind kind) {
     if (!b.n) return STK_OK;
     const auto* jobs = static_cast<const LevelJob<T>*>(b.jobs);
-    const dim3 grid((unsigned)b.blocks), block(2 * (small ? RX_SMALL : RX_WIDE) * RY);
-    if (up && small)
-        hipLaunchKernelGGL((k_mg_pair<T, true, RX_SMALL>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
-    else if (up)
-        hipLaunchKernelGGL((k_mg_pair<T, true, RX_WIDE>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
-    else if (small)
-        hipLaunchKernelGGL((k_mg_pair<T, false, RX_SMALL>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
-    else
-        hipLaunchKernelGGL((k_mg_pair<T, false, RX_WIDE>), grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
+    const dim3 grid((unsigned)b.blocks), block(2 * (kind == PAIR_WIDE ? RX_WIDE : RX_SMALL) * RY);
+    const auto kernel = kind == PAIR_REST ? k_mg_pair<T, false, RX_SMALL, true>
+                        : kind == PAIR_WIDE ? (up ? k_mg_pair<T, true, RX_WIDE, false> : k_mg_pair<T, false, RX_WIDE, false>)
+                                            : (up ? k_mg_pair<T, true, RX_SMALL, false> : k_mg_pair<T, false, RX_SMALL, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, jobs, b.pre, b.n, T(omega));
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
+
 void mg_pair_walk_shape(const stk_ctx* ctx, int es, const int* nx, const int* ny, int n, std::vector<FineShape>* shapes,
                         std::vector<int>* pre) {
     const int64_t slots = (int64_t)std::max(ctx->num_cu, 1) * (es == 8 ? 4 : 8) / RG;
@@ -330,7 +364,7 @@ int mg_pair_walk(stk_ctx* ctx, const Batch& b, const FineShape* shapes, double o
 template int mg_pair_walk<double>(stk_ctx*, const Batch&, const FineShape*, double, bool);
 template int mg_pair_walk<float>(stk_ctx*, const Batch&, const FineShape*, double, bool);
 
-template int mg_pair<double>(stk_ctx*, const Batch&, double, bool, bool);
-template int mg_pair<float>(stk_ctx*, const Batch&, double, bool, bool);
+template int mg_pair<double>(stk_ctx*, const Batch&, double, bool, PairKind);
+template int mg_pair<float>(stk_ctx*, const Batch&, double, bool, PairKind);
 
 }  // namespace stk

@@ -85,4 +85,31 @@ __device__ __forceinline__ double prolong_sy(const LevelJob<T>& J, int i, int j)
     return s;
 }
 
+// The coarse right-hand side P^T r / 4 at one coarse unknown from its 3 x 4 window of fine
+// values rv[normal][tangential]: fine faces 2 N - 1 .. 2 N + 1 of the coarse face N with 1/2,
+// 1, 1/2, fine rows 2 M - 1 .. 2 M + 2 of the coarse row M with 1/4, 3/4, 3/4, 1/4, mirrored at
+// the walls (lo, hi: there is a row below, above).  Terms in window order.
+template <typename T>
+__device__ __forceinline__ T restrict_sum(const T (&rv)[3][4], bool lo, bool hi) {
+    const double wt[4] = {0.25, lo ? 0.75 : 1.0, hi ? 0.75 : 1.0, 0.25};
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double t = s + (a == 1 ? 0.25 : 0.125) * wt[q] * (double)rv[a][q];
+            s = (q == 0 && !lo) || (q == 3 && !hi) ? s : t;
+        }
+    return T(s);
+}
+// It and the coarse iterate at the coarse unknown (comp, k): 0, or (J.first) the first sweep
+// from 0, w = jac_step(0, omega / d, b, -0) with d the diagonal there.
+template <typename T>
+__device__ __forceinline__ void store_coarse(const LevelJob<T>& J, int comp, int64_t k, bool unk, T bc, T d, T omega) {
+    bc = unk ? bc : T(0);
+    (comp == 0 ? J.cbx : J.cby)[k] = bc;
+    if (J.first) (comp == 0 ? J.cwx : J.cwy)[k] = unk ? jac_step<T>(T(0), omega / d, bc, -T(0)) : T(0);
+    else (comp == 0 ? J.cvx : J.cvy)[k] = T(0);
+}
+
 }  // namespace stk
