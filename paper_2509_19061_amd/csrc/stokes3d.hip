@@ -235,7 +235,7 @@ __global__ __launch_bounds__(J3X* J3Y) void k_jacobi3d(Fields3<T> f, T omega, co
 // 2^32 bytes), and every load is made unconditionally from a place on the
 // arrays and its value dropped where it does not count, so no load waits under
 // a branch.  Same operands and same row arithmetic as the gathering kernel.
-constexpr int ZX = 64, ZY = 4, ZS = 32;               // tile columns, rows, planes per segment
+constexpr int ZX = 64, ZY = 4, ZS = 32;               // tile columns, rows, most planes per segment
 constexpr int ZNT = ZX * ZY;
 constexpr int ZWX = ZX + 2, ZWY = ZY + 2;              // staged window (one halo cell each side)
 constexpr int ZPL = ZWX * ZWY;                         // window cells of one component and plane
@@ -339,13 +339,13 @@ template <typename T, int OP>
 __global__ __launch_bounds__(ZNT) void k_walk3d(Fields3<T> f, T omega, const T* __restrict__ vx,
                                                  const T* __restrict__ vy, const T* __restrict__ vz,
                                                  T* __restrict__ ox, T* __restrict__ oy, T* __restrict__ oz,
-                                                 double* __restrict__ part, int ntx, int nty) {
+                                                 double* __restrict__ part, int ntx, int nty, int zs) {
     __shared__ T ring[4 * ZSLOT];
     const int nx = f.nx, ny = f.ny, nz = f.nz;
     // tiles numbered x fastest, then y, then z segments, renumbered by XCD
     const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int tx = t % ntx, ty = (t / ntx) % nty, tz = t / (ntx * nty);
-    const int i0 = tx * ZX, j0 = ty * ZY, k0 = tz * ZS, k1 = min(k0 + ZS, nz);
+    const int i0 = tx * ZX, j0 = ty * ZY, k0 = tz * zs, k1 = min(k0 + zs, nz);
     const int i = i0 + (int)(threadIdx.x % ZX), j = j0 + (int)(threadIdx.x / ZX);
     const bool act = i < nx && j < ny;
     const int ic = min(i, nx - 1), jc = min(j, ny - 1);  // inactive threads load from the last cell
@@ -663,28 +663,36 @@ int check_grid3(const stk_grid3* g) {
     return STK_OK;
 }
 
-// Workgroups of the plane-streaming kernels, 0 where they cannot take the grid:
-// they address each array by 32-bit byte offsets.
+// Workgroups of the plane-streaming kernels, 0 where they cannot take the grid (they
+// address each array by 32-bit byte offsets), and *zs, the planes of a segment: at most ZS,
+// equal, and fewer (not under 4; each segment stages three planes more than it owns) while
+// there are less than two workgroups per CU.  A sweep with segments of 32 and with these,
+// FP64: 24^3 39 and 9.4 us, 70 x 108 x 36 62 and 14, 120^3 51 and 45, 160 x 144 x 150 (30
+// planes) 125 and 115 us.
 template <typename T>
-int64_t walk3d_groups(const stk_grid3* g) {
-    const int64_t ntx = (g->nx + ZX - 1) / ZX, nty = (g->ny + ZY - 1) / ZY, ntz = (g->nz + ZS - 1) / ZS;
-    const int64_t nwg = ntx * nty * ntz;
+int64_t walk3d_groups(const stk_ctx* ctx, const stk_grid3* g, int* zs) {
+    const int64_t nt = (int64_t)((g->nx + ZX - 1) / ZX) * ((g->ny + ZY - 1) / ZY);
+    int n = (g->nz + ZS - 1) / ZS;
+    while (nt * n < 2 * ctx->num_cu && n < g->nz / 4) ++n;
+    *zs = (g->nz + n - 1) / n;
+    const int64_t nwg = nt * ((g->nz + *zs - 1) / *zs);
     return nwg < INT32_MAX && (uint64_t)(g->nz + 1) * (uint64_t)g->lp * sizeof(T) <= UINT32_MAX ? nwg : 0;
 }
 template <typename T, int OP>
-void walk3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, int64_t nwg, double omega, const void* vx,
+void walk3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, int64_t nwg, int zs, double omega, const void* vx,
             const void* vy, const void* vz, void* ox, void* oy, void* oz, void* part) {
     hipLaunchKernelGGL((k_walk3d<T, OP>), dim3((unsigned)nwg), dim3(ZX * ZY), 0, ctx->stream, f, T(omega),
                        static_cast<const T*>(vx), static_cast<const T*>(vy), static_cast<const T*>(vz),
                        static_cast<T*>(ox), static_cast<T*>(oy), static_cast<T*>(oz), static_cast<double*>(part),
-                       (g->nx + ZX - 1) / ZX, (g->ny + ZY - 1) / ZY);
+                       (g->nx + ZX - 1) / ZX, (g->ny + ZY - 1) / ZY, zs);
 }
 
 template <typename T>
 int launch_jacobi3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, double omega, const void* vx,
                     const void* vy, const void* vz, void* ox, void* oy, void* oz) {
-    if (const int64_t nwg = walk3d_groups<T>(g)) {
-        walk3d<T, Z_JACOBI>(ctx, g, f, nwg, omega, vx, vy, vz, ox, oy, oz, nullptr);
+    int zs = 0;
+    if (const int64_t nwg = walk3d_groups<T>(ctx, g, &zs)) {
+        walk3d<T, Z_JACOBI>(ctx, g, f, nwg, zs, omega, vx, vy, vz, ox, oy, oz, nullptr);
     } else {
         hipLaunchKernelGGL(k_jacobi3d<T>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream, f, T(omega),
                            static_cast<const T*>(vx), static_cast<const T*>(vy), static_cast<const T*>(vz),
@@ -697,8 +705,9 @@ int launch_jacobi3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, doubl
 template <typename T>
 int launch_residual3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
                       const void* vz, void* rx, void* ry, void* rz) {
-    if (const int64_t nwg = walk3d_groups<T>(g)) {
-        walk3d<T, Z_RESIDUAL>(ctx, g, f, nwg, 1.0, vx, vy, vz, rx, ry, rz, nullptr);
+    int zs = 0;
+    if (const int64_t nwg = walk3d_groups<T>(ctx, g, &zs)) {
+        walk3d<T, Z_RESIDUAL>(ctx, g, f, nwg, zs, 1.0, vx, vy, vz, rx, ry, rz, nullptr);
     } else {
         hipLaunchKernelGGL(k_residual3d<T>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream, f, (const T*)vx, (const T*)vy,
                            (const T*)vz, (T*)rx, (T*)ry, (T*)rz);
@@ -711,13 +720,14 @@ int launch_residual3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, con
 template <typename T>
 int launch_energy3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
                     const void* vz, double* red) {
-    const int64_t nwg = walk3d_groups<T>(g);
+    int zs = 0;
+    const int64_t nwg = walk3d_groups<T>(ctx, g, &zs);
     const dim3 gr = grid3(g);
     const int64_t npart = nwg ? nwg : (int64_t)gr.x * gr.y * gr.z;
     void* part = nullptr;
     STK_TRY(scratch(ctx, stk_ctx::S_PART, sizeof(double) * 2 * (size_t)npart, &part));
     if (nwg)
-        walk3d<T, Z_ENERGY>(ctx, g, f, nwg, 1.0, vx, vy, vz, nullptr, nullptr, nullptr, part);
+        walk3d<T, Z_ENERGY>(ctx, g, f, nwg, zs, 1.0, vx, vy, vz, nullptr, nullptr, nullptr, part);
     else
         hipLaunchKernelGGL(k_energy3d<T>, gr, dim3(J3X, J3Y), 0, ctx->stream, f, (const T*)vx, (const T*)vy,
                            (const T*)vz, (double*)part);
