@@ -59,20 +59,19 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per launch of the streaming RAS kernel (4096^2, FP64, T = 64,
-# k = h = 4) from rocprofv3 FETCH_SIZE / WRITE_SIZE, each scaled by what the
+# HBM bytes per launch of the pipelined sweeps (4096^2, FP64, k = 4) from rocprofv3 FETCH_SIZE / WRITE_SIZE, each scaled by what the
 # counter reads for the stream probe k_stream6 of known size in the same run
-# (profiles/k_ras_stream_4096_f64_k4.md).
+# (profiles/k_jacobi_pipe_4096_f64_k4.md).
 # Valid only for the kernel code it was measured on: reported as null once the
 # hash of its sources (comments and blank space removed) differs.
-RAS_TRAFFIC = {"sources_sha256_16": "6f82aceae28ffd59", "bytes_per_launch": 1.1088e9, "n": 4096, "k": 4, "dtype": "f64"}
+RAS_TRAFFIC = {"sources_sha256_16": "5afedb37010da74b", "bytes_per_launch": 1.1808e9, "n": 4096, "k": 4, "dtype": "f64"}
 
 
 def ras_sources_hash():
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("ras_stream.hip", "stencil.hpp", "wave.hpp"):
+    for f in ("jacobi_pipe.hip", "jacobi_pipe.hpp", "rowstream.hpp", "stencil.hpp", "wave.hpp"):
         with open(os.path.join(ROOT, "paper_2509_19061_amd", "csrc", f), encoding="utf-8") as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)  # block comments
@@ -172,28 +171,19 @@ def main():
         f"E = {e[3]:.3e}")
 
     # ---- dominant kernel: one RAS outer iteration per launch, timed live ----
-    # (a context that insists on the streaming kernel, so the timed kernel is known)
-    os.environ["STK_RAS_KERNEL"] = "stream"
-    kctx = api.Context(0)
-    del os.environ["STK_RAS_KERNEL"]
-    kernel_name = "k_ras_stream"
+    kernel_name = "k_jacobi_pipe" if k <= 10 else "k_ras_stream"
     bx, by = dp.fx, dp.fy
     ax, ay = dp.velocity()
     cx, cy = dp.velocity()
     shifts = api.ras_shifts(3, 64, 64, 64)
     nl = max(sweeps // k, 8)
-    try:
-        api.ras_outer(kctx, dt, dp.grid, ax, ay, dp.eta_c, dp.eta_n, bx, by, cx, cy, 0.7, 64, 64, k, k, *shifts[0])
-    except api.StkError:
-        kctx.close()
-        kctx, kernel_name = ctx, "k_ras"
     for t in range(2):
-        api.ras_outer(kctx, dt, dp.grid, ax, ay, dp.eta_c, dp.eta_n, bx, by, cx, cy, 0.7, 64, 64, k, k, *shifts[t])
+        api.ras_outer(ctx, dt, dp.grid, ax, ay, dp.eta_c, dp.eta_n, bx, by, cx, cy, 0.7, 64, 64, k, k, *shifts[t])
     torch.cuda.synchronize()
     ev0.record()
     for t in range(nl):
         src, dst = ((ax, ay), (cx, cy)) if t % 2 == 0 else ((cx, cy), (ax, ay))
-        api.ras_outer(kctx, dt, dp.grid, *src, dp.eta_c, dp.eta_n, bx, by, *dst, 0.7, 64, 64, k, k,
+        api.ras_outer(ctx, dt, dp.grid, *src, dp.eta_c, dp.eta_n, bx, by, *dst, 0.7, 64, 64, k, k,
                       *shifts[t % len(shifts)])
     ev1.record()
     torch.cuda.synchronize()
@@ -207,11 +197,11 @@ def main():
     # (6 planes read, 2 written) over the same arrays, timed the same way
     probe_in = [dp.eta_c, dp.eta_n, dp.fx, dp.fy, ax, ay]
     for _ in range(3):
-        api.stream_probe(kctx, dt, dp.grid, probe_in, [cx, cy])
+        api.stream_probe(ctx, dt, dp.grid, probe_in, [cx, cy])
     torch.cuda.synchronize()
     ev0.record()
     for _ in range(20):
-        api.stream_probe(kctx, dt, dp.grid, probe_in, [cx, cy])
+        api.stream_probe(ctx, dt, dp.grid, probe_in, [cx, cy])
     ev1.record()
     torch.cuda.synchronize()
     probe_ms = ev0.elapsed_time(ev1) / 20
@@ -223,7 +213,7 @@ def main():
                "ras_alg_rate_over_ceiling": round(achieved / probe_gbs, 4)}
     log(f"[bench] streaming ceiling: {probe_ms:.4f} ms, {probe_gbs:.0f} GB/s ({probe_gbs / HBM_PEAK_GBS:.1%} of peak); "
         f"RAS at {achieved / probe_gbs:.1%} of it")
-    fp32 = run_fp32_leg(kctx, prob, sweeps) if args.dtype == "f64" and args.variants == "all" else None
+    fp32 = run_fp32_leg(ctx, prob, sweeps) if args.dtype == "f64" and args.variants == "all" else None
 
     # ---- all variants, 100 sweeps each ----
     variants = {}
@@ -313,7 +303,7 @@ def main():
             log(f"[bench] CPU oracle, 1 thread: {cpu['one_thread']['value']} GLUP/s ({el1:.1f} s)")
 
     del vx, vy, ax, ay, cx, cy
-    t_ok = (kernel_name == "k_ras_stream" and RAS_TRAFFIC["sources_sha256_16"] == ras_sources_hash()
+    t_ok = (kernel_name == "k_jacobi_pipe" and RAS_TRAFFIC["sources_sha256_16"] == ras_sources_hash()
             and (n, k, args.dtype) == (RAS_TRAFFIC["n"], RAS_TRAFFIC["k"], RAS_TRAFFIC["dtype"]))
     traffic = RAS_TRAFFIC["bytes_per_launch"] if t_ok else None
     solve = run_solves(ctx, args.solve_n) if args.solve_n > 0 else None
@@ -365,8 +355,6 @@ def main():
         "fp64_floor": floor,
     }
     print(json.dumps(out), flush=True)
-    if kctx is not ctx:
-        kctx.close()
     ctx.close()
 
 
@@ -379,9 +367,7 @@ def kernel_only(args):
     dt = torch.float64 if args.dtype == "f64" else torch.float32
     n, k = args.n, args.k
     prob = inputs.smoother_workload(n, 2)
-    os.environ["STK_RAS_KERNEL"] = "stream"
     ctx = api.Context(0)
-    del os.environ["STK_RAS_KERNEL"]
     dp = fields.DeviceProblem(prob, dt)
     (ax, ay), (cx, cy) = dp.velocity(), dp.velocity()
     shifts = api.ras_shifts(3, args.kernel_only, 64, 64)
@@ -398,7 +384,7 @@ def kernel_only(args):
     probe_in = [dp.eta_c, dp.eta_n, dp.fx, dp.fy, ax, ay]
     _, csecs = _timed(lambda: [api.stream_probe(ctx, dt, dp.grid, probe_in, [cx, cy]) for _ in range(2)])
     w = 8 if dt == torch.float64 else 4
-    out = {"kernel": "k_ras_stream", "n": n, "k": k, "launches": args.kernel_only,
+    out = {"kernel": "k_jacobi_pipe", "n": n, "k": k, "launches": args.kernel_only,
            "ms_per_launch": round(secs * 1e3 / args.kernel_only, 4),
            "alg_bytes_per_launch": 8 * w * n * n,
            "calibration_kernel": "k_stream6", "calibration_read_bytes": 6 * w * (n + 1) * dp.ld,
@@ -674,9 +660,9 @@ def run_fp32_leg(ctx, prob, sweeps, ks=(2, 4, 8)):
     alg = 8 * 4 * cells
     ach = alg / (launch_ms * 1e-3) / 1e9
     out["roofline"] = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                       "frac": round(ach / HBM_PEAK_GBS, 4), "kernel": "k_ras_stream<float> (k=4, per launch)",
+                       "frac": round(ach / HBM_PEAK_GBS, 4), "kernel": "k_jacobi_pipe<float> (k=4, per launch)",
                        "launch_ms": round(launch_ms, 4), "alg_bytes_per_launch": alg}
-    log(f"[bench] fp32 k_ras_stream k=4: {launch_ms:.4f} ms/launch, {ach:.0f} GB/s effective")
+    log(f"[bench] fp32 k_jacobi_pipe k=4: {launch_ms:.4f} ms/launch, {ach:.0f} GB/s effective")
     del ax, ay, cx, cy, dp
     return out
 
