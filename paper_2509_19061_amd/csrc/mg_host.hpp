@@ -35,8 +35,8 @@ inline int64_t pad_ld(int nx) { return ((int64_t)nx + 1 + 63) / 64 * 64; }
 struct PlanT {
     int n = 0, depth = 0, maxcn = 0;
     std::vector<Batch> fine, crs;       // per depth: fine-block and coarse-block batches of LevelJob
-    std::vector<const void*> cjobs;     // per depth: CoarseJob array of instances whose coarsest it is
-    std::vector<int> ncj;
+    const void* cjobs = nullptr;        // CoarseJob array of the instances that are solved on their coarsest level
+    int ncj = 0;
     // finest level smoothed by batched RAS outer iterations (64 x 64 tiles, halo
     // = k = the sweep count, so each is k Jacobi sweeps exactly): job arrays
     // v -> w and w -> v, the finest-level jobs with v and w exchanged (residual
