@@ -453,9 +453,10 @@ int stk_uzawa_solve(stk_mg* mg, const stk_grid* g, double* vx, double* vy, doubl
  * runs its own Anderson steps (the history restarts with the stage, whose
  * map F differs), and max_cycles bounds the steps of all stages together.
  * hist (nullable, HOST, max_cycles + 1 doubles): E of x_0, x_1, ..;
- * rep->cycles counts F evaluations.  Allocates 6 (depth + 1) planes of
- * (ny + 1) * ld doubles and 9 doubles per 256 plane elements (the products'
- * partial sums) for the call's duration.  The l2 norm and the combination
+ * rep->cycles counts F evaluations.  Needs 6 min(depth + 1, max_cycles) planes
+ * of (ny + 1) * ld doubles and 9 doubles per 256 plane elements (the products'
+ * partial sums): up to 1 GiB in the context's scratch, beyond it allocated for
+ * the call's duration.  The l2 norm and the combination
  * take no wall value: walls are read as 0 and written as 0.  Synchronises once per
  * step.  STK_ENOTCONV as stk_uzawa_solve. */
 int stk_uzawa_anderson(stk_mg* mg, const stk_grid* g, double* vx, double* vy, double* p, const double* eta_c,

@@ -13,10 +13,11 @@
 // p: ny x nx).
 //
 // Kernels (FP64, bound by HBM bandwidth):
-//   k_aa_diff_dots  r = F - x, and the products of r with the window's
-//                 residuals (itself included), per-workgroup partials;
-//                 k_aa_dots_final sums them in a fixed order (one workgroup
-//                 per product)
+//   k_aa_begin    x copied to where F is evaluated
+//   k_aa_diff_dots  F stored in the window, r = F - x, and the products of r
+//                 with the window's residuals (itself included), per-workgroup
+//                 partials; k_aa_dots_final sums them in a fixed order (one
+//                 workgroup per product)
 //   k_aa_combine  x = sum_t a_t F_t (products and sums rounded separately, in
 //                 the order t = 0, 1, ..)
 #include <algorithm>
@@ -32,6 +33,15 @@ namespace {
 
 constexpr int AA_MAX = 9;  // window of at most 9 residuals: depth m <= 8
 constexpr int AT = 256;
+
+// The window's memory stays with the context up to this size, and is allocated for the
+// call beyond.  In the driver a free of some hundred MB can take longer than the steps do:
+// 2 steps on 1120 x 864 of depth 3 (190 MB), called in a loop, took 1.0 ms a call at times
+// and 5.5 ms at others while each call allocated and freed its window; now 0.70 ms, and
+// 8 steps on 136 x 96 0.97 ms instead of 1.31 (that and the copies left out).  A larger window
+// belongs to steps that take longer in the same ratio, and is too much to hold back from
+// other uses of the device.
+constexpr size_t WINDOW_KEPT = (size_t)1 << 30;
 
 struct Planes {
     const double* v[AA_MAX][3];
@@ -58,14 +68,33 @@ __device__ __forceinline__ double wsum(double v) {
     return v;
 }
 
+// x to the planes in which F is evaluated (the used extents).
+//
+// Bound by its launch on the grids that Anderson steps are run on: one launch for the
+// three planes, where a copy for each took 5.4 us of the stream and its gap.
+__global__ __launch_bounds__(AT) void k_aa_begin(int nx, int ny, int64_t ld, const double* __restrict__ xx,
+                                                 const double* __restrict__ xy, const double* __restrict__ xp,
+                                                 double* __restrict__ ox, double* __restrict__ oy,
+                                                 double* __restrict__ op) {
+    const int64_t q = (int64_t)blockIdx.x * AT + threadIdx.x;
+    if (q >= (int64_t)(ny + 1) * ld) return;
+    bool ex, ey, ep, ux, uy;
+    masks(q, ld, nx, ny, ex, ey, ep, ux, uy);
+    if (ex) ox[q] = xx[q];
+    if (ey) oy[q] = xy[q];
+    if (ep) op[q] = xp[q];
+}
+
 // r = F - x written to the new residual's planes (0 outside the used
-// extents), and part[t * nblk + block] = sum over the block's elements of
+// extents), F's velocity to the window's planes wx, wy where it was evaluated
+// elsewhere (wx != NULL; unknowns only: nothing else of the window is read), and part[t * nblk + block] = sum over the block's elements of
 // r . r_t for the window's older residuals t < n - 1 and r . r for t = n - 1
 // (the window's newest entry is r itself and is not read back).
 __global__ __launch_bounds__(AT) void k_aa_diff_dots(int nx, int ny, int64_t ld, const double* __restrict__ fx,
                                                      const double* __restrict__ fy, const double* __restrict__ fp,
                                                      const double* __restrict__ xx, const double* __restrict__ xy,
-                                                     const double* __restrict__ xp, double* __restrict__ rx,
+                                                     const double* __restrict__ xp, double* __restrict__ wx,
+                                                     double* __restrict__ wy, double* __restrict__ rx,
                                                      double* __restrict__ ry, double* __restrict__ rp, Planes o,
                                                      double* __restrict__ part) {
     __shared__ double red[AA_MAX][AT / 64];
@@ -75,9 +104,12 @@ __global__ __launch_bounds__(AT) void k_aa_diff_dots(int nx, int ny, int64_t ld,
     if (q < cnt) {
         bool ex, ey, ep, ux, uy;
         masks(q, ld, nx, ny, ex, ey, ep, ux, uy);
-        a = ux ? fx[q] - xx[q] : 0.0;  // wall values of F and x take no part
-        b = uy ? fy[q] - xy[q] : 0.0;
+        const double f = ux ? fx[q] : 0.0, h = uy ? fy[q] : 0.0;
+        a = ux ? f - xx[q] : 0.0;  // wall values of F and x take no part
+        b = uy ? h - xy[q] : 0.0;
         c = ep ? fp[q] - xp[q] : 0.0;
+        if (wx && ux) wx[q] = f;
+        if (wx && uy) wy[q] = h;
         rx[q] = a;
         ry[q] = b;
         rp[q] = c;
@@ -224,19 +256,28 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
     STK_TRY(use_device(ctx));
     const int W = depth + 1;                          // ring of W slots
     const int64_t plane = (int64_t)(g->ny + 1) * g->ld;
-    const size_t pb = (size_t)plane * sizeof(double);
-    Dev ring, dots;
-    STK_TRY(ring.alloc(pb * 3 * 2 * (size_t)W));      // F and R vectors, 3 planes each
-    STK_TRY(dots.alloc(sizeof(double) * AA_MAX));
-    double* base = static_cast<double*>(ring.p);
+    const int64_t nblk = (plane + AT - 1) / AT;
+    // The window (F and R vectors, 3 planes each, for as many slots as the steps can
+    // reach) and the products' per-workgroup partials, which are not in S_PART: the Uzawa
+    // cycles and norms of every step use (and may regrow) that.
+    const int64_t win = plane * 3 * 2 * std::max(1, std::min(W, o.max_cycles));
+    const size_t bytes = sizeof(double) * (size_t)(win + nblk * AA_MAX);
+    Dev own;
+    void* mem = nullptr;
+    if (bytes <= WINDOW_KEPT) {
+        const int rc = scratch(ctx, stk_ctx::S_AA, bytes, &mem);
+        if (rc != STK_OK) {
+            (void)hipGetLastError();
+            return rc;
+        }
+    } else {
+        STK_TRY(own.alloc(bytes));
+        mem = own.p;
+    }
+    double* base = static_cast<double*>(mem);
+    double* part = base + win;
     auto F = [&](int s, int c) { return base + ((int64_t)(2 * s) * 3 + c) * plane; };
     auto R = [&](int s, int c) { return base + ((int64_t)(2 * s + 1) * 3 + c) * plane; };
-    const int64_t nblk = (plane + AT - 1) / AT;
-    // the products' per-workgroup partials have a buffer of their own: the Uzawa
-    // cycles and norms of every step use (and may regrow) the context's scratch
-    Dev parts;
-    STK_TRY(parts.alloc(sizeof(double) * (size_t)nblk * AA_MAX));
-    double* part = static_cast<double*>(parts.p);
     const dim3 eg((unsigned)nblk), eb(AT);
     std::vector<double> H((size_t)W * W, 0.0);       // Gram matrix over ring slots
     double out[5];
@@ -259,22 +300,22 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
             // F(x_k) into slot sk: one Uzawa cycle from x_k.  The hierarchy's
             // level 0 has the caller's row stride: the V-cycle runs in its own
             // level-0 vectors (iterate loaded from x_k, right-hand side folded in
-            // place).
-            const size_t rowb = (size_t)g->ld * sizeof(double);
-            STK_HIP(hipMemcpy2DAsync(F(sk, 2), rowb, p, rowb, (size_t)g->nx * sizeof(double), g->ny,
-                                     hipMemcpyDeviceToDevice, ctx->stream));
-            if (o.mode == STK_SOLVE_F32_REFINED) {
+            // place), and the pass over F that forms the residual stores it in the slot.
+            const bool mixed = o.mode == STK_SOLVE_F32_REFINED;
+            double* fvx = mixed ? F(sk, 0) : zx;
+            double* fvy = mixed ? F(sk, 1) : zy;
+            hipLaunchKernelGGL(k_aa_begin, eg, eb, 0, ctx->stream, g->nx, g->ny, g->ld, (const double*)vx,
+                               (const double*)vy, (const double*)p, fvx, fvy, F(sk, 2));
+            STK_HIP(hipGetLastError());
+            if (mixed) {
                 // FP32 V-cycles on the FP64 residual
-                STK_TRY(copy_vel_in(mm, vx, vy, g->ld, F(sk, 0), F(sk, 1), g->ld, sizeof(double)));
                 for (int c = 0; c < o.vcycles; ++c)
                     STK_TRY(mixed_correction(mm, g, F(sk, 0), F(sk, 1), p, ec, en, fx, fy));
             } else {
-                STK_TRY(copy_vel_in(mm, vx, vy, g->ld, zx, zy, g->ld, sizeof(double)));
                 STK_TRY(launch_fold_rhs(ctx, STK_F64, g, fx, fy, p, rx0, ry0));
                 for (int c = 0; c < o.vcycles; ++c) STK_TRY(run_vcycle(ctx, *mm->plan[0], mm->o, 0));
-                STK_TRY(copy_vel_in(mm, zx, zy, g->ld, F(sk, 0), F(sk, 1), g->ld, sizeof(double)));
             }
-            STK_TRY(stk_uzawa_pressure(ctx, g, F(sk, 0), F(sk, 1), ec, o.omega_p, F(sk, 2)));
+            STK_TRY(stk_uzawa_pressure(ctx, g, fvx, fvy, ec, o.omega_p, F(sk, 2)));
             // products of r_k with the window r_{k-mk} .. r_k (oldest first) into
             // the Gram matrix over ring slots
             const int mk = std::min(depth, kk);
@@ -282,17 +323,16 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
             D.n = mk + 1;
             for (int t = 0; t <= mk; ++t)
                 for (int c = 0; c < 3; ++c) D.v[t][c] = R((kk - mk + t) % W, c);
-            hipLaunchKernelGGL(k_aa_diff_dots, eg, eb, 0, ctx->stream, g->nx, g->ny, g->ld, F(sk, 0), F(sk, 1),
-                               F(sk, 2), vx, vy, p, R(sk, 0), R(sk, 1), R(sk, 2), D, part);
+            hipLaunchKernelGGL(k_aa_diff_dots, eg, eb, 0, ctx->stream, g->nx, g->ny, g->ld, (const double*)fvx,
+                               (const double*)fvy, F(sk, 2), vx, vy, p, mixed ? nullptr : F(sk, 0), F(sk, 1), R(sk, 0),
+                               R(sk, 1), R(sk, 2), D, part);
             hipLaunchKernelGGL(k_aa_dots_final, dim3((unsigned)D.n), dim3(1024), 0, ctx->stream, (const double*)part,
-                               nblk, (double*)dots.p);
+                               nblk, ctx->host_red_dev);
             STK_HIP(hipGetLastError());
-            double d[AA_MAX];
-            STK_HIP(hipMemcpyAsync(d, dots.p, sizeof(double) * D.n, hipMemcpyDeviceToHost, ctx->stream));
             STK_HIP(hipStreamSynchronize(ctx->stream));
             for (int t = 0; t <= mk; ++t) {
                 const int st = (kk - mk + t) % W;
-                H[(size_t)sk * W + st] = H[(size_t)st * W + sk] = d[t];
+                H[(size_t)sk * W + st] = H[(size_t)st * W + sk] = ctx->host_red[t];
             }
             // x_1 = F(x_0); later x_{k+1} = sum alpha_t F(x_{k-mk+t})
             Planes P{};
