@@ -294,6 +294,7 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
         double* zy = static_cast<double*>(mm->ks[0][VS_Z].y);
         double* rx0 = static_cast<double*>(mm->ks[0][VS_R].x);
         double* ry0 = static_cast<double*>(mm->ks[0][VS_R].y);
+        bool have = false;  // the norm of x_kk stored the right-hand side of its V-cycle
         int kk = 0;  // index of the current iterate x_kk = (vx, vy, p) within the stage
         while (k < o.max_cycles && (last ? out[3] > o.tol : kk < o.stage_cycles)) {
             const int sk = kk % W;
@@ -310,9 +311,9 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
             if (mixed) {
                 // FP32 V-cycles on the FP64 residual
                 for (int c = 0; c < o.vcycles; ++c)
-                    STK_TRY(mixed_correction(mm, g, F(sk, 0), F(sk, 1), p, ec, en, fx, fy));
+                    STK_TRY(mixed_correction(mm, g, F(sk, 0), F(sk, 1), p, ec, en, fx, fy, have && c == 0));
             } else {
-                STK_TRY(launch_fold_rhs(ctx, STK_F64, g, fx, fy, p, rx0, ry0));
+                if (!have) STK_TRY(launch_fold_rhs(ctx, STK_F64, g, fx, fy, p, rx0, ry0));
                 for (int c = 0; c < o.vcycles; ++c) STK_TRY(run_vcycle(ctx, *mm->plan[0], mm->o, 0));
             }
             STK_TRY(stk_uzawa_pressure(ctx, g, fvx, fvy, ec, o.omega_p, F(sk, 2)));
@@ -353,7 +354,13 @@ int stk_uzawa_anderson(stk_mg* m, const stk_grid* g, double* vx, double* vy, dou
             STK_HIP(hipGetLastError());
             ++k;
             ++kk;
-            STK_TRY(stk_energy_norm(ctx, STK_F64, g, vx, vy, p, eta_c, eta_n, fx, fy, out));
+            EnergyOut eo;
+            if (k < o.max_cycles && (last || kk < o.stage_cycles)) {
+                if (!mixed) eo = {rx0, ry0, false};
+                else if (last) eo = mixed_rhs(mm);  // (the residual of the true system)
+            }
+            STK_TRY(energy_norm(ctx, g, vx, vy, p, eta_c, eta_n, fx, fy, out, eo));
+            have = eo.x != nullptr;
             if (hist) hist[k] = out[3];
         }
         return STK_OK;

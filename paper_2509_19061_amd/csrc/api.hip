@@ -49,6 +49,30 @@ int scratch(stk_ctx* ctx, int s, size_t bytes, void** out) {
     return STK_OK;
 }
 
+// The sums that an energy launch left in the context's pinned buffer, and the norms.
+static int read_energy(stk_ctx* ctx, double out[5]) {
+    STK_HIP(hipStreamSynchronize(ctx->stream));
+    const double nv = ctx->host_red[0], np = ctx->host_red[1], nf = ctx->host_red[2];
+    out[0] = nv;
+    out[1] = np;
+    out[2] = nf;
+    out[3] = std::sqrt((nv + np) / nf);
+    out[4] = std::sqrt(nv / nf);
+    for (int k = 0; k < 5; ++k)
+        if (!std::isfinite(out[k])) return set_error(STK_ENONFINITE, "energy norm is not finite (out[%d] = %g)", k, out[k]);
+    return STK_OK;
+}
+
+int energy_norm(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
+                const double* eta_c, const double* eta_n, const double* fx, const double* fy, double out[5],
+                const EnergyOut& o) {
+    if (o.x)
+        STK_TRY(launch_energy_out(ctx, g, vx, vy, p, eta_c, eta_n, fx, fy, ctx->host_red_dev, o));
+    else
+        STK_TRY(launch_energy(ctx, STK_F64, g, vx, vy, p, eta_c, eta_n, fx, fy, ctx->host_red_dev));
+    return read_energy(ctx, out);
+}
+
 // Can red-black Gauss-Seidel take the pipelined passes?  They are out of place; its
 // half-sweeps are in place and need no scratch, so they stay for what the passes cannot
 // do: rows too long, no memory left for the scratch arrays, or a stream being captured
@@ -348,16 +372,7 @@ int stk_energy_norm(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* v
     // the last reduction writes the sums to pinned host memory (64^2: 28.8 us a call with a copy
     // behind it, now 25.1)
     STK_TRY(launch_energy(ctx, dt, g, vx, vy, p, eta_c, eta_n, fx, fy, ctx->host_red_dev));
-    STK_HIP(hipStreamSynchronize(ctx->stream));
-    const double nv = ctx->host_red[0], np = ctx->host_red[1], nf = ctx->host_red[2];
-    out[0] = nv;
-    out[1] = np;
-    out[2] = nf;
-    out[3] = std::sqrt((nv + np) / nf);
-    out[4] = std::sqrt(nv / nf);
-    for (int k = 0; k < 5; ++k)
-        if (!std::isfinite(out[k])) return set_error(STK_ENONFINITE, "energy norm is not finite (out[%d] = %g)", k, out[k]);
-    return STK_OK;
+    return read_energy(ctx, out);
 }
 
 }  // extern "C"

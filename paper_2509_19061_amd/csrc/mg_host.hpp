@@ -111,9 +111,12 @@ int copy_vel_in(stk_mg* m, const void* sx, const void* sy, int64_t sld, void* dx
 int ensure_dtype(stk_mg* m, int t);
 // FP32 V-cycle correction of an FP64 velocity (uzawa.hip): v += V32(0, (float) r)
 // for the FP64 residual r = f - G p - M v of the finest level (viscosities ec,
-// en), in the caller's layout.
+// en), in the caller's layout.  have: r is in place already (where mixed_rhs points).
 int mixed_correction(stk_mg* m, const stk_grid* g, double* vx, double* vy, const double* p, const double* ec,
-                     const double* en, const double* fx, const double* fy);
+                     const double* en, const double* fx, const double* fy, bool have);
+// Where an energy pass stores the FP32 residual for the next mixed_correction (nothing if
+// that needs a pass of its own).
+EnergyOut mixed_rhs(stk_mg* m);
 // Viscosity continuation (uzawa.hip, Sec. 6.2): for theta = s / o.stages,
 // s < o.stages, calls stage(hierarchy of (1 - theta) eta_min + theta eta, its
 // cell and nodal viscosities, false), then stage(m, eta_c, eta_n, true) for

@@ -15,6 +15,8 @@
 // result is bitwise reproducible.  The two quotients by a diagonal share its
 // reciprocal, and the sum of r_p^2 eta_c is divided once: with five FP64
 // divisions a cell the FP32 norm was bound by them (4096^2: 160 us, now 113).
+#include <type_traits>
+
 #include "rowstream.hpp"
 #include "stk_internal.hpp"
 
@@ -103,23 +105,39 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// One triple (N_v, N_p, N_f) per wave -> part[3 wv + c].
-template <typename T>
+// One triple (N_v, N_p, N_f) per wave -> part[3 wv + c].  The outer loops measure the
+// iterate from which their next cycle starts, and the right-hand side of that cycle is on
+// the way: OUT 1 also stores b = f - G p, OUT 2 the residual rounded to FP32, with the
+// values of the passes that form them alone.  Those read 3 and 7 planes again and cost a
+// launch (an Uzawa cycle at 1024^2, FP64: 244 and 238 us; 1280 x 960, mixed: 234 and 221).
+template <typename T, int OUT>
 __global__ __launch_bounds__(64 * WPB) void k_energy(int nx, int ny, int64_t ld, double idx, double idy, double sp,
                                                      const T* __restrict__ vx,
                                                      const T* __restrict__ vy, const T* __restrict__ p,
                                                      const T* __restrict__ ec, const T* __restrict__ en,
                                                      const T* __restrict__ fx, const T* __restrict__ fy,
-                                                     double* __restrict__ part) {
+                                                     double* __restrict__ part, EnergyOut out) {
     const int wv = xcd_tile((int)blockIdx.x, (int)gridDim.x) * WPB + wave_in_group();
     const Place q = place(wv, nx, ny, walk_length(nx, ny));
     if (q.y0 >= q.y1) return;  // the whole wave (no triple: it is past the last one)
     const Loader<T> L = make_loader<T>(vx, vy, ec, en, fx, fy, p, ld, nx, ny, q.i);
     const int i = q.i;
     const bool xcol = q.own && i >= 1 && i <= nx - 1, ycol = q.own && i >= 0 && i <= nx - 1;
+    using O = std::conditional_t<OUT == 2, float, double>;
+    const unsigned col = (unsigned)i * (unsigned)sizeof(O);
+    const unsigned s_x = q.own ? col : OOB, s_y = ycol ? col : OOB;
     double nv = 0.0, np = 0.0, nf = 0.0;
     walk_rows<T>(L, q.y0, q.y1, [&](const Row<T>& a, const Row<T>& b, const Row<T>& c, int j) {
         const Res<double> r = residual_row<T, double>(a, b, c, p != nullptr, idx, idy);
+        if (OUT) {
+            double x = r.rx, y = r.ry;
+            if (OUT == 1) {
+                x = b.bx + (b.p - wave_shift<DPP_FROM_PREV>(b.p)) * idx;
+                y = b.by + (b.p - a.p) * idy;
+            }
+            store_pair<O>((O*)out.x, (O*)out.y, ld, nx, ny, j, xcol && j <= ny - 1 ? O(x) : O(0),
+                          ycol && j >= 1 && j <= ny - 1 ? O(y) : O(0), s_x, s_y);
+        }
         if (xcol && j <= ny - 1) {
             const double f = b.bx, g = jac_factor(1.0, r.dx_);
             nv += r.rx * r.rx * g;
@@ -210,6 +228,21 @@ int launch_energy(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx,
     return launch_energy_into(ctx, dt, g, vx, vy, p, eta_c, eta_n, fx, fy, static_cast<double*>(part), dst, false);
 }
 
+int launch_energy_out(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
+                      const double* eta_c, const double* eta_n, const double* fx, const double* fy, double* dst,
+                      const EnergyOut& out) {
+    void* part = nullptr;
+    const int64_t triples = energy_partials(g);
+    STK_TRY(scratch(ctx, stk_ctx::S_PART, sizeof(double) * 3 * (size_t)triples, &part));
+    const double idx = 1.0 / g->dx, idy = 1.0 / g->dy, sp = 2.0 * idx * idx + 2.0 * idy * idy;
+    hipLaunchKernelGGL(out.f32 ? (k_energy<double, 2>) : (k_energy<double, 1>), dim3(walk_workgroups(g->nx, g->ny)),
+                       dim3(64 * WPB), 0, ctx->stream, g->nx, g->ny, g->ld, idx, idy, sp, vx, vy, p, eta_c, eta_n, fx,
+                       fy, (double*)part, out);
+    hipLaunchKernelGGL(k_reduce_triples, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, triples, dst, 0);
+    STK_HIP(hipGetLastError());
+    return STK_OK;
+}
+
 int launch_energy_into(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                        const void* eta_c, const void* eta_n, const void* fx, const void* fy, double* part,
                        double* dst, bool finish) {
@@ -218,15 +251,15 @@ int launch_energy_into(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void
     const double idx = 1.0 / g->dx, idy = 1.0 / g->dy, sp = 2.0 * idx * idx + 2.0 * idy * idy;
     const dim3 block(64 * WPB);
     if (dt == STK_F64)
-        hipLaunchKernelGGL(k_energy<double>, dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
+        hipLaunchKernelGGL((k_energy<double, 0>), dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
                            idy, sp, (const double*)vx, (const double*)vy, (const double*)p,
                            (const double*)eta_c, (const double*)eta_n, (const double*)fx, (const double*)fy,
-                           (double*)part);
+                           (double*)part, EnergyOut{});
     else
-        hipLaunchKernelGGL(k_energy<float>, dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
+        hipLaunchKernelGGL((k_energy<float, 0>), dim3(nwg), block, 0, ctx->stream, g->nx, g->ny, g->ld, idx,
                            idy, sp, (const float*)vx, (const float*)vy, (const float*)p,
                            (const float*)eta_c, (const float*)eta_n, (const float*)fx, (const float*)fy,
-                           (double*)part);
+                           (double*)part, EnergyOut{});
     hipLaunchKernelGGL(k_reduce_triples, dim3(1), dim3(1024), 0, ctx->stream, (const double*)part, triples, dst,
                        finish ? 1 : 0);
     STK_HIP(hipGetLastError());

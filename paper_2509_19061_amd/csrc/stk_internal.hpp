@@ -151,6 +151,19 @@ int launch_residual(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* v
                     const void* eta_c, const void* eta_n, const void* fx, const void* fy, void* rx, void* ry,
                     void* rp);
 // Energy partial sums -> 3 doubles in device memory `dst` (N_v, N_p, N_f).
+// What the energy pass of an outer loop stores beside its sums, for the V-cycle that
+// follows from the same iterate: b = f - G p (doubles) or, f32, the residual in floats.
+struct EnergyOut {
+    void *x = nullptr, *y = nullptr;
+    bool f32 = false;
+};
+int launch_energy_out(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
+                      const double* eta_c, const double* eta_n, const double* fx, const double* fy, double* dst,
+                      const EnergyOut& out);
+// stk_energy_norm of checked FP64 arguments, storing `o` where o.x is set.
+int energy_norm(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
+                const double* eta_c, const double* eta_n, const double* fx, const double* fy, double out[5],
+                const EnergyOut& o);
 int launch_energy(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                   const void* eta_c, const void* eta_n, const void* fx, const void* fy, double* dst);
 // Triples of partial sums the energy kernel writes for grid g.

@@ -322,17 +322,23 @@ int uzawa_stage(stk_mg* mm, const stk_grid* g, double* vx, double* vy, double* p
     stk_ctx* ctx = mm->ctx;
     stk_mg* self = mm;
     if (!mm->plan[0]) STK_TRY(make_plan(ctx, &self, 1, 0, &mm->plan[0]));
+    // the norm of a cycle stores the right-hand side of the next, if there may be one
+    auto more = [&](int n) { return k < o.max_cycles && (last || n < o.stage_cycles); };
     if (o.mode == STK_SOLVE_F32_REFINED) {
         // v += V32(0, (float)(f - G p - M v)) per V-cycle; the V-cycle is
         // consistent, so in exact arithmetic this is the FP64 cycle
         int n = 0;
+        bool have = false;
         while (k < o.max_cycles && (last ? out[3] > o.tol : n < o.stage_cycles)) {
             for (int c = 0; c < o.vcycles; ++c)
-                STK_TRY(mixed_correction(mm, g, vx, vy, p, ec_step, en_step, fx, fy));
+                STK_TRY(mixed_correction(mm, g, vx, vy, p, ec_step, en_step, fx, fy, have && c == 0));
             STK_TRY(pressure_update(ctx, g, vx, vy, ec_step, o.omega_p, p));
             ++k;
             ++n;
-            STK_TRY(stk_energy_norm(ctx, STK_F64, g, vx, vy, p, eta_c, eta_n, fx, fy, out));
+            // (the residual is that of the true system, which the last stage's is)
+            const EnergyOut eo = last && more(n) ? mixed_rhs(mm) : EnergyOut{};
+            STK_TRY(energy_norm(ctx, g, vx, vy, p, eta_c, eta_n, fx, fy, out, eo));
+            have = eo.x != nullptr;
             if (hist) hist[k] = out[3];
         }
         return STK_OK;
@@ -343,13 +349,16 @@ int uzawa_stage(stk_mg* mm, const stk_grid* g, double* vx, double* vy, double* p
     double* by = static_cast<double*>(mm->ks[0][VS_R].y);
     STK_TRY(copy_vel_in(mm, vx, vy, g->ld, wx, wy, g->ld, sizeof(double)));
     int n = 0;
+    bool have = false;
     while (k < o.max_cycles && (last ? out[3] > o.tol : n < o.stage_cycles)) {
-        STK_TRY(launch_fold_rhs(ctx, STK_F64, g, fx, fy, p, bx, by));  // b = f - G p
+        if (!have) STK_TRY(launch_fold_rhs(ctx, STK_F64, g, fx, fy, p, bx, by));  // b = f - G p
         for (int c = 0; c < o.vcycles; ++c) STK_TRY(run_vcycle(ctx, *mm->plan[0], mm->o, 0));
         STK_TRY(pressure_update(ctx, g, wx, wy, ec_step, o.omega_p, p));
         ++k;
         ++n;
-        STK_TRY(stk_energy_norm(ctx, STK_F64, g, wx, wy, p, eta_c, eta_n, fx, fy, out));
+        const EnergyOut eo = more(n) ? EnergyOut{bx, by, false} : EnergyOut{};
+        STK_TRY(energy_norm(ctx, g, wx, wy, p, eta_c, eta_n, fx, fy, out, eo));
+        have = eo.x != nullptr;
         if (hist) hist[k] = out[3];
     }
     STK_TRY(copy_vel_in(mm, wx, wy, g->ld, vx, vy, g->ld, sizeof(double)));
@@ -360,7 +369,7 @@ int uzawa_stage(stk_mg* mm, const stk_grid* g, double* vx, double* vy, double* p
 }  // namespace
 
 int mixed_correction(stk_mg* m, const stk_grid* g, double* vx, double* vy, const double* p, const double* ec,
-                     const double* en, const double* fx, const double* fy) {
+                     const double* en, const double* fx, const double* fy, bool have) {
     stk_ctx* ctx = m->ctx;
     stk_mg* self = m;
     if (!m->plan[1]) STK_TRY(make_plan(ctx, &self, 1, 1, &m->plan[1]));
@@ -371,14 +380,20 @@ int mixed_correction(stk_mg* m, const stk_grid* g, double* vx, double* vy, const
     // r32 = (float)(f - G p - M v) and, unless the V-cycle starts from zero by itself, z32 = 0 in one pass
     FineIo io;
     io.zero = m->plan[1]->fused;
-    STK_TRY(launch_residual_to32(ctx, g, vx, vy, p, ec, en, fx, fy, static_cast<float*>(m->ks[1][VS_R].x),
-                                 static_cast<float*>(m->ks[1][VS_R].y), io.zero ? nullptr : z32x,
-                                 io.zero ? nullptr : z32y));
+    if (!have)
+        STK_TRY(launch_residual_to32(ctx, g, vx, vy, p, ec, en, fx, fy, static_cast<float*>(m->ks[1][VS_R].x),
+                                     static_cast<float*>(m->ks[1][VS_R].y), io.zero ? nullptr : z32x,
+                                     io.zero ? nullptr : z32y));
     STK_TRY(run_vcycle(ctx, *m->plan[1], m->o, 1, io));
     hipLaunchKernelGGL(k_add_z, eg, eb, 0, ctx->stream, g->nx, g->ny, g->ld, (const float*)z32x, (const float*)z32y,
                        vx, vy);
     STK_HIP(hipGetLastError());
     return STK_OK;
+}
+
+EnergyOut mixed_rhs(stk_mg* m) {
+    if (!m->plan[1] || !m->plan[1]->fused) return {};  // (a V-cycle that needs z32 = 0 stored)
+    return {m->ks[1][VS_R].x, m->ks[1][VS_R].y, true};
 }
 
 int continuation(stk_mg* m, const stk_grid* g, const double* eta_c, const double* eta_n, const stk_uzawa_opts& o,
