@@ -351,7 +351,7 @@ int stk_batch_destroy(stk_batch* b);
  * caller-owned; vx, vy are read now and written when the solve finishes, p,
  * fx, fy are read now).  *slot receives its slot id.  STK_EINVAL if no slot is
  * free, the handle is already in a batch, or its nu1, nu2, omega differ from
- * the batch's.  Asynchronous except for pressure staging. */
+ * the batch's.  Asynchronous, except that it waits for p to be read. */
 int stk_batch_add(stk_batch* b, stk_mg* mg, double* vx, double* vy, const double* p, const double* fx,
                   const double* fy, double tol, int max_iters, int* slot);
 /* Advance every in-flight solve by up to `iters` Krylov iterations.  On

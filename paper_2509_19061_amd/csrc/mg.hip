@@ -368,7 +368,6 @@ int ensure_dtype(stk_mg* m, int t) {
         STK_TRY(dalloc(m, fb0, &m->ks[t][sl].y));
     }
     if (t == 0) {
-        STK_TRY(dalloc(m, fb0, &m->zero64));
         STK_TRY(dalloc(m, fb0, &m->zero[0].x));
         STK_TRY(dalloc(m, fb0, &m->zero[0].y));
     }
@@ -844,10 +843,10 @@ static int vcycle(stk_ctx* ctx, const PlanT& P, const stk_mg_opts& o, const Fine
             STK_TRY(coarse_stage<T>(ctx, P.relax[d + 1], P.relax_t[d + 1], o, nr, first_sweep_done(o, nr)));
         }
     }
-    // Every instance's coarsest solve in one launch, however deep its hierarchy: a launch is
-    // bound by its own round trips (about 30 us) and has one workgroup an instance, and those
-    // of other depths ran one after another (a batch of 1024^2, 512^2 and 256^2, FP32: 3.61 ->
-    // 3.53 ms for 11 iterations).
+    // Every instance's coarsest solve in one launch, however deep its hierarchy: a launch has
+    // a start and an end that fill the chip badly, and those of other depths ran one after
+    // another (a mixed batch with 287 MB of inverses: 34 + 34 us, now 60, 4.8 TB/s; 3.61 ->
+    // 3.53 ms for 12 iterations).
     STK_TRY(mg_coarse<T>(ctx, P.cjobs, P.ncj, P.maxcn));
     for (int d = P.depth - 1; d >= 0; --d) {
         const Batch& F = P.fine[d];
@@ -895,12 +894,28 @@ void free_plan(PlanT*& P) {
     P = nullptr;
 }
 
+// One launch for both components: a 2D copy each took two operations of the stream, and at
+// 1024^2 13 us for what moves in 8.
+template <typename U>
+__global__ __launch_bounds__(256) void k_copy_vel(int nx, int ny, const U* __restrict__ sx, const U* __restrict__ sy,
+                                                  int64_t sld, U* __restrict__ dx, U* __restrict__ dy, int64_t dld) {
+    const int nb = (nx + 64) / 64;  // workgroups across
+    const int i = (int)(blockIdx.x % nb) * 64 + (int)threadIdx.x, j = (int)(blockIdx.x / nb) * 4 + (int)threadIdx.y;
+    const int64_t s = (int64_t)j * sld + i, d = (int64_t)j * dld + i;
+    if (j < ny && i <= nx) dx[d] = sx[s];
+    if (j <= ny && i < nx) dy[d] = sy[s];
+}
+
 int copy_vel_in(stk_mg* m, const void* sx, const void* sy, int64_t sld, void* dx, void* dy, int64_t dld, size_t es) {
     const MgLevel& L = m->L[0];
-    STK_HIP(hipMemcpy2DAsync(dx, dld * es, sx, sld * es, (size_t)(L.nx + 1) * es, L.ny, hipMemcpyDeviceToDevice,
-                             m->ctx->stream));
-    STK_HIP(hipMemcpy2DAsync(dy, dld * es, sy, sld * es, (size_t)L.nx * es, L.ny + 1, hipMemcpyDeviceToDevice,
-                             m->ctx->stream));
+    const dim3 grid((unsigned)((L.nx + 64) / 64) * (unsigned)((L.ny + 4) / 4)), block(64, 4);
+    if (es == 8)
+        hipLaunchKernelGGL(k_copy_vel<uint64_t>, grid, block, 0, m->ctx->stream, L.nx, L.ny, (const uint64_t*)sx,
+                           (const uint64_t*)sy, sld, (uint64_t*)dx, (uint64_t*)dy, dld);
+    else
+        hipLaunchKernelGGL(k_copy_vel<uint32_t>, grid, block, 0, m->ctx->stream, L.nx, L.ny, (const uint32_t*)sx,
+                           (const uint32_t*)sy, sld, (uint32_t*)dx, (uint32_t*)dy, dld);
+    STK_HIP(hipGetLastError());
     return STK_OK;
 }
 

@@ -139,7 +139,6 @@ struct stk_mg {
     double* cainv = nullptr;
     stk::Field2 ks[2][stk::VS_N];  // finest-level slots: row 0 FP64 (all), row 1 FP32 (R, Z only)
     stk::Field2 zero[2];           // zero right-hand side for the operator apply
-    void* zero64 = nullptr;        // FP64 zeros (pressure of a p = 0 fold)
     bool have[2] = {false, false};
     std::vector<void*> mem;
     size_t bytes = 0;

@@ -63,6 +63,41 @@ int precondition(stk_ctx* ctx, const PlanT& P, const PlanT* P32, const stk_mg_op
     return run_vcycle(ctx, *P32, o, 1, io);
 }
 
+// A problem into the handle's vectors, from the caller's row stride (uld) to the level's:
+// X <- v, F <- f and B = f - G p (p null: f), B on the unknowns and 0 on the walls.
+//
+// Bound by its launch on small grids: copies of the four planes and of p, a pass for B and
+// an allocation for p's copy were five to seven operations of the stream an instance and
+// a wait (6 iterations at 112^2 with them 773 us, now 743; three mixed instances, 5
+// iterations: 1390 and 1354).
+constexpr int LX = 64, LY = 4;
+__global__ __launch_bounds__(LX* LY) void k_load(int nx, int ny, int64_t uld, int64_t ld, double idx, double idy,
+                                                 const double* __restrict__ vx, const double* __restrict__ vy,
+                                                 const double* __restrict__ p, const double* __restrict__ fx,
+                                                 const double* __restrict__ fy, double* __restrict__ X0,
+                                                 double* __restrict__ X1, double* __restrict__ F0,
+                                                 double* __restrict__ F1, double* __restrict__ B0,
+                                                 double* __restrict__ B1) {
+    const int nb = (nx + LX) / LX;  // workgroups across
+    const int i = (int)(blockIdx.x % nb) * LX + (int)threadIdx.x, j = (int)(blockIdx.x / nb) * LY + (int)threadIdx.y;
+    if (i > nx || j > ny) return;
+    const int64_t u = (int64_t)j * uld + i, k = (int64_t)j * ld + i;
+    const bool ux = j < ny && i >= 1 && i <= nx - 1, uy = i < nx && j >= 1 && j <= ny - 1;
+    const double pc = p && (ux || uy) ? p[u] : 0.0;
+    if (j < ny) {
+        const double f = fx[u], w = p && ux ? p[u - 1] : 0.0;
+        X0[k] = vx[u];
+        F0[k] = f;
+        B0[k] = ux ? f + (pc - w) * idx : 0.0;
+    }
+    if (i < nx) {
+        const double f = fy[u], s = p && uy ? p[u - uld] : 0.0;
+        X1[k] = vy[u];
+        F1[k] = f;
+        B1[k] = uy ? f + (pc - s) * idy : 0.0;
+    }
+}
+
 // The iterate's update, which also clears an FP64 Z for a plan that needs it.
 int update_op(const PlanT& P) { return P.fused ? OP_UPDATE_KEEP : OP_UPDATE; }
 
@@ -364,31 +399,15 @@ int stk_batch_add(stk_batch* b, stk_mg* m, double* vx, double* vy, const double*
     if (b->mode == STK_SOLVE_F32_REFINED) STK_TRY(ensure_dtype(m, 1));
     // x0 -> X, f -> F, b = f - G p -> B (FP64, the handle's layout)
     const MgLevel& L = m->L[0];
-    stk_grid g{L.nx, L.ny, L.ld, L.dx, L.dy};
     const Field2& X = m->ks[0][VS_X];
     const Field2& B = m->ks[0][VS_B];
     const Field2& F = m->ks[0][VS_F];
-    STK_TRY(copy_vel_in(m, vx, vy, m->user_ld, X.x, X.y, L.ld, 8));
-    STK_TRY(copy_vel_in(m, fx, fy, m->user_ld, F.x, F.y, L.ld, 8));
-    const void* pres = m->zero64;  // p = 0
-    void* ptmp = nullptr;
-    if (p) {  // the caller's pressure, restrided to the handle's layout
-        hipError_t e = hipMalloc(&ptmp, (size_t)L.ny * L.ld * 8);
-        if (e != hipSuccess) return set_error(STK_ENOMEM, "pressure staging: %s", hipGetErrorString(e));
-        e = hipMemcpy2DAsync(ptmp, L.ld * 8, p, m->user_ld * 8, (size_t)L.nx * 8, L.ny, hipMemcpyDeviceToDevice,
-                             ctx->stream);
-        if (e != hipSuccess) {
-            (void)hipFree(ptmp);
-            return hip_fail(e, "copy p");
-        }
-        pres = ptmp;
-    }
-    const int rc = launch_fold_rhs(ctx, STK_F64, &g, F.x, F.y, pres, B.x, B.y);
-    if (ptmp) {
-        (void)hipStreamSynchronize(ctx->stream);
-        (void)hipFree(ptmp);
-    }
-    if (rc) return rc;
+    const unsigned grid = (unsigned)((L.nx + LX) / LX) * (unsigned)((L.ny + LY) / LY);
+    hipLaunchKernelGGL(k_load, dim3(grid), dim3(LX, LY), 0, ctx->stream, L.nx, L.ny, m->user_ld, L.ld, 1.0 / L.dx,
+                       1.0 / L.dy, (const double*)vx, (const double*)vy, p, fx, fy, (double*)X.x, (double*)X.y,
+                       (double*)F.x, (double*)F.y, (double*)B.x, (double*)B.y);
+    STK_HIP(hipGetLastError());
+    if (p) STK_HIP(hipStreamSynchronize(ctx->stream));  // the caller may free p on return
     Slot& s = b->slots[id];
     s = Slot{};
     s.m = m;
