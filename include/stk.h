@@ -308,8 +308,8 @@ int stk_mg_footprint(const stk_grid* g, const stk_mg_opts* opts, int mode, size_
 /* One V(nu1, nu2)-cycle for M v = b on the finest level, in place on (vx, vy);
  * device arrays in the layout of the grid given at creation, dtype dt (FP32
  * uses FP32 copies of the viscosities and coarse stencils; the coarsest solve
- * is FP64).
- * Asynchronous. */
+ * is FP64).  (bx, by) may share memory with (vx, vy): b is then what the arrays
+ * hold when the call is made.  Asynchronous. */
 int stk_mg_vcycle(stk_mg* mg, stk_dtype dt, void* vx, void* vy, const void* bx, const void* by);
 
 /* Solve M v = f - G p to the velocity energy residual E_v = sqrt(N_v / N_f)

@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "coarse_stencil.hpp"
+#include "extents.hpp"
 #include "mg_host.hpp"
 #include "rowstream.hpp"
 
@@ -1128,7 +1129,12 @@ int stk_mg_vcycle(stk_mg* m, stk_dtype dt, void* vx, void* vy, const void* bx, c
     if (!m->plan[t]) STK_TRY(make_plan(ctx, &self, 1, t, &m->plan[t]));
     const size_t es = t ? 4 : 8;
     const int64_t ld0 = m->L[0].ld;
-    if (m->plan[t]->fused && m->user_ld == ld0) {  // the finest level's passes read and write the caller's arrays
+    // The finest level's passes read and write the caller's arrays, unless the velocity and the
+    // right-hand side share memory: the pass up reads b around the cells that it owns while other
+    // waves already store v.
+    const MgLevel& L0 = m->L[0];
+    if (m->plan[t]->fused && m->user_ld == ld0 &&
+        !velocity_shares(L0.nx, L0.ny, ld0, (int64_t)es, vx, vy, bx, by)) {
         FineIo io;
         io.vx = vx;
         io.vy = vy;
