@@ -135,7 +135,10 @@ void stk_smooth_opts_default(stk_smooth_opts* o);
  * `halo` cells (clipped to the domain) plus a one-cell frozen ring, runs k
  * Jacobi sweeps there, and writes back its owned cells only; all tiles read
  * the same snapshot, so the result is deterministic.  With halo >= k-1 this
- * equals k Jacobi sweeps exactly.  sweeps = 0 is a no-op.  Asynchronous.
+ * equals k Jacobi sweeps exactly.  sweeps = 0 is a no-op.  Without a pressure
+ * (fx, fy) may share memory with (vx, vy): f is then what the arrays hold when
+ * the call is made (RBGS: at each unknown, what it holds when it is relaxed).
+ * Asynchronous.
  * Errors: STK_EINVAL (bad sizes/pointers/options), STK_EUNSUPPORTED (RAS
  * tile plus halo exceeding the LDS budget), STK_ENOMEM, STK_EHIP. */
 int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy, const void* p,

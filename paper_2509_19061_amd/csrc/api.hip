@@ -7,6 +7,7 @@
 #include <cstring>
 #include <vector>
 
+#include "extents.hpp"
 #include "stk_internal.hpp"
 
 namespace stk {
@@ -274,8 +275,12 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
         f.bx = bx;
         f.by = by;
     }
+    // A right-hand side in the velocity's memory: a pass that stores v there would change b
+    // under the waves that still read it around their own cells, so the last pass goes to
+    // scratch too.  The half-sweeps read b at the unknown that they relax, and run on.
+    const bool shared = !p && velocity_shares(g->nx, g->ny, g->ld, (int64_t)elem_size(dt), vx, vy, fx, fy);
     const int kr = rbgs_pipe_sweeps(sweeps);
-    if (variant == STK_RBGS && !rbgs_has_scratch(ctx, dt, g, vbytes, (sweeps + kr - 1) / kr)) {
+    if (variant == STK_RBGS && (shared || !rbgs_has_scratch(ctx, dt, g, vbytes, (sweeps + kr - 1) / kr))) {
         STK_TRY(launch_zero_walls(ctx, dt, g, vx, vy));
         for (int s = 0; s < sweeps; ++s) STK_TRY(launch_rbgs(ctx, dt, g, f, omega, vx, vy));
         return STK_OK;
@@ -290,12 +295,12 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
 
     // Out-of-place steps: the first reads the caller's arrays, the last writes them, and the
     // ones between alternate over two scratch pairs, so no copy is needed for n >= 2 steps
-    // (two buffers alone would end an odd count in scratch).
+    // (two buffers alone would end an odd count in scratch).  Shared: all end in scratch.
     const int n = piped ? (total + kp - 1) / kp : ras ? nouter : sweeps;
     void *tx = nullptr, *ty = nullptr, *ux = nullptr, *uy = nullptr;
     STK_TRY(scratch(ctx, stk_ctx::S_VX, vbytes, &tx));
     STK_TRY(scratch(ctx, stk_ctx::S_VY, vbytes, &ty));
-    if (n >= 3) {
+    if (n >= (shared ? 2 : 3)) {
         STK_TRY(scratch(ctx, stk_ctx::S_VX2, vbytes, &ux));
         STK_TRY(scratch(ctx, stk_ctx::S_VY2, vbytes, &uy));
     }
@@ -303,7 +308,7 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
     int left = total;
     for (int t = 0; t < n; ++t) {
         void *dx = tx, *dy = ty;  // next
-        if (t == n - 1 && n >= 2) {
+        if (t == n - 1 && n >= 2 && !shared) {
             dx = vx;
             dy = vy;
         } else if (cx == tx) {

@@ -46,3 +46,44 @@ def test_vcycle(ctx, nx, ny, dtype, shared):
     torch.cuda.synchronize()
     m.close()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# one to three passes of the pipelined sweeps; thin overlap and tiles of one pass each
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("nx,ny", [(33, 20), (700, 500)])
+@pytest.mark.parametrize("variant,opts", [("jacobi", {}), ("jacobi_fused", {}), ("ras", {}),
+                                          ("ras", dict(k=4, halo=0, tile_x=32, tile_y=32))])
+@pytest.mark.parametrize("sweeps", [1, 4, 9, 21])
+def test_smooth(ctx, nx, ny, dtype, variant, opts, sweeps):
+    from paper_2509_19061_amd import api
+    p, d, v0 = problem(nx, ny, dtype)
+    for shared in SHARED:
+        out = []
+        for apart in (True, False):
+            v = [t.clone() for t in v0]
+            b = [f if s is None else v[s].clone() if apart else v[s] for s, f in zip(shared, (d.fx, d.fy))]
+            api.smooth(ctx, dtype, d.grid, *v, None, d.eta_c, d.eta_n, *b, sweeps, variant, **opts)
+            out.append(v)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), shared
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("nx,ny", [(33, 20), (300, 200)])
+def test_red_black_takes_the_running_values(ctx, nx, ny, dtype):
+    """f = v: the value of an unknown when it is relaxed, colour by colour."""
+    from gpu_util import normwise
+    from oracle import stokes as S
+    from paper_2509_19061_amd import api
+    p, d, v = problem(nx, ny, dtype)
+    ox, oy = d.get_vx(v[0]), d.get_vy(v[1])
+    (cx, cy), sweeps = d.velocity(ox, oy), 4
+    api.smooth(ctx, dtype, d.grid, cx, cy, None, d.eta_c, d.eta_n, d.fx, d.fy, sweeps, "rbgs")  # warms the scratch
+    api.smooth(ctx, dtype, d.grid, *v, None, d.eta_c, d.eta_n, *v, sweeps, "rbgs", omega=0.9)
+    torch.cuda.synchronize()
+    # an unknown is relaxed once a sweep and read by others, never by itself, so its value at
+    # that time is the one that the sweep starts from
+    for _ in range(sweeps):
+        ox, oy = S.rbgs(p, ox, oy, 0.9, ox, oy)
+    tol = 1e-12 if dtype == torch.float64 else sweeps * 1e-5
+    assert normwise(d.get_vx(v[0]), ox) <= tol and normwise(d.get_vy(v[1]), oy) <= tol
