@@ -12,9 +12,11 @@
 // and the columns i +- 1 come from neighbouring lanes (DPP).  The energy sums
 // accumulate per lane row by row, then over the wave's lanes (shuffles), one
 // triple per wave; one workgroup adds the triples in a fixed order, so the
-// result is bitwise reproducible.  The two quotients by a diagonal share its
-// reciprocal, and the sum of r_p^2 eta_c is divided once: with five FP64
-// divisions a cell the FP32 norm was bound by them (4096^2: 160 us, now 113).
+// result is bitwise reproducible.  The sum of r_p^2 eta_c is divided once, by the wave:
+// FP64 divisions bound the FP32 norm (a call at 4096^2: 161 us with five a cell and
+// 64-row segments, 127 with four and 16-row ones).  The quotients by a diagonal stay
+// divisions: the product with a reciprocal that both share takes 120 us there (FP64: the
+// same 175 us), but it rounds each quotient twice.
 #include <type_traits>
 
 #include "rowstream.hpp"
@@ -139,14 +141,14 @@ __global__ __launch_bounds__(64 * WPB) void k_energy(int nx, int ny, int64_t ld,
                           ycol && j >= 1 && j <= ny - 1 ? O(y) : O(0), s_x, s_y);
         }
         if (xcol && j <= ny - 1) {
-            const double f = b.bx, g = jac_factor(1.0, r.dx_);
-            nv += r.rx * r.rx * g;
-            nf += f * f * g;
+            const double f = b.bx;
+            nv += r.rx * r.rx / r.dx_;
+            nf += f * f / r.dx_;
         }
         if (ycol && j >= 1 && j <= ny - 1) {
-            const double f = b.by, g = jac_factor(1.0, r.dy_);
-            nv += r.ry * r.ry * g;
-            nf += f * f * g;
+            const double f = b.by;
+            nv += r.ry * r.ry / r.dy_;
+            nf += f * f / r.dy_;
         }
         if (ycol && j <= ny - 1) np += r.rp * r.rp * double(b.ec);
     });
