@@ -404,9 +404,9 @@ __global__ __launch_bounds__(ZNT) void k_walk3d(Fields3<T> f, T omega, const T* 
         const T mz = mvz3c<T>(f, v, i, j, k, Row3<T>{c.ecz, c.ec, sxz, sxz_x, syz, syz_y}, dz);
         if constexpr (OP == Z_ENERGY) {
             auto add = [&](bool in, T b, T m, T d) {  // a cell that holds no unknown adds 0
-                const double r = (double)b - (double)m, w = in ? 1.0 / (double)d : 0.0;
-                nv += in ? r * r * w : 0.0;
-                nf += in ? (double)b * (double)b * w : 0.0;
+                const double r = (double)b - (double)m, e = in ? (double)d : 1.0;
+                nv += in ? r * r / e : 0.0;
+                nf += in ? (double)b * (double)b / e : 0.0;
             };
             add(act && xi0, c.bx, mx, dx);
             add(act && yj0, c.by, my, dy);

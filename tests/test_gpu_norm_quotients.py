@@ -11,6 +11,8 @@ import pytest
 import torch
 
 from oracle import stokes as S
+from oracle import stokes3d as S3
+from paper_2509_19061_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +56,25 @@ def test_one_entry_2d(ctx, dx, dy, dtype):
                                 allow_nonfinite=True)
             o = S.energy(p, np.zeros_like(fx), np.zeros_like(fy), fx, fy)
             assert e[2] == o[2] and e[0] == o[0], (es, fs, n, e, o)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_one_entry_3d(ctx, dtype):
+    from paper_2509_19061_amd import api, fields
+    rng = np.random.default_rng(8)
+    nx, ny, nz = 4, 5, 3
+    for es, fs in SCALES[dtype]:
+        p = I.Problem3(nx, ny, nz, 0.25, 0.5, 0.125, whole(rng, (nz, ny, nx), es),
+                       whole(rng, (nz, ny + 1, nx + 1), es), whole(rng, (nz + 1, ny, nx + 1), es),
+                       whole(rng, (nz + 1, ny + 1, nx), es), np.zeros((nz, ny, nx + 1)), np.zeros((nz, ny + 1, nx)),
+                       np.zeros((nz + 1, ny, nx)))
+        d = fields.DeviceProblem3(p, dtype)
+        v = d.velocity()
+        for n in range(40):
+            f = [np.zeros_like(p.fx), np.zeros_like(p.fy), np.zeros_like(p.fz)]
+            at = [rng.integers(0, nz), rng.integers(0, ny), rng.integers(0, nx)]
+            at[2 - n % 3] = rng.integers(1, (nx, ny, nz)[n % 3])  # not on the component's walls
+            f[n % 3][tuple(at)] = float(torch.tensor(np.ldexp(rng.uniform(1.0, 2.0), fs), dtype=dtype))
+            e = api.energy_norm3d(ctx, dtype, d.grid, v, d.eta, d.velocity(f))
+            o = S3.energy(p, *(np.zeros_like(a) for a in f), *f)
+            assert e[1] == o[1] and e[0] == o[0], (es, fs, n, e, o)
