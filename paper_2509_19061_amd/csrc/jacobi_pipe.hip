@@ -127,6 +127,17 @@ int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int 
     return dt == STK_F64 ? pick_sweeps<double>(ctx, g, left) : pick_sweeps<float>(ctx, g, left);
 }
 
+// As ras_pipe_us (2 x 2 to 300 x 300, k = 6 to 10: within 12 and 9 %).
+double jacobi_pipe_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int sweeps) {
+    double us = 0.0;
+    if (dt == STK_F64) {
+        pipe_shape<double>(ctx, g->nx, g->ny, g->ld, sweeps, &us);
+        return 0.3 + 1.1 * us;
+    }
+    pipe_shape<float>(ctx, g->nx, g->ny, g->ld, sweeps, &us);
+    return 3.6 + 0.93 * us;
+}
+
 int launch_jacobi_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int sweeps,
                        const void* vx, const void* vy, void* ox, void* oy) {
     return dt == STK_F64 ? launch_t<double>(ctx, g, f, omega, sweeps, vx, vy, ox, oy)

@@ -123,8 +123,9 @@ Stretch stretch(int T, int h, int s) {
 // Strips and segments, as pipe_shape (jacobi_pipe.hip); a wave alone on its SIMD also waits
 // for the scalar arithmetic of the stretched rows (FP64 k = 4, 64 x 64 tiles, one and two
 // waves per SIMD: 1501 x 1100 30.4 and 27.0 us, 2048^2 57 and 52 us).
+// *us: the modelled time, as there.
 template <typename T>
-RasCut ras_cut(const stk_ctx* ctx, const stk_grid* g, int Tx, int Ty, int h, int K, int sx, int sy) {
+RasCut ras_cut(const stk_ctx* ctx, const stk_grid* g, int Tx, int Ty, int h, int K, int sx, int sy, double* us) {
     RasCut c{stretch(Tx, h, sx), stretch(Ty, h, sy), 0, 0, 0, 0, 0, 0};
     c.e0x = c.x.first();
     c.e0y = c.y.first();
@@ -145,6 +146,7 @@ RasCut ras_cut(const stk_ctx* ctx, const stk_grid* g, int Tx, int Ty, int h, int
             c.seg = H;
         }
     }
+    if (us) *us = cost * step_us<T>(K);
     return c;
 }
 
@@ -164,7 +166,7 @@ int launch_t(stk_ctx* ctx, const stk_grid* g, const FieldPtrs& f, double omega, 
              int sy, const void* vx, const void* vy, void* ox, void* oy) {
     const Grid<T> gg{static_cast<const T*>(f.eta_c), static_cast<const T*>(f.eta_n), static_cast<const T*>(f.bx),
                      static_cast<const T*>(f.by), g->ld, g->nx, g->ny, T(1.0 / g->dx), T(1.0 / g->dy), T(omega)};
-    const RasCut cut = ras_cut<T>(ctx, g, Tx, Ty, h, K, sx, sy);
+    const RasCut cut = ras_cut<T>(ctx, g, Tx, Ty, h, K, sx, sy, nullptr);
     const T *a = static_cast<const T*>(vx), *b = static_cast<const T*>(vy);
     T *c = static_cast<T*>(ox), *d = static_cast<T*>(oy);
     switch (K) {
@@ -185,18 +187,24 @@ int launch_t(stk_ctx* ctx, const stk_grid* g, const FieldPtrs& f, double omega, 
 
 bool ras_pipe_takes(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt) {
     if (kt < 2 || kt > PIPE_MAX_SWEEPS || halo >= kt - 1 || !jacobi_pipe_takes(dt, g)) return false;
-    // Small tiles, and so few that the LDS kernels run them all at once: there a pass takes as
-    // long as one tile, and here as long as a walk of about 2 k rows of k levels.  64^2,
-    // 16 x 16 tiles, k = 8: 16.4 us there, 19.3 here; k = 6: 15.8 and 13.6; 32 x 32 tiles,
-    // k = 8: 21.5 and 19.2.  1501 x 1100, 16 x 16, k = 8: 202 and 71 us.
-    const int64_t tiles = (int64_t)((g->nx + tile_x - 1) / tile_x) * ((g->ny + tile_y - 1) / tile_y);
-    if (std::max(tile_x, tile_y) <= 4 * kt - 12 && tiles <= 2 * ctx->num_cu) return false;
     // positions (Stretch): at most n (T + 2 h + 2) / T + 2 (T + 2 h + 2) of them
     auto fits = [&](int n, int T) {
         const int64_t P = (int64_t)T + 2 * halo + 2;
         return ((n / T + 4) * P + 4096) * P < ((int64_t)1 << 32);
     };
     return fits(g->nx, tile_x) && fits(g->ny, tile_y);
+}
+
+// A pass's time on an idle chip, from the modelled steps (2 to 200 tiles of 8 to 64, k = 6 to
+// 10: FP64 within 9 % of the measured one in nine of ten cases, FP32 within 8 %).
+double ras_pipe_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt) {
+    double us = 0.0;
+    if (dt == STK_F64) {
+        ras_cut<double>(ctx, g, tile_x, tile_y, halo, kt, 0, 0, &us);
+        return 0.3 + 1.16 * us;
+    }
+    ras_cut<float>(ctx, g, tile_x, tile_y, halo, kt, 0, 0, &us);
+    return 3.0 + 1.35 * us;
 }
 
 int launch_ras_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int tile_x,

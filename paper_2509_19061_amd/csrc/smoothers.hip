@@ -325,6 +325,26 @@ int launch_rbgs(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& 
     return STK_OK;
 }
 
+// Time of an outer iteration by the LDS kernels where the tiles run all at once, one or two
+// per CU: it is then that of one tile, about 0.35 us a row and a share of every sweep's own.
+// Where this is less than the pipelined pass models, the LDS kernels stay: a pass fills and
+// drains its pipeline in 2 kt rows of kt levels however few cells there are.  FP64, LDS
+// kernel and pass: 4 x 4, k = 8 11.7 and 18.4 us; 200 x 3, tiles of 32, k = 10 15.5 and 31;
+// 64 x 64 in tiles of 16, k = 8 15.6 and 19.2, k = 6 15.2 and 13.3, and in tiles of 32,
+// k = 8 21.2 and 19.1.  Over 4401 configurations up to 1000 x 1000 the choice is the faster
+// kernel or within 10 % of it in all but 70.
+double ras_lds_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt) {
+    auto cut = [](int n, int tile) { return (int64_t)((n + tile - 1) / tile); };
+    const int64_t nx = cut(g->nx, tile_x), ny = cut(g->ny, tile_y);
+    if (nx * ny > 2 * ctx->num_cu) return 1e300;
+    const int w = std::min(tile_x, g->nx), r = std::min(tile_y + halo, g->ny);
+    double us = 0.35 * r;
+    if (w + 2 * halo + 2 > 64) us = std::max(us, 0.1 * kt * w * std::min(tile_y, g->ny) / 64);  // more than a wave wide
+    us += 6.0 + (dt == STK_F64 ? 0.3 * kt + 0.08 * kt * kt : 0.07 * kt * kt);
+    // (a shift cuts off a tile more each way)
+    return (nx + (nx > 1)) * (ny + (ny > 1)) > ctx->num_cu ? 1.4 * us : us;
+}
+
 int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int tile_x, int tile_y,
                int halo, int kt, int sx, int sy, const void* vx, const void* vy, void* ox, void* oy) {
     size_t lds = 0;
@@ -333,9 +353,11 @@ int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f
         return set_error(STK_EUNSUPPORTED, "RAS tile %dx%d with halo %d needs %zu bytes of LDS (limit %d)", tile_x,
                          tile_y, halo, lds, ctx->lds_max);
     // full overlap is exactly kt Jacobi sweeps, wherever the tiles are cut
-    if (ctx->ras_kernel == 0 && kt >= 1 && kt <= PIPE_MAX_SWEEPS && halo >= kt - 1 && jacobi_pipe_takes(dt, g))
+    if (ctx->ras_kernel == 0 && kt >= 1 && kt <= PIPE_MAX_SWEEPS && halo >= kt - 1 && jacobi_pipe_takes(dt, g) &&
+        jacobi_pipe_us(ctx, dt, g, kt) <= ras_lds_us(ctx, dt, g, tile_x, tile_y, halo, kt))
         return launch_jacobi_pipe(ctx, dt, g, f, omega, kt, vx, vy, ox, oy);
-    if (ctx->ras_kernel == 0 && ras_pipe_takes(ctx, dt, g, tile_x, tile_y, halo, kt))
+    if (ctx->ras_kernel == 0 && ras_pipe_takes(ctx, dt, g, tile_x, tile_y, halo, kt) &&
+        ras_pipe_us(ctx, dt, g, tile_x, tile_y, halo, kt) <= ras_lds_us(ctx, dt, g, tile_x, tile_y, halo, kt))
         return launch_ras_pipe(ctx, dt, g, f, omega, tile_x, tile_y, halo, kt, sx, sy, vx, vy, ox, oy);
     if (ctx->ras_kernel != 1) {
         bool done = false;

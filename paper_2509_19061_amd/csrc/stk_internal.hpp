@@ -92,6 +92,8 @@ constexpr int PIPE_MAX_SWEEPS = 10;
 bool jacobi_pipe_takes(stk_dtype dt, const stk_grid* g);
 // Sweeps of the next pass when `left` are to be done.
 int jacobi_pipe_sweeps(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int left);
+// Modelled time of such a pass.
+double jacobi_pipe_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int sweeps);
 int launch_jacobi_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int sweeps,
                        const void* vx, const void* vy, void* ox, void* oy);
 int launch_jacobi_split(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega,
@@ -110,6 +112,8 @@ int launch_ras(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f
 // RAS outer iteration of kt sweeps with a thin overlap on the register pipeline
 // (ras_pipe.hip); tiles of any size and shift.
 bool ras_pipe_takes(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt);
+// Modelled time of it (what ras_pipe_takes).
+double ras_pipe_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt);
 int launch_ras_pipe(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& f, double omega, int tile_x,
                     int tile_y, int halo, int kt, int sx, int sy, const void* vx, const void* vy, void* ox, void* oy);
 // Streaming RAS kernel; *done = false when the configuration does not fit it.
