@@ -678,6 +678,28 @@ int64_t walk3d_groups(const stk_ctx* ctx, const stk_grid3* g, int* zs) {
     const int64_t nwg = nt * ((g->nz + *zs - 1) / *zs);
     return nwg < INT32_MAX && (uint64_t)(g->nz + 1) * (uint64_t)g->lp * sizeof(T) <= UINT32_MAX ? nwg : 0;
 }
+// Does an outer iteration of full overlap take less time by tiles than its kt sweeps by
+// the walk?  On small grids: a sweep walks zs planes one after the other whatever their
+// size, and a tile's kt sweeps stay in LDS behind one launch.  Modelled us a sweep, from
+// 2448 configurations up to 64^3 (tiles of 2 to 16, k = 1 to 6; the choice is more than
+// 10 % off in 32 and 27 of them); FP64, tiles of 8, k = 2, tiles and walk: 4^3 3.3 and
+// 10.1, 8^3 6.2 and 12.1, 16^3 15.8 and 10.0, 24^3 17.7 and 9.0; tiles of 4, k = 2: 24^3
+// 8.1 and 9.0, 40^3 18.5 and 9.1.
+template <typename T>
+bool tiles_faster3d(const stk_ctx* ctx, const stk_grid3* g, int tile, int h, int kt) {
+    int zs = 0;
+    const int64_t nwg = walk3d_groups<T>(ctx, g, &zs);
+    if (nwg == 0 || nwg > ctx->num_cu) return false;
+    double walk = sizeof(T) == 8 ? 2.5 + 1.65 * zs : 1.8 + 1.35 * zs;
+    if (g->nx <= 12) walk *= 1.2;  // most lanes load one place
+    double n = 1.0, w = 1.0;       // workgroups, cells of a tile's window
+    for (const int m : {g->nx, g->ny, g->nz}) {
+        n *= (m + tile - 1) / tile + 1;
+        w *= std::min(tile + 2 * h, m);
+    }
+    const double it = std::ceil(w / 256.0);
+    return 4.5 + it * (1.4 * kt + n / std::max(ctx->num_cu, 1) * 0.5 * (1 + kt)) < walk * kt;
+}
 template <typename T, int OP>
 void walk3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, int64_t nwg, int zs, double omega, const void* vx,
             const void* vy, const void* vz, void* ox, void* oy, void* oz, void* part) {
@@ -826,10 +848,16 @@ int stk_smooth3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, void* vx, void*
                                  stk_ctx::S_BY};
     for (int q = 0; q < 6; ++q) STK_TRY(scratch(ctx, slots[q], fb, &t[q]));
     // RAS with an overlap of at least k - 1 is exactly its sweeps of Jacobi, wherever the
-    // tiles are cut (the frozen ring, at distance k, enters only exact values), and a sweep
-    // of the plane-streaming kernel costs a seventh of a tile's: 87 against 610 us at
-    // 160 x 144 x 150 in FP64.
-    const bool tiles = variant == STK_RAS_JACOBI && o.halo >= 0 && o.halo < o.k - 1;
+    // tiles are cut (the frozen ring, at distance k, enters only exact values): by the walk,
+    // whose sweep takes a fifth of the tiles' (115 against 610 us at 160 x 144 x 150 in FP64,
+    // tiles of 8, k = 2), but on small grids.
+    bool tiles = false;
+    if (variant == STK_RAS_JACOBI) {
+        const int kt = std::min(o.k, sweeps), h = o.halo < 0 ? kt : o.halo;
+        tiles = (o.halo >= 0 && o.halo < o.k - 1) ||
+                (dt == STK_F64 ? tiles_faster3d<double>(ctx, g, o.tile, h, kt)
+                               : tiles_faster3d<float>(ctx, g, o.tile, h, kt));
+    }
     const int k = tiles ? o.k : 1;
     const int nsteps = (sweeps + k - 1) / k;
     std::vector<int32_t> sh;
@@ -864,9 +892,9 @@ int stk_smooth3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, void* vx, void*
         left -= kt;
         int rc;
         if (tiles) {
+            const int h = o.halo < 0 ? kt : o.halo;
             rc = stk_ras_outer3d(ctx, dt, g, src[0], src[1], src[2], eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz, dst[0],
-                                 dst[1], dst[2], o.omega, o.tile, o.halo, kt, sh[3 * st], sh[3 * st + 1],
-                                 sh[3 * st + 2]);
+                                 dst[1], dst[2], o.omega, o.tile, h, kt, sh[3 * st], sh[3 * st + 1], sh[3 * st + 2]);
         } else if (dt == STK_F64) {
             rc = launch_jacobi3d<double>(ctx, g, fields3<double>(g, eta_c, eta_xy, eta_xz, eta_yz, bx, by, bz), o.omega,
                                          src[0], src[1], src[2], dst[0], dst[1], dst[2]);
