@@ -33,10 +33,10 @@
 //                two buffers), k sweeps run there with a barrier between
 //                sweeps, the owned unknowns are written back; coefficients
 //                and right-hand side come from global memory (L2).
-//                The residual and the norms' sums take the same walk.
-//   k_energy3d   per-workgroup FP64 sums of r^2/d and f^2/d (arrays beyond 2^32
-//                bytes), summed in a fixed order by a second kernel
-//                (reproducible).
+//   k_residual3d, k_energy3d  residual, and per-workgroup FP64 sums of r^2/d and
+//                f^2/d, with every operand from global memory: for small grids and
+//                arrays beyond 2^32 bytes, the walk otherwise; the sums are added in a
+//                fixed order by another kernel (reproducible).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -724,11 +724,22 @@ int launch_jacobi3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, doubl
     return STK_OK;
 }
 
+// Workgroups of the walk for the residual and the norm, 0 where the gathering kernels take
+// them: also on small grids, whose cells they work on all at once while the walk goes from
+// plane to plane.  Up to 3 gathering workgroups per CU (a call, FP64, gathering and walk:
+// 4 x 4 x 64 23.0 and 27.5 us, 24^3 21.7 and 25.2, 80 x 80 x 10 23.5 and 26.9, 48^3 25.6 and
+// 25.6, 56^3 27.9 and 25.9, 64^3 36.9 and 26.9; FP32 48^3 23.4 and 24.3, 64^3 27.4 and 24.7).
+template <typename T>
+int64_t walk3d_groups_once(const stk_ctx* ctx, const stk_grid3* g, int* zs) {
+    const dim3 gr = grid3(g);
+    return (int64_t)gr.x * gr.y * gr.z <= 3 * ctx->num_cu ? 0 : walk3d_groups<T>(ctx, g, zs);
+}
+
 template <typename T>
 int launch_residual3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
                       const void* vz, void* rx, void* ry, void* rz) {
     int zs = 0;
-    if (const int64_t nwg = walk3d_groups<T>(ctx, g, &zs)) {
+    if (const int64_t nwg = walk3d_groups_once<T>(ctx, g, &zs)) {
         walk3d<T, Z_RESIDUAL>(ctx, g, f, nwg, zs, 1.0, vx, vy, vz, rx, ry, rz, nullptr);
     } else {
         hipLaunchKernelGGL(k_residual3d<T>, grid3(g), dim3(J3X, J3Y), 0, ctx->stream, f, (const T*)vx, (const T*)vy,
@@ -743,7 +754,7 @@ template <typename T>
 int launch_energy3d(stk_ctx* ctx, const stk_grid3* g, const Fields3<T>& f, const void* vx, const void* vy,
                     const void* vz, double* red) {
     int zs = 0;
-    const int64_t nwg = walk3d_groups<T>(ctx, g, &zs);
+    const int64_t nwg = walk3d_groups_once<T>(ctx, g, &zs);
     const dim3 gr = grid3(g);
     const int64_t npart = nwg ? nwg : (int64_t)gr.x * gr.y * gr.z;
     void* part = nullptr;

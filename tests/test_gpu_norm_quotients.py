@@ -58,11 +58,12 @@ def test_one_entry_2d(ctx, dx, dy, dtype):
             assert e[2] == o[2] and e[0] == o[0], (es, fs, n, e, o)
 
 
+# the second grid is large enough for the plane walk
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-def test_one_entry_3d(ctx, dtype):
+@pytest.mark.parametrize("nx,ny,nz", [(4, 5, 3), (3, 2, 769)])
+def test_one_entry_3d(ctx, nx, ny, nz, dtype):
     from paper_2509_19061_amd import api, fields
     rng = np.random.default_rng(8)
-    nx, ny, nz = 4, 5, 3
     for es, fs in SCALES[dtype]:
         p = I.Problem3(nx, ny, nz, 0.25, 0.5, 0.125, whole(rng, (nz, ny, nx), es),
                        whole(rng, (nz, ny + 1, nx + 1), es), whole(rng, (nz + 1, ny, nx + 1), es),
