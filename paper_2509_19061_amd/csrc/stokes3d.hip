@@ -851,6 +851,11 @@ int stk_smooth3d(stk_ctx* ctx, stk_dtype dt, const stk_grid3* g, void* vx, void*
     if (variant == STK_RAS_JACOBI && ras3d_lds(o.tile, o.halo < 0 ? o.k : o.halo, elem_size(dt)) > (size_t)ctx->lds_max)
         return set_error(STK_EUNSUPPORTED, "3D RAS tile does not fit in LDS");
     if (sweeps == 0) return STK_OK;
+    // given shifts are refused as an outer iteration refuses them, also where none is cut
+    if (variant == STK_RAS_JACOBI && o.shifts)
+        for (int64_t q = 0, n = 3 * (int64_t)((sweeps - 1) / o.k + 1); q < n; ++q)
+            if (o.shifts[q] % o.tile < 0)
+                return set_error(STK_EINVAL, "tile >= 1, halo >= 0, kt >= 1 and shifts >= 0 required");
     STK_TRY(use_device(ctx));
     // ping-pong through two scratch triples; the last step writes the caller's arrays
     const size_t fb = (size_t)(g->nz + 1) * (size_t)g->lp * elem_size(dt);
