@@ -138,6 +138,9 @@ void stk_smooth_opts_default(stk_smooth_opts* o);
  * equals k Jacobi sweeps exactly.  sweeps = 0 is a no-op.  Without a pressure
  * (fx, fy) may share memory with (vx, vy): f is then what the arrays hold when
  * the call is made (RBGS: at each unknown, what it holds when it is relaxed).
+ * Scratch: two velocity pairs at most; RBGS has two of its own, which the
+ * context keeps as the others, and works in place, without them, when the
+ * stream is being captured or no memory is left for them.
  * Asynchronous.
  * Errors: STK_EINVAL (bad sizes/pointers/options), STK_EUNSUPPORTED (RAS
  * tile plus halo exceeding the LDS budget), STK_ENOMEM, STK_EHIP. */

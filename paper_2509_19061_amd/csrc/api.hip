@@ -74,22 +74,30 @@ int energy_norm(stk_ctx* ctx, const stk_grid* g, const double* vx, const double*
     return read_energy(ctx, out);
 }
 
-// Can red-black Gauss-Seidel take the pipelined passes?  They are out of place; its
-// half-sweeps are in place and need no scratch, so they stay for what the passes cannot
-// do: rows too long, no memory left for the scratch arrays, or a stream being captured
-// (where none may be allocated) with a context that does not hold them yet.
-bool rbgs_has_scratch(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, size_t bytes, int passes) {
+// Scratch of red-black Gauss-Seidel's pipelined passes: t[0..1], and t[2..3] for three passes
+// or more; false where its half-sweeps, which are in place and need none, have to do: rows
+// too long, no memory left, or a stream being captured.  A captured call takes none whatever
+// the context holds: a graph must not name memory that a later, larger call frees.  For the
+// same reason the slots are its own: growing them takes nothing from a graph of other calls.
+bool rbgs_scratch(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, size_t bytes, int passes, void* t[4]) {
     if (!jacobi_pipe_takes(dt, g)) return false;
-    constexpr int slots[] = {stk_ctx::S_VX, stk_ctx::S_VY, stk_ctx::S_VX2, stk_ctx::S_VY2};
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    bool grown[4] = {};
     for (int q = 0; q < (passes >= 3 ? 4 : 2); ++q) {
-        if (ctx->slot_bytes[slots[q]] >= bytes) continue;
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        void* p = nullptr;
-        if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone ||
-            scratch(ctx, slots[q], bytes, &p) != STK_OK) {
-            (void)hipGetLastError();
-            return false;
-        }
+        grown[q] = ctx->slot_bytes[stk_ctx::S_RB + q] < bytes;
+        if (scratch(ctx, stk_ctx::S_RB + q, bytes, &t[q]) == STK_OK) continue;
+        (void)hipGetLastError();
+        for (int u = 0; u < q; ++u)  // of no use without this one
+            if (grown[u]) {
+                (void)hipFree(ctx->slot[stk_ctx::S_RB + u]);
+                ctx->slot[stk_ctx::S_RB + u] = nullptr;
+                ctx->slot_bytes[stk_ctx::S_RB + u] = 0;
+            }
+        return false;
     }
     return true;
 }
@@ -280,7 +288,8 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
     // scratch too.  The half-sweeps read b at the unknown that they relax, and run on.
     const bool shared = !p && velocity_shares(g->nx, g->ny, g->ld, (int64_t)elem_size(dt), vx, vy, fx, fy);
     const int kr = rbgs_pipe_sweeps(sweeps);
-    if (variant == STK_RBGS && (shared || !rbgs_has_scratch(ctx, dt, g, vbytes, (sweeps + kr - 1) / kr))) {
+    void* rb[4] = {};
+    if (variant == STK_RBGS && (shared || !rbgs_scratch(ctx, dt, g, vbytes, (sweeps + kr - 1) / kr, rb))) {
         STK_TRY(launch_zero_walls(ctx, dt, g, vx, vy));
         for (int s = 0; s < sweeps; ++s) STK_TRY(launch_rbgs(ctx, dt, g, f, omega, vx, vy));
         return STK_OK;
@@ -297,12 +306,14 @@ int stk_smooth(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, void* vx, void* vy
     // ones between alternate over two scratch pairs, so no copy is needed for n >= 2 steps
     // (two buffers alone would end an odd count in scratch).  Shared: all end in scratch.
     const int n = piped ? (total + kp - 1) / kp : ras ? nouter : sweeps;
-    void *tx = nullptr, *ty = nullptr, *ux = nullptr, *uy = nullptr;
-    STK_TRY(scratch(ctx, stk_ctx::S_VX, vbytes, &tx));
-    STK_TRY(scratch(ctx, stk_ctx::S_VY, vbytes, &ty));
-    if (n >= (shared ? 2 : 3)) {
-        STK_TRY(scratch(ctx, stk_ctx::S_VX2, vbytes, &ux));
-        STK_TRY(scratch(ctx, stk_ctx::S_VY2, vbytes, &uy));
+    void *tx = rb[0], *ty = rb[1], *ux = rb[2], *uy = rb[3];
+    if (!rbgs) {
+        STK_TRY(scratch(ctx, stk_ctx::S_VX, vbytes, &tx));
+        STK_TRY(scratch(ctx, stk_ctx::S_VY, vbytes, &ty));
+        if (n >= (shared ? 2 : 3)) {
+            STK_TRY(scratch(ctx, stk_ctx::S_VX2, vbytes, &ux));
+            STK_TRY(scratch(ctx, stk_ctx::S_VY2, vbytes, &uy));
+        }
     }
     const void *cx = vx, *cy = vy;  // current iterate
     int left = total;
