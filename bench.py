@@ -7,6 +7,9 @@ Step: 100 sweeps of RAS-Jacobi (tile 64 x 64, halo = k = 4, shift stream
 seed 3) through stk_smooth, followed by the energy norm (Sec. 6.4).
 Value: GLUP/s = cells x sweeps / step time (HIP events on the stream).
 
+stdout is one JSON line: the headline, its roofline and CPU baseline, and the
+main figures of the sections below; their full record is a line of stderr.
+
 Also reported: every smoother variant at 100 sweeps (Jacobi split, fused,
 RBGS, RAS k = 2, 4, 8 with halo k (= Jacobi^k) and with halo 0 (the paper's
 thin-overlap form), each with the energy residual reached after 100 sweeps
@@ -82,6 +85,33 @@ def ras_sources_hash():
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+# What the one line on stdout holds: the headline's keys whole, and of every other section the
+# figures named here.  (Whole, the line is 20 KB, and readers that keep the end of the output
+# lost its beginning.)  The full record goes to stderr.
+HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline", "ceiling", "wall_ms_per_step")
+FIGURES = {"glups", "solves_per_s", "iterations", "converged", "all_converged", "ms_per_iteration", "cycles",
+           "ms_per_cycle", "latency_p50_s", "latency_p99_s", "launch_ms"}
+
+
+def figures(section):
+    """The figures of a section, nested as there; parts without any are left out."""
+    out = {}
+    for k, v in section.items():
+        if isinstance(v, dict) and k != "by_size":
+            v = figures(v)
+            if v:
+                out[k] = v
+        elif k in FIGURES:
+            out[k] = v
+    return out
+
+
+def headline(record):
+    """The line of stdout for a full record."""
+    return {k: v if k in HEADLINE or not isinstance(v, dict) else figures(v) for k, v in record.items()}
 
 
 def main():
@@ -354,7 +384,8 @@ def main():
         "uzawa": uz,
         "fp64_floor": floor,
     }
-    print(json.dumps(out), flush=True)
+    log("[bench] full record: " + json.dumps(out))
+    print(json.dumps(headline(out)), flush=True)
     ctx.close()
 
 
