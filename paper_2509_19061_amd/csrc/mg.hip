@@ -545,8 +545,11 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     STK_TRY(upload(P, pe, &dpe));
                     P->rest_p[d] = Batch{dj, (const int*)dpe, (int)jobs.size(), pe.back()};
                 }
-                // The walk from 6 (down) and 16 (up) of the smaller regions per CU on: a 512^2
-                // level has 1849, 1024^2 7310, where both sides are measured (mg_pair.hip)
+                // The walk from 6 of the smaller regions per CU on (down), and from 16 in FP64 and
+                // 32 in FP32 (up).  What it adds to a V-cycle, in us, at 448^2, 512^2, 640^2, 768^2,
+                // 896^2, 1024^2 and 1280^2 (5.6, 7.2, 11.4, 16.5, 22, 29 and 45 regions per CU of
+                // 256): down FP64 0, -4, -4, -23, -29, -38, -53, FP32 1, 0, 0, -10, -12, -27, -51;
+                // up FP64 from 512^2 on 1, 0, -12, -13, -20, -40, FP32 11, 14, 6, 7, 1, -9.
                 if (ps.back() >= 6 * ctx->num_cu) {
                     std::vector<int> wx, wy, pw;
                     for (const LevelJob<T>& J : jobs) {
@@ -560,7 +563,7 @@ static int build_plan(stk_ctx* ctx, stk_mg* const* mgs, int n, int t, PlanT* P, 
                     STK_TRY(upload(P, pw, &dpw));
                     P->walk_p[d] = Batch{dj, (const int*)dpw, (int)jobs.size(), pw.back()};
                     P->walk_shapes[d] = static_cast<const FineShape*>(dsh);
-                    P->walk_up[d] = ps.back() >= 16 * ctx->num_cu;
+                    P->walk_up[d] = ps.back() >= (sizeof(T) == 8 ? 16 : 32) * ctx->num_cu;
                 }
             }
             if (d == 0) {  // the finest level is matrix-free: row-streaming smoothing and residual
