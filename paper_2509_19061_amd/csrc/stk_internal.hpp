@@ -154,7 +154,6 @@ int launch_copy_velocity(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const vo
 int launch_residual(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                     const void* eta_c, const void* eta_n, const void* fx, const void* fy, void* rx, void* ry,
                     void* rp);
-// Energy partial sums -> 3 doubles in device memory `dst` (N_v, N_p, N_f).
 // What the energy pass of an outer loop stores beside its sums, for the V-cycle that
 // follows from the same iterate: b = f - G p (doubles) or, f32, the residual in floats.
 struct EnergyOut {
@@ -168,6 +167,8 @@ int launch_energy_out(stk_ctx* ctx, const stk_grid* g, const double* vx, const d
 int energy_norm(stk_ctx* ctx, const stk_grid* g, const double* vx, const double* vy, const double* p,
                 const double* eta_c, const double* eta_n, const double* fx, const double* fy, double out[5],
                 const EnergyOut& o);
+// N_v, N_p, N_f into the 3 doubles at dst, which the device can write (device memory, or
+// the device address of pinned host memory).
 int launch_energy(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const void* vx, const void* vy, const void* p,
                   const void* eta_c, const void* eta_n, const void* fx, const void* fy, double* dst);
 // Triples of partial sums the energy kernel writes for grid g.
