@@ -3,6 +3,7 @@
 // temporally blocked Jacobi (paper Sec. 4, Sec. 5, Alg. 2), plus the
 // right-hand-side fold b = f - G p and a velocity copy.
 #include <algorithm>
+#include <cmath>
 
 #include "stencil.hpp"
 #include "stk_internal.hpp"
@@ -331,15 +332,18 @@ int launch_rbgs(stk_ctx* ctx, stk_dtype dt, const stk_grid* g, const FieldPtrs& 
 // drains its pipeline in 2 kt rows of kt levels however few cells there are.  FP64, LDS
 // kernel and pass: 4 x 4, k = 8 11.7 and 18.4 us; 200 x 3, tiles of 32, k = 10 15.5 and 31;
 // 64 x 64 in tiles of 16, k = 8 15.6 and 19.2, k = 6 15.2 and 13.3, and in tiles of 32,
-// k = 8 21.2 and 19.1.  Over 4401 configurations up to 1000 x 1000 the choice is the faster
-// kernel or within 10 % of it in all but 70.
+// k = 8 21.2 and 19.1.  Over 6093 configurations up to 1000 x 1000 the choice is the faster
+// kernel or within 10 % of it in all but 136, and within 25 % in all but 17.
 double ras_lds_us(const stk_ctx* ctx, stk_dtype dt, const stk_grid* g, int tile_x, int tile_y, int halo, int kt) {
     auto cut = [](int n, int tile) { return (int64_t)((n + tile - 1) / tile); };
     const int64_t nx = cut(g->nx, tile_x), ny = cut(g->ny, tile_y);
     if (nx * ny > 2 * ctx->num_cu) return 1e300;
     const int w = std::min(tile_x, g->nx), r = std::min(tile_y + halo, g->ny);
     double us = 0.35 * r;
-    if (w + 2 * halo + 2 > 64) us = std::max(us, 0.1 * kt * w * std::min(tile_y, g->ny) / 64);  // more than a wave wide
+    if (w + 2 * halo + 2 > 64) {  // more than a wave wide: by area (100 x 30, k = 8 45 us; 90 x 8, k = 10 9.7)
+        const double area = (double)w * std::min(tile_y, g->ny);
+        us = std::max(us, 0.1 * kt * area / 64 * std::sqrt(std::min(1.0, area / 3000)));
+    }
     us += 6.0 + (dt == STK_F64 ? 0.3 * kt + 0.08 * kt * kt : 0.07 * kt * kt);
     // (a shift cuts off a tile more each way)
     return (nx + (nx > 1)) * (ny + (ny > 1)) > ctx->num_cu ? 1.4 * us : us;
