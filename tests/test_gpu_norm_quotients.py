@@ -58,6 +58,46 @@ def test_one_entry_2d(ctx, dx, dy, dtype):
             assert e[2] == o[2] and e[0] == o[0], (es, fs, n, e, o)
 
 
+@pytest.mark.parametrize("nx,ny,length", [(2, 2, 1.0), (63, 40, 1.0), (300, 517, 1.0), (130, 60, 2.0 ** -37),
+                                          (61, 65, 2.0 ** 25)])
+@pytest.mark.parametrize("contrast", [1.0, 1e6])
+def test_fp32_fields_have_the_norms_of_the_same_fields_in_fp64(ctx, nx, ny, length, contrast):
+    """Sums and quotients are FP64 for both, in one order, so N_v, N_p and N_f are the same bits
+    on cells of any size, and where a field is 0, infinite or not a number."""
+    from paper_2509_19061_amd import api, fields
+    rng = np.random.default_rng(nx + ny)
+
+    def f32(a):
+        return np.asarray(a, np.float32).astype(np.float64)
+
+    eta_c = f32(np.exp(rng.uniform(0, np.log(contrast) + 1e-9, (ny, nx))))
+    eta_n = f32(np.exp(rng.uniform(0, np.log(contrast) + 1e-9, (ny + 1, nx + 1))))
+    p = SimpleNamespace(nx=nx, ny=ny, dx=length / nx, dy=length / ny, eta_c=eta_c, eta_n=eta_n,
+                        fx=f32(rng.standard_normal((ny, nx + 1))), fy=f32(rng.standard_normal((ny + 1, nx))))
+    vx, vy = f32(rng.standard_normal((ny, nx + 1))), f32(rng.standard_normal((ny + 1, nx)))
+    pr = f32(rng.standard_normal((ny, nx)))
+    for case in ("plain", "zeros", "inf force", "nan velocity", "zero viscosity", "inf viscosity"):
+        q = SimpleNamespace(**vars(p))
+        x = vx.copy()
+        q.fx, q.eta_c, q.eta_n = p.fx.copy(), p.eta_c.copy(), p.eta_n.copy()
+        if case == "zeros":
+            x[:], q.fx[:] = 0.0, 0.0
+        elif case == "inf force":
+            q.fx[ny // 2, 1] = np.inf
+        elif case == "nan velocity":
+            x[ny // 2, 1] = np.nan
+        elif case == "zero viscosity":
+            q.eta_c[:], q.eta_n[:] = 0.0, 0.0
+        elif case == "inf viscosity":
+            q.eta_c[0, 0] = np.inf
+        out = []
+        for dtype in (torch.float32, torch.float64):
+            d = fields.DeviceProblem(q, dtype)
+            out.append(api.energy_norm(ctx, dtype, d.grid, *d.velocity(x, vy), d.field(pr), d.eta_c, d.eta_n, d.fx,
+                                       d.fy, allow_nonfinite=True))
+        np.testing.assert_array_equal(out[0], out[1], err_msg=case)
+
+
 # the second grid is large enough for the plane walk
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("nx,ny,nz", [(4, 5, 3), (3, 2, 769)])
