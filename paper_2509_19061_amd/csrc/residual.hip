@@ -16,7 +16,7 @@
 // FP64 divisions bound the FP32 norm (a call at 4096^2: 161 us with five a cell and
 // 64-row segments, 127 with four and 16-row ones).  The quotients by a diagonal stay
 // divisions: the product with a reciprocal that both share takes 120 us there (FP64: the
-// same 175 us), but it rounds each quotient twice.
+// same 175 us) but rounds each quotient twice, and corrected by its residual 128.
 #include <type_traits>
 
 #include "rowstream.hpp"
